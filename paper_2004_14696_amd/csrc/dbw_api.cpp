@@ -60,6 +60,11 @@ struct dbw_ctx {
   // single pass with several slabs per worker): source and column tiles
   int slab_src = 0;
   int64_t slab_nblocks = 0;
+  // dbw_step with g_rows SELECTED on the small-class GEMM path: the gradient
+  // kernels write every row to Ga and the PS kernel copies the selected ones
+  // to G (the choice is made in that kernel, after the gradients)
+  bool copy_rows = false;
+  float* Ga = nullptr;           // [n][P] rows dbw_step aggregates (G, or its own buffer)
 
   char* pool = nullptr;
   // device buffers (carved from pool)
@@ -80,6 +85,8 @@ struct dbw_ctx {
   int32_t* err = nullptr;
   float* Gp = nullptr;
   float* lossp = nullptr;
+  dbw::sg_u32x4* Wp = nullptr;
+  dbw::sg_u32x4* Rp = nullptr;
   float* Z = nullptr;
   float* ce = nullptr;
   float* sqpart = nullptr;
@@ -457,7 +464,7 @@ dbw_status launch_grads(dbw_ctx* c, const float* w, const float* X, const int32_
     a.W = w; a.X = X; a.y = y; a.rows = rows; a.S = cf.S;
     a.n = cf.n; a.B = cf.B; a.d = cf.d; a.C = cf.C;
     a.G = G; a.loss = loss;
-    a.Gp = c->Gp; a.lossp = c->lossp; a.Z = c->Z; a.ce = c->ce;
+    a.Gp = c->Gp; a.lossp = c->lossp; a.Wp = c->Wp; a.Rp = c->Rp; a.Z = c->Z; a.ce = c->ce;
     a.err = c->err;
     a.keep_slabs = keep_slabs ? 1 : 0;
     a.row_mask = row_mask;
@@ -558,9 +565,11 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
   c->agg_nblocks = dbw::agg_blocks(P);
   if (cf.g_rows != DBW_G_ROWS_ALL && cf.model == DBW_SOFTMAX && c->splan.fused && c->splan.slabs > 1 &&
       c->splan.part % 4 == 0 && dbw::agg_blocks(c->splan.part) <= dbw::kStepPsMaxBlocks) {
-    c->slab_src = c->splan.fused == 2 ? dbw::SRC_SLAB_TILES : dbw::SRC_SLABS;
+    c->slab_src = dbw::SRC_SLAB_TILES;
     c->slab_nblocks = dbw::agg_blocks(c->splan.part);
   }
+  c->copy_rows = cf.g_rows == DBW_G_ROWS_SELECTED && cf.model == DBW_SOFTMAX && !c->splan.fused && cf.C <= 16 &&
+                 c->agg_nblocks <= dbw::kStepPsMaxBlocks;
   const int64_t part_blocks = std::max(c->agg_nblocks, c->slab_nblocks);
 
   // workspace layout
@@ -579,7 +588,9 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
        sSel = take(sizeof(int32_t) * n), sTicks = take(sizeof(int64_t) * n),
        sSt = take(sizeof(dbw_estimator_state)), sErr = take(4),
        sSqp = take(sizeof(float) * n * part_blocks), sPart = take(sizeof(double) * 2 * part_blocks);
-  Span sGp, sLp, sZ, sCe, sH, sdA, sH1, sC1, sF, sC2, sYl, sdP2, sdP1, sPa1, sPa2;
+  Span sGa;
+  if (c->copy_rows) sGa = take(sizeof(float) * n * P);
+  Span sGp, sLp, sWp, sRp, sZ, sCe, sH, sdA, sH1, sC1, sF, sC2, sYl, sdP2, sdP1, sPa1, sPa2;
   if (cf.model == DBW_SOFTMAX) {
     if (c->splan.fused) {
       if (c->splan.slabs > 1) {
@@ -587,7 +598,9 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
         sLp = take(sizeof(float) * n * c->splan.slabs);
       }
     } else {
-      sZ = take(sizeof(float) * rowsN * cf.C);
+      sWp = take(c->splan.w_bytes);
+      sRp = take(c->splan.r_bytes);
+      sZ = take(sizeof(float) * c->splan.z_floats);
       sCe = take(sizeof(float) * rowsN);
     }
   } else {
@@ -618,7 +631,9 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
   c->objective = (double*)at(sObj); c->k = (int32_t*)at(sK); c->b = (int32_t*)at(sB);
   c->sel = (int32_t*)at(sSel); c->ticks = (int64_t*)at(sTicks); c->st = (dbw_estimator_state*)at(sSt);
   c->err = (int32_t*)at(sErr); c->sqpart = (float*)at(sSqp); c->part = (double*)at(sPart);
+  c->Ga = c->copy_rows ? (float*)at(sGa) : c->G;
   c->Gp = (float*)at(sGp); c->lossp = (float*)at(sLp);
+  c->Wp = (dbw::sg_u32x4*)at(sWp); c->Rp = (dbw::sg_u32x4*)at(sRp);
   c->Z = (float*)at(sZ); c->ce = (float*)at(sCe); c->Hh = (float*)at(sH); c->dA = (float*)at(sdA);
   c->cH1 = (float*)at(sH1); c->cCode1 = (uint8_t*)at(sC1); c->cF = (float*)at(sF); c->cCode2 = (uint8_t*)at(sC2);
   c->cYlab = (int32_t*)at(sYl); c->cdP2 = (float*)at(sdP2); c->cdP1 = (float*)at(sdP1);
@@ -816,7 +831,7 @@ DBW_API dbw_status dbw_step(dbw_ctx* c, float* w, const float* X, const int32_t*
                           (c->cfg.model == DBW_SOFTMAX || c->cfg.g_rows == DBW_G_ROWS_SELECTED);
   // 0. worker gradients first (see above)
   if (!mask_first)
-    if (dbw_status s = launch_grads(c, w, X, y, rows, c->G, loss, slab); s != DBW_OK) return s;
+    if (dbw_status s = launch_grads(c, w, X, y, rows, c->Ga, loss, slab); s != DBW_OK) return s;
   // 1. T_hat_t in the pinned slot: solved by the worker since k_{t-2} became
   //    known, or here when no job was posted (first step of a history)
   {
@@ -870,8 +885,9 @@ DBW_API dbw_status dbw_step(dbw_ctx* c, float* w, const float* X, const int32_t*
     ca.do_choose = 1; ca.do_select = 1; ca.k_out = c->k; ca.b_out = c->b;
     ca.objective = c->objective; ca.sel = c->sel; ca.mask = c->mask; ca.err = c->err;
     dbw::AggArgs aa{};
-    aa.G = c->G; aa.P = c->P; aa.n = n; aa.sel = c->sel; aa.k_dev = c->k; aa.g_out = c->g; aa.w = w;
+    aa.G = c->Ga; aa.P = c->P; aa.n = n; aa.sel = c->sel; aa.k_dev = c->k; aa.g_out = c->g; aa.w = w;
     aa.eta = static_cast<float>(c->cfg.eta); aa.sqpart = c->sqpart; aa.part = c->part; aa.mode = dbw::AGG_FUSED;
+    if (c->copy_rows) aa.G_rows = c->G;
     if (slab) {
       aa.src = c->slab_src; aa.Gp = c->Gp; aa.slabs = c->splan.slabs; aa.slab_len = c->splan.part;
       aa.d = c->cfg.d; aa.C = c->cfg.C; aa.B = c->cfg.B; aa.lossp = c->lossp; aa.loss = loss;

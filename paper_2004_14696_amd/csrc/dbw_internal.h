@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "dbw.h"
+#include "split_gemm.h"
 
 namespace dbw {
 
@@ -29,13 +30,17 @@ inline int64_t agg_blocks(int64_t P) { return (P + AGG_TILE - 1) / AGG_TILE; }
 // ---------------------------------------------------------------------------
 // Worker-gradient plans.
 struct SoftmaxPlan {
-  int fused = 0;          // 2: matrix-core single pass; 1: VALU single pass; 0: GEMM path
-  int threads = 0;        // fused: threads per block
-  int per_thread = 0;     // fused 1: d-elements per thread (M); fused 2: float4 groups per lane (U)
+  int fused = 0;          // 1: single pass over X; 0: GEMM path
+  int per_thread = 0;     // fused: float4 groups per lane (U)
   int cpad = 0;           // fused: class template (>= C)
   int slabs = 1;          // fused: row slabs per worker
   int rows_per_slab = 0;
   int64_t part = 0;       // floats of one slab partial (fused, slabs > 1)
+  // GEMM path (per_thread: 16-column tiles of a wave)
+  int tiles = 0;          // 16-column tiles of all classes, a multiple of per_thread
+  int64_t w_bytes = 0;    // W and the residuals as product fragments
+  int64_t r_bytes = 0;
+  int64_t z_floats = 0;   // logits, where a wave does not hold all classes
 };
 
 struct MlpPlan {
@@ -61,7 +66,9 @@ struct SoftmaxArgs {
   // workspace
   float* Gp;             // [n*slabs][d*C] slab partials (fused, slabs > 1)
   float* lossp;          // [n*slabs]
-  float* Z;              // [n*B][C] logits / residuals (GEMM path)
+  sg_u32x4* Wp;             // W as product fragments (GEMM path)
+  sg_u32x4* Rp;             // the residuals as product fragments, by worker (GEMM path)
+  float* Z;              // [n*B][C] logits (GEMM path, more than one column chunk)
   float* ce;             // [n*B] per-row CE (GEMM path)
   int32_t* err;
   int keep_slabs;        // 1: leave the slab partials for the PS kernel (no slab reduction)
@@ -180,18 +187,18 @@ struct AggArgs {
   int mode;
   // k_step_ps only: where worker j's gradient row comes from
   int src;              // AggSrc
-  const float* Gp;      // SRC_SLABS*: slab partials, worker j's slab q at (j slabs + q) slab_len
+  const float* Gp;      // SRC_SLAB_TILES: slab partials, worker j's slab q at (j slabs + q) slab_len
   int slabs;
   int64_t slab_len;     // floats of one slab partial (a multiple of 4)
   int d, C, B;
   const float* lossp;   // [n][slabs] slab loss sums -> loss[n] (the mean over B)
   float* loss;
-  float* G_rows;        // nullable: the selected rows are written here in [d][C] order
+  float* G_rows;        // nullable (k_step_ps): the selected rows are written here in [d][C] order
 };
 // Gradient rows of k_step_ps: the G rows themselves, or the sum of a worker's
-// slab partials in slab order, laid out as [d][C] or in the matrix-core
-// kernel's tile order (64-feature groups; see k_softmax.hip).
-enum AggSrc { SRC_ROWS = 0, SRC_SLABS = 1, SRC_SLAB_TILES = 2 };
+// slab partials in slab order, laid out in the single-pass kernel's tile order
+// (64-feature groups; see k_softmax.hip).
+enum AggSrc { SRC_ROWS = 0, SRC_SLAB_TILES = 1 };
 hipError_t launch_aggregate(const AggArgs& a, hipStream_t s);
 // Choice, selection by the host-sorted arrival order, and fused aggregation
 // in one launch (dbw_step); ca.order_src must be set.  Used up to this many

@@ -329,10 +329,8 @@ __device__ __forceinline__ int col_index(int lane, int q) {
 // 16 g + 4 t + jq, t = 0..3.
 // (Elements and columns fit 32 bits: a worker's partials are addressed by
 // one buffer descriptor, below 2^32 bytes.)
-template <int SRC>
 __device__ __forceinline__ int slab_column(const AggArgs& a, int e) {
   if (e >= a.slab_len) return -1;
-  if (SRC == SRC_SLABS) return e < a.P ? e : -1;
   const int C = a.C;
   const int grp = e / (64 * C);
   const int r = e - grp * 64 * C;
@@ -345,12 +343,11 @@ __device__ __forceinline__ int slab_column(const AggArgs& a, int e) {
 // Columns of w of the lane's four elements e0 .. e0 + 3 (-1: padding or
 // past the partial) and the mask of those that are columns.  The same for
 // every row, so taken once.
-template <int SRC>
 __device__ __forceinline__ int slab_lane_cols(const AggArgs& a, int e0, int (&col)[4]) {
   int m = 0;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    col[t] = slab_column<SRC>(a, e0 + t);
+    col[t] = slab_column(a, e0 + t);
     if (col[t] >= 0) m |= 1 << t;
   }
   return m;
@@ -426,8 +423,8 @@ __device__ __forceinline__ void agg_load_round(const AggArgs& a, const int32_t* 
   }
 }
 
-// Shifted sums of the loaded rows, and their squared norms; from slab
-// partials, the rows are also stored in [d][C] order when G_rows is set.
+// Shifted sums of the loaded rows, and their squared norms; the rows are also
+// stored in [d][C] order when G_rows is set (columns ocol, where vmask).
 template <int MODE, int SRC = SRC_ROWS, int U = AGG_U>
 __device__ __forceinline__ void agg_accumulate(const AggArgs& a, const float (&x)[U][4], const int (&jj)[U],
                                                const float (&c)[4], float (&s1)[4], float (&s2)[4],
@@ -436,7 +433,7 @@ __device__ __forceinline__ void agg_accumulate(const AggArgs& a, const float (&x
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     if (jj[u] < 0) break;
-    if (SRC != SRC_ROWS && a.G_rows) {
+    if (a.G_rows) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if (vmask >> q & 1) a.G_rows[(int64_t)jj[u] * a.P + ocol[q]] = x[u][q];
@@ -476,7 +473,7 @@ __device__ void agg_finish(const AggArgs& a, int k, const float (&c)[4], const f
 
   const int64_t col = base + tid;
   // slab layouts: the element's column of w (-1 at padding, whose sums are 0)
-  const int64_t out = SRC == SRC_ROWS ? col : slab_column<SRC>(a, static_cast<int>(col));
+  const int64_t out = SRC == SRC_ROWS ? col : slab_column(a, static_cast<int>(col));
   const int64_t ncol = SRC == SRC_ROWS ? P : a.slab_len;
   const float kf = static_cast<float>(k);
   double m2 = 0.0, g2 = 0.0;
@@ -676,7 +673,7 @@ __global__ __launch_bounds__(STEP_PS_WAVES * WAVE) void k_step_ps(ChooseArgs ca,
   load_state(ca.st, &cs.st);
   const int64_t col = (int64_t)blockIdx.x * AGG_TILE + tid;
   int64_t wcol = col < a.P ? col : -1;
-  if (SRC != SRC_ROWS) wcol = slab_column<SRC>(a, static_cast<int>(col));
+  if (SRC != SRC_ROWS) wcol = slab_column(a, static_cast<int>(col));
   const float w_old = tid < AGG_TILE && wcol >= 0 && a.w ? a.w[wcol] : 0.f;
   const bool given = inl.n_inline == n;
   for (int i = tid; i < n; i += blockDim.x) {
@@ -695,7 +692,16 @@ __global__ __launch_bounds__(STEP_PS_WAVES * WAVE) void k_step_ps(ChooseArgs ca,
   // the first rows of the arrival order are loaded while the choice runs
   // (k_t >= 1 rows are needed; rows past k_t are dropped)
   int ocol[4];
-  const int vmask = SRC == SRC_ROWS ? 0 : slab_lane_cols<SRC>(a, static_cast<int>(blockIdx.x) * AGG_TILE + lane * 4, ocol);
+  int vmask = 0;
+  if (SRC == SRC_ROWS) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      ocol[q] = static_cast<int>(blockIdx.x) * AGG_TILE + col_index<VEC4>(lane, q);
+      if (ocol[q] < a.P) vmask |= 1 << q;
+    }
+  } else {
+    vmask = slab_lane_cols(a, static_cast<int>(blockIdx.x) * AGG_TILE + lane * 4, ocol);
+  }
   float c[4];
   agg_shift<VEC4, AGG_FUSED, SRC, S>(a, sh_order, c, vmask);
   float x[RU][4];
@@ -947,8 +953,7 @@ hipError_t launch_step_ps(const ChooseArgs& ca, const AggArgs& a, const StepInli
     // slab partials: float4 pieces of 4 consecutive elements
     if (a.slab_len % 4 != 0 || !a.Gp || !a.lossp || !a.loss || a.slabs < 1) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(agg_blocks(a.slab_len)));
-    if (a.src == SRC_SLAB_TILES) launch_step_ps_slabs<SRC_SLAB_TILES>(ca, a, inl, grid, block, s);
-    else launch_step_ps_slabs<SRC_SLABS>(ca, a, inl, grid, block, s);
+    launch_step_ps_slabs<SRC_SLAB_TILES>(ca, a, inl, grid, block, s);
     return hipGetLastError();
   }
   const dim3 grid(static_cast<unsigned>(agg_blocks(a.P)));

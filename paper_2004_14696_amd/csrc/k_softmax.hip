@@ -6,16 +6,14 @@
 //   loss_i = (1/B) sum_b (logsumexp(z_b) - z_{b,y_b})
 //
 // Two implementations:
-//  * k_softmax_fused -- small C (<= 16): one pass over X.  Each thread owns a
-//    strided slice of the feature dimension and keeps both its slice of W
-//    and of the gradient accumulator in registers.  Rows stream through in
-//    chunks of R: per-thread partial logits are reduced across the block
-//    through LDS, R threads run the softmax, and every thread folds the
-//    residuals into its accumulator.  A worker's rows are split over
-//    `slabs` blocks (to fill the 256 CUs); a second kernel sums the slab
+//  * k_softmax_mfma -- small C (<= 16), large minibatches: one pass over X
+//    (each wave keeps its slice of the features and of the gradient in
+//    registers; rows stream through in chunks).  A worker's rows are split
+//    over `slabs` blocks to fill the 256 CUs; a second kernel sums the slab
 //    partials in a fixed order.
-//  * GEMM path -- any C: logits Z = X W (tiled fp32 GEMM), row softmax in
-//    place (residuals), then a per-worker GEMM G_i = X_i^T R_i.
+//  * GEMM path -- everything else: logits Z = X W, row softmax (residuals), then
+//    a per-worker product G_i = X_i^T R_i, on the bf16 matrix cores with every
+//    fp32 operand in three parts (split_gemm.h).
 //
 // Minibatch rows are read either from a materialised X [n][B][d] or by row
 // index from a resident dataset; both read each sample once per pass.
@@ -27,7 +25,7 @@
 
 #include "dbw_buffer.h"
 #include "dbw_internal.h"
-#include "mfma_gemm.h"
+#include "split_gemm.h"
 
 namespace dbw {
 namespace {
@@ -74,168 +72,6 @@ __device__ __forceinline__ int64_t xcd_logical(int64_t b, int64_t per_xcd) {
 }
 
 constexpr int FUSED_MAX_ROWS = 1024;   // rows of one slab staged in LDS
-
-template <int CP, int M, int T, int R>
-__global__ __launch_bounds__(T) void k_softmax_fused(SoftmaxArgs a, int slabs, int rps, int64_t per_xcd) {
-  constexpr int V = R * CP;            // partial logits per thread
-  constexpr int G = T / V;             // reduction groups (>= 1)
-  static_assert(G >= 1, "block too small for the chunk");
-  static_assert(R == 4 && CP <= 16, "softmax wave layout: 4 rows x 16 lanes");
-  __shared__ float red[T][V + 1];
-  __shared__ float red2[G][V];
-  __shared__ float rr[V];
-  __shared__ float sh_loss[R];
-  __shared__ int sh_row[FUSED_MAX_ROWS];
-  __shared__ int sh_lab[FUSED_MAX_ROWS];
-
-  const int64_t logical = xcd_logical(blockIdx.x, per_xcd);
-  if (logical >= (int64_t)a.n * slabs) return;
-  const int i = static_cast<int>(logical / slabs);
-  const int q = static_cast<int>(logical % slabs);
-  const int tid = threadIdx.x;
-  const int d = a.d, C = a.C;
-  const int64_t P = (int64_t)d * C;
-  const int b0 = q * rps;
-  const int b1 = min(a.B, b0 + rps);
-  const int nrows = b1 - b0;
-
-  // the slab's row indices and labels, validated once
-  for (int r = tid; r < nrows; r += T) {
-    const int64_t row = sample_row(a, i, b0 + r, true);
-    sh_row[r] = static_cast<int>(row);
-    sh_lab[r] = sample_label(a, row, true);
-  }
-
-  // this thread's slice of W; features j >= d and classes c >= C read as 0
-  const __amdgpu_buffer_rsrc_t wrs = make_rsrc(a.W, static_cast<uint32_t>(P * 4));
-  float wr[M][CP];
-  float acc[M][CP];
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const int j = tid + m * T;
-#pragma unroll
-    for (int c = 0; c < CP; ++c) {
-      const uint32_t off = c < C ? static_cast<uint32_t>((j * C + c) * 4) : kOutOfRange;
-      wr[m][c] = buf_f32(wrs, off);
-      acc[m][c] = 0.f;
-    }
-  }
-  float loss_acc = 0.f;
-  const float invB = 1.0f / static_cast<float>(a.B);
-  __syncthreads();
-
-  // rows of chunk `cb` (relative to b0) into x; rows past the slab read as 0
-  auto load_chunk = [&](int cb, float (&x)[R][M]) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int rr_ = cb + r;
-      const bool row_ok = rr_ < nrows;
-      const int row = __builtin_amdgcn_readfirstlane(sh_row[row_ok ? rr_ : 0]);
-      // a resource over the row (empty past the slab): j >= d reads 0
-      const __amdgpu_buffer_rsrc_t xr =
-          make_rsrc(a.X + static_cast<int64_t>(row) * d, row_ok ? static_cast<uint32_t>(d * 4) : 0u);
-#pragma unroll
-      for (int m = 0; m < M; ++m) x[r][m] = buf_f32(xr, static_cast<uint32_t>((tid + m * T) * 4));
-    }
-  };
-
-  float xa[R][M], xb[R][M];
-  load_chunk(0, xa);
-  for (int cb = 0; cb < nrows; cb += R) {
-    // partial logits over this thread's slice of the features
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-#pragma unroll
-      for (int c = 0; c < CP; ++c) {
-        float z = 0.f;
-#pragma unroll
-        for (int m = 0; m < M; ++m) z = fmaf(xa[r][m], wr[m][c], z);
-        red[tid][r * CP + c] = z;
-      }
-    }
-    // next chunk's loads fly during the reduction and the softmax
-    load_chunk(cb + R, xb);
-    __syncthreads();
-    if (tid < V * G) {
-      const int v = tid % V, g = tid / V;
-      float s = 0.f;
-#pragma unroll 4
-      for (int t = g; t < T; t += G) s += red[t][v];
-      red2[g][v] = s;
-    }
-    __syncthreads();
-    // wave 0: 16 lanes per row (R == 4) finish the reduction and run the
-    // softmax; lane (r, c) holds logit c of row r.
-    if (tid < WAVE) {
-      const int r = tid / 16, c = tid % 16;
-      const int rb = cb + r;
-      float z = 0.f;
-      if (c < CP) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) z += red2[g][r * CP + c];
-      }
-      const bool valid = c < C;
-      float zmax = valid ? z : -INFINITY;
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, o, 16));
-      const float sh = z - zmax;
-      const float e = valid ? expf(sh) : 0.f;
-      float se = e;
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) se += __shfl_xor(se, o, 16);
-      const bool row_ok = rb < nrows;
-      const int lab = row_ok ? sh_lab[rb] : 0;
-      const float zy = __shfl(sh, r * 16 + lab, WAVE);
-      if (c < CP) rr[r * CP + c] = row_ok ? (e / se - (c == lab ? 1.f : 0.f)) * invB : 0.f;
-      // CE = log(sum_c e^{z_c - zmax}) - (z_y - zmax)
-      if (c == 0 && row_ok) loss_acc += logf(se) - zy;
-    }
-    __syncthreads();
-    // fold the residuals into the gradient slice, row by row
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      float rv[CP];
-#pragma unroll
-      for (int c = 0; c < CP; ++c) rv[c] = rr[r * CP + c];
-#pragma unroll
-      for (int m = 0; m < M; ++m)
-#pragma unroll
-        for (int c = 0; c < CP; ++c) acc[m][c] = fmaf(xa[r][m], rv[c], acc[m][c]);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int m = 0; m < M; ++m) xa[r][m] = xb[r][m];
-  }
-  if (tid < WAVE && tid % 16 == 0) sh_loss[tid / 16] = loss_acc;
-  __syncthreads();
-  float block_loss = 0.f;
-#pragma unroll
-  for (int r = 0; r < R; ++r) block_loss += sh_loss[r];
-
-  if (slabs == 1) {
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      const int j = tid + m * T;
-      if (j < d && (!a.row_mask || a.row_mask[i]))
-#pragma unroll
-        for (int c = 0; c < CP; ++c)
-          if (c < C) a.G[(int64_t)i * P + (int64_t)j * C + c] = acc[m][c];
-    }
-    if (tid == 0) a.loss[i] = block_loss * invB;
-    return;
-  }
-  float* gp = a.Gp + ((int64_t)i * slabs + q) * P;
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const int j = tid + m * T;
-    if (j < d)
-#pragma unroll
-      for (int c = 0; c < CP; ++c)
-        if (c < C) gp[(int64_t)j * C + c] = acc[m][c];
-  }
-  if (tid == 0) a.lossp[(int64_t)i * slabs + q] = block_loss;
-}
 
 // ---------------------------------------------------------------------------
 // Matrix-core variant of the single pass (C <= 16, d % 4 == 0, d <= 3072).
@@ -658,596 +494,345 @@ __global__ __launch_bounds__(256) void k_slab_reduce_tiles(SoftmaxArgs a, int sl
   }
 }
 
-// Sum of the slab partials of every worker in slab order (a kernel of its
-// own: the launch boundary orders the partial writes before these reads).
-// blockIdx.y = worker; each thread adds 4 consecutive elements.
-__global__ __launch_bounds__(256) void k_slab_reduce(SoftmaxArgs a, int slabs) {
-  const int i = blockIdx.y;
-  const int64_t P = (int64_t)a.d * a.C;
-  const int64_t e0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  const float* src = a.Gp + (int64_t)i * slabs * P;
-  float* dst = a.G + (int64_t)i * P;
-  if (e0 < P && (!a.row_mask || a.row_mask[i])) {
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, static_cast<uint32_t>(slabs * P * 4));
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    if ((P & 3) == 0) {
-      for (int q = 0; q < slabs; ++q) {
-        const float4 v = buf_f32x4(rs, static_cast<uint32_t>((q * P + e0) * 4));
-        s0 += v.x; s1 += v.y; s2 += v.z; s3 += v.w;
-      }
-      *reinterpret_cast<float4*>(dst + e0) = make_float4(s0, s1, s2, s3);
+// ---------------------------------------------------------------------------
+// GEMM path (any C, d, B): products on the bf16 matrix cores in three parts
+// (split_gemm.h).  W is packed into fragments, the logits kernel leaves the
+// residuals as fragments of the second product (from its registers when a
+// wave holds all classes of its rows, C <= 16 SG_NARROW; else through Z and
+// k_rows_pack), and the gradient kernel forms G_i = X_i^T R_i.
+//
+// The rows of the logits product are padded per worker to whole tiles of 16
+// (tpw tiles), so that a tile's residuals belong to one worker's fragments.
+
+constexpr int SG_DIRECT = 4;   // up to so many column tiles a K-split wave reads W itself
+
+// Z[m][c] = sum_j X[row(m)][j] W[j][c] on MT x NT tiles of 16 x 16 per wave;
+// blockIdx.x = NW MT row tiles, blockIdx.y = NT column tiles.  NARROW: all
+// classes are in the wave: softmax, residuals (p - onehot(y)) / B as
+// fragments and the rows' cross entropy.  Otherwise Z is stored.  KS: the
+// block's waves share MT row tiles and split K (sg_loop_k).  256 x 512 x 3072 x
+// 100: 430 - 475 us (fp32 matrix-core form 629), 1.6 GB of X at 3.4 - 3.7 TB/s
+// and 1.1 - 1.3 PFLOP/s of issued bf16 products, both near what the chip holds.
+template <int MT, int NT, int NW, int OCC, bool KS, bool NARROW, bool TINY = false>
+__global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int tiles, int tpw) {
+  __shared__ std::conditional_t<KS, SgRed<MT, NT, NW>, SgLds<NT, NW>> L;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, c = lane & 15;
+  const int d = a.d, C = a.C, B = a.B;
+  const int64_t xrows = a.rows ? a.S : (int64_t)a.n * B;
+  const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
+  const int t0 = (KS ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * NW + wv) * MT;
+  const int nt0 = static_cast<int>(blockIdx.y) * NT;
+  const bool report = blockIdx.y == 0 && g == 0 && (!KS || wv == 0);
+  SgRows<MT, TINY> X(xs, d);
+  int lab[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int i = (t0 + t) / tpw, b = (t0 + t) % tpw * 16 + c;
+    X.roff[t] = kOutOfRange;
+    lab[t] = 0;
+    if (i < a.n && b < B) {
+      const int64_t row = sample_row(a, i, b, report);
+      if (NARROW) lab[t] = a.y[row];   // checked where it is used
+      X.roff[t] = static_cast<uint32_t>(row * d * 4) + 32 * g;
+    }
+  }
+  sg_f32x4 acc[NT][MT];
+  sg_zero<MT, NT>(acc);
+  {
+    auto prep = [&](int kb, float (&x)[MT][8]) { X.prep(kb, x); };
+    auto frag = [&](int kb) { return a.Wp + sg_frag(kb, tiles, nt0, 0) * 64; };
+    if constexpr (KS && NT <= SG_DIRECT)
+      sg_loop_k<MT, NT, NW>(L, 0, X.slices(), X, prep, SgMatrix<NT>(make_rsrc(a.W, static_cast<uint32_t>((int64_t)d * C * 4)), C, nt0 * 16), acc);
+    else if constexpr (KS)
+      sg_loop_k<MT, NT, NW>(L, 0, X.slices(), X, prep, SgFrags<NT>{frag(0), (int64_t)tiles * 192}, acc);
+    else sg_loop<MT, NT, NW, MT == 1 ? 2 : 1>(L, 0, X.slices(), X, prep, frag, acc);
+  }
+  if (KS && wv > 0) return;
+  sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
+    const int i = (t0 + t) / tpw, b = (t0 + t) % tpw * 16 + 4 * g + r, cc = (nt0 + nt) * 16 + c;
+    if (i >= a.n || b >= B || cc >= C) return 0.f;
+    const float* x = a.X + sample_row(a, i, b, false) * d;
+    float s = 0.f;
+    for (int j = 0; j < d; ++j) s = fmaf(x[j], a.W[(int64_t)j * C + cc], s);
+    return s;
+  });
+
+  if (NARROW) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) lab[t] = checked_label(a, lab[t]);
+  }
+  const float invB = 1.0f / static_cast<float>(B);
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int i = (t0 + t) / tpw, bt = (t0 + t) % tpw;
+    if (i >= a.n) break;
+    const int b0 = bt * 16 + 4 * g;   // this lane's rows b0 .. b0 + 3
+    if constexpr (!NARROW) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (b0 + r < B)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) {
+            const int cc = (nt0 + nt) * 16 + c;
+            if (cc < C) a.Z[((int64_t)i * B + b0 + r) * C + cc] = acc[nt][t][r];
+          }
     } else {
-      float acc4[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int q = 0; q < slabs; ++q)
+      // the row's classes are the 16 lanes of a DPP row
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int64_t idx = e0 + e;
-          acc4[e] += buf_f32(rs, idx < P ? static_cast<uint32_t>((q * P + idx) * 4) : kOutOfRange);
-        }
+      for (int r = 0; r < 4; ++r) {
+        float mx = -INFINITY;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (e0 + e < P) dst[e0 + e] = acc4[e];
-    }
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    float s = 0.f;
-    for (int q = 0; q < slabs; ++q) s += a.lossp[(int64_t)i * slabs + q];
-    a.loss[i] = s / static_cast<float>(a.B);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// GEMM path.  64 x 64 output tile, 16-deep K slices staged in LDS, 256
-// threads each computing a 4 x 4 sub-tile.
-constexpr int GBM = 64, GBN = 64, GBK = 16;
-
-// Z[m][c] = sum_j X[row(m)][j] W[j][c] for m < n*B, c < C.
-__global__ __launch_bounds__(256) void k_logits_gemm(SoftmaxArgs a) {
-  __shared__ float As[GBK][GBM + 4];
-  __shared__ float Bs[GBK][GBN + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int64_t Mrows = (int64_t)a.n * a.B;
-  const int64_t m0 = (int64_t)blockIdx.y * GBM;
-  const int n0 = blockIdx.x * GBN;
-  const int d = a.d, C = a.C;
-  // A loader: row m0 + tid/4, k offset (tid%4)*4; out-of-range reads are 0
-  const int la_m = tid / 4, la_k = (tid % 4) * 4;
-  const int64_t am = m0 + la_m;
-  const int64_t xrows = a.rows ? a.S : Mrows;
-  const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t ws = make_rsrc(a.W, static_cast<uint32_t>((int64_t)d * C * 4));
-  int64_t arow = -1;
-  if (am < Mrows) {
-    const int wi = static_cast<int>(am / a.B), wb = static_cast<int>(am % a.B);
-    arow = sample_row(a, wi, wb, la_k == 0);
-  }
-  const int lb_k = tid / 16, lb_n = (tid % 16) * 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < d; k0 += GBK) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int kk = k0 + la_k + e;
-      const uint32_t off = (arow >= 0 && kk < d) ? static_cast<uint32_t>((arow * d + kk) * 4) : kOutOfRange;
-      As[la_k + e][la_m] = buf_f32(xs, off);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int kk = k0 + lb_k, nn = n0 + lb_n + e;
-      const uint32_t off = (kk < d && nn < C) ? static_cast<uint32_t>(((int64_t)kk * C + nn) * 4) : kOutOfRange;
-      Bs[lb_k][lb_n + e] = buf_f32(ws, off);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < GBK; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        av[e] = As[kk][ty * 4 + e];
-        bv[e] = Bs[kk][tx * 4 + e];
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(av[r], bv[c], acc[r][c]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int64_t m = m0 + ty * 4 + r;
-    if (m >= Mrows) continue;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int nn = n0 + tx * 4 + c;
-      if (nn < C) a.Z[m * C + nn] = acc[r][c];
-    }
-  }
-}
-
-// Row softmax in place: Z[m] <- (softmax(Z[m]) - onehot(y)) / B; ce[m] = CE.
-__global__ __launch_bounds__(256) void k_rows_softmax(SoftmaxArgs a) {
-  const int lane = threadIdx.x % WAVE;
-  const int64_t m = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
-  if (m >= (int64_t)a.n * a.B) return;
-  const int C = a.C;
-  float* z = a.Z + m * C;
-  const int wi = static_cast<int>(m / a.B), wb = static_cast<int>(m % a.B);
-  const int lab = sample_label(a, sample_row(a, wi, wb, false), lane == 0);
-  float mx = -INFINITY;
-  for (int c = lane; c < C; c += WAVE) mx = fmaxf(mx, z[c]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, WAVE));
-  float se = 0.f;
-  for (int c = lane; c < C; c += WAVE) se += expf(z[c] - mx);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o, WAVE);
-  const float zy = z[lab];
-  const float inv = 1.0f / se, invB = 1.0f / static_cast<float>(a.B);
-  __syncthreads();  // every lane has read z[lab] before it is overwritten
-  for (int c = lane; c < C; c += WAVE) z[c] = (expf(z[c] - mx) * inv - (c == lab ? 1.f : 0.f)) * invB;
-  if (lane == 0) a.ce[m] = (logf(se) + mx) - zy;
-}
-
-// G_i[j][c] = sum_b X_i[b][j] R_i[b][c]; blockIdx.z = worker.
-__global__ __launch_bounds__(256) void k_grads_gemm(SoftmaxArgs a) {
-  __shared__ float As[GBK][GBM + 4];
-  __shared__ float Bs[GBK][GBN + 4];
-  __shared__ float sh[256];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int i = blockIdx.z;
-  const int j0 = blockIdx.y * GBM;
-  const int n0 = blockIdx.x * GBN;
-  const int d = a.d, C = a.C, B = a.B;
-  const int64_t P = (int64_t)d * C;
-  const int64_t xrows = a.rows ? a.S : (int64_t)a.n * B;
-  const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.Z + (int64_t)i * B * C, static_cast<uint32_t>((int64_t)B * C * 4));
-  const int l_k = tid / 16, l_x = (tid % 16) * 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < B; k0 += GBK) {
-    const int b = k0 + l_k;
-    const int64_t xrow = b < B ? sample_row(a, i, b, false) : -1;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int j = j0 + l_x + e;
-      const uint32_t xo = (xrow >= 0 && j < d) ? static_cast<uint32_t>((xrow * d + j) * 4) : kOutOfRange;
-      As[l_k][l_x + e] = buf_f32(xs, xo);
-      const int nn = n0 + l_x + e;
-      const uint32_t ro = (b < B && nn < C) ? static_cast<uint32_t>(((int64_t)b * C + nn) * 4) : kOutOfRange;
-      Bs[l_k][l_x + e] = buf_f32(rs, ro);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < GBK; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        av[e] = As[kk][ty * 4 + e];
-        bv[e] = Bs[kk][tx * 4 + e];
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(av[r], bv[c], acc[r][c]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int j = j0 + ty * 4 + r;
-    if (j >= d) continue;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int nn = n0 + tx * 4 + c;
-      if (nn < C && (!a.row_mask || a.row_mask[i])) a.G[(int64_t)i * P + (int64_t)j * C + nn] = acc[r][c];
-    }
-  }
-  if (blockIdx.x == 0 && blockIdx.y == 0) {
-    // loss_i = mean CE over the worker's rows (fixed order)
-    float s = 0.f;
-    for (int b = tid; b < B; b += 256) s += a.ce[(int64_t)i * B + b];
-    sh[tid] = s;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-      if (tid < st) sh[tid] += sh[tid + st];
-      __syncthreads();
-    }
-    if (tid == 0) a.loss[i] = sh[0] / static_cast<float>(B);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Matrix-core fp32 GEMMs for the large-C path (C % 4 == 0, d % 4 == 0):
-// 128 x 128 tiles, or 64 x 64 when the large tiles cannot fill the chip;
-// main loops in mfma_gemm.h.
-
-// Z[m][c] = sum_j X[row(m)][j] W[j][c]; blockIdx.x = class tile, y = row tile.
-template <int WT>
-__global__ __launch_bounds__(256) void k_logits_mfma(SoftmaxArgs a) {
-  constexpr int BM = 32 * WT, NP = mfma_pieces<WT>();
-  __shared__ MfmaLds<WT> L;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wm = wv >> 1, wn = wv & 1;
-  const int64_t Mrows = (int64_t)a.n * a.B;
-  const int64_t m0 = (int64_t)blockIdx.y * BM;
-  const int n0 = blockIdx.x * BM;
-  const int d = a.d, C = a.C;
-  const int64_t xrows = a.rows ? a.S : Mrows;
-  const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t ws = make_rsrc(a.W, static_cast<uint32_t>((int64_t)d * C * 4));
-  int64_t xrow[NP];
-#pragma unroll
-  for (int s2 = 0; s2 < NP; ++s2) {
-    const int q = tid + s2 * 256;
-    const int64_t m = m0 + q / 4;
-    xrow[s2] = -1;
-    if (m < Mrows) xrow[s2] = sample_row(a, static_cast<int>(m / a.B), static_cast<int>(m % a.B), (q % 4) == 0);
-  }
-  mfma_f32x4 acc[WT][WT];
-  mfma_zero<WT>(acc);
-  mfma_gemm_rows_w<WT>(L, xs, xrow, d, ws, C, n0, acc);
-#pragma unroll
-  for (int mt = 0; mt < WT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t m = m0 + wm * 16 * WT + mt * 16 + 4 * (lane >> 4) + r;
-      if (m >= Mrows) continue;
-#pragma unroll
-      for (int nt = 0; nt < WT; ++nt) {
-        const int c = n0 + wn * 16 * WT + nt * 16 + (lane & 15);
-        if (c < C) a.Z[m * C + c] = acc[mt][nt][r];
-      }
-    }
-}
-
-// G_i[j][c] = sum_b X[row(i,b)][j] R_i[b][c]; blockIdx.x = class tile,
-// y = feature tile, z = worker.  Block (0, 0, i) also writes loss_i.
-template <int WT>
-__global__ __launch_bounds__(256) void k_grads_mfma(SoftmaxArgs a) {
-  constexpr int BM = 32 * WT;
-  __shared__ MfmaLds<WT> L;
-  __shared__ int sh_row[FUSED_MAX_ROWS];
-  __shared__ float sh[256];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wm = wv >> 1, wn = wv & 1;
-  const int i = blockIdx.z;
-  const int j0 = blockIdx.y * BM, n0 = blockIdx.x * BM;
-  const int d = a.d, C = a.C, B = a.B;
-  const int64_t P = (int64_t)d * C;
-  const int64_t xrows = a.rows ? a.S : (int64_t)a.n * B;
-  const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.Z + (int64_t)i * B * C, static_cast<uint32_t>((int64_t)B * C * 4));
-  for (int b = tid; b < B; b += 256) sh_row[b] = static_cast<int>(sample_row(a, i, b, false));
-  __syncthreads();
-  mfma_f32x4 acc[WT][WT];
-  mfma_zero<WT>(acc);
-  mfma_gemm_xt_r<WT>(L, xs, sh_row, d, j0, rs, B, C, n0, acc);
-  // the G rows of workers outside the row mask are computed but not stored
-  const bool write_g = !a.row_mask || a.row_mask[i];
-#pragma unroll
-  for (int mt = 0; mt < WT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = j0 + wm * 16 * WT + mt * 16 + 4 * (lane >> 4) + r;
-      if (j >= d) continue;
-#pragma unroll
-      for (int nt = 0; nt < WT; ++nt) {
-        const int c = n0 + wn * 16 * WT + nt * 16 + (lane & 15);
-        if (c < C && write_g) a.G[(int64_t)i * P + (int64_t)j * C + c] = acc[mt][nt][r];
-      }
-    }
-  if (blockIdx.x == 0 && blockIdx.y == 0) {
-    // loss_i = mean CE over the worker's rows (fixed order)
-    float s = 0.f;
-    for (int b = tid; b < B; b += 256) s += a.ce[(int64_t)i * B + b];
-    sh[tid] = s;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-      if (tid < st) sh[tid] += sh[tid + st];
-      __syncthreads();
-    }
-    if (tid == 0) a.loss[i] = sh[0] / static_cast<float>(B);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Matrix-core path for 16 < C <= 16 NT (C % 4 == 0): the narrow-N loops of
-// mfma_gemm.h put all classes of a row in one wave, so the row softmax runs
-// in the logits kernel's registers (a 16-lane DPP row holds the row's
-// classes) and the residuals are written once; then G_i = X_i^T R_i with
-// blocks of 64 MT features x all classes.
-constexpr int NARROW_MT = 2;
-
-// Z[m][c] = (softmax(x_m W)_c - [c = y_m]) / B, ce[m] = CE of row m;
-// blockIdx.x = tile of 64 MT rows.  RS > 0: C = 16 (NT - 1) + 4 RS, the last
-// tile in 4-wide stripes.
-template <int MT, int NT, int RS>
-__global__ __launch_bounds__(256, 4) void k_logits_softmax_mfma(SoftmaxArgs a) {
-  using Lds = MfmaLdsN<MT, NT, 64 * MT + 4>;
-  constexpr int BM = Lds::BM, BN = Lds::BN;
-  constexpr int NPA = BM / 64;                          // A: BM rows x 4 float4
-  constexpr int NPB = (4 * BN + 255) / 256;             // B: 16 k rows x BN / 4 float4
-  __shared__ Lds L;
-  __shared__ int sh_lab[BM];
-  const int tid = threadIdx.x, lane = tid & 63, wm = tid >> 6;
-  const int64_t Mrows = (int64_t)a.n * a.B;
-  const int64_t m0 = (int64_t)blockIdx.x * BM;
-  const int d = a.d, C = a.C;
-  const int64_t xrows = a.rows ? a.S : Mrows;
-  const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t ws = make_rsrc(a.W, static_cast<uint32_t>((int64_t)d * C * 4));
-  if (tid < BM) {
-    const int64_t m = m0 + tid;
-    int lab = 0;
-    if (m < Mrows) {
-      const int64_t row = sample_row(a, static_cast<int>(m / a.B), static_cast<int>(m % a.B), true);
-      lab = sample_label(a, row, true);
-    }
-    sh_lab[tid] = lab;
-  }
-  int64_t xrow[NPA];
-#pragma unroll
-  for (int s2 = 0; s2 < NPA; ++s2) {
-    const int64_t m = m0 + (tid + s2 * 256) / 4;
-    xrow[s2] = m < Mrows ? sample_row(a, static_cast<int>(m / a.B), static_cast<int>(m % a.B), false) : -1;
-  }
-  // byte offsets of this thread's pieces at k0 = 0 (out of range where the
-  // piece has no row or class); whole slices add k0 in the scalar offset
-  uint32_t aoff[NPA], boff[NPB];
-#pragma unroll
-  for (int s2 = 0; s2 < NPA; ++s2) {
-    const int kq = 4 * ((tid + s2 * 256) % 4);
-    aoff[s2] = xrow[s2] >= 0 ? static_cast<uint32_t>((xrow[s2] * d + kq) * 4) : kOutOfRange;
-  }
-#pragma unroll
-  for (int s2 = 0; s2 < NPB; ++s2) {
-    const int q = tid + s2 * 256;
-    const int kb = q / (BN / 4), nb = 4 * (q % (BN / 4));
-    boff[s2] = q < 4 * BN && nb < C ? static_cast<uint32_t>((kb * C + nb) * 4) : kOutOfRange;
-  }
-  auto load = [&](int k0, float4 (&ra)[NPA], float4 (&rb)[NPB]) {
-    if (k0 + MBK <= d) {
-#pragma unroll
-      for (int s2 = 0; s2 < NPA; ++s2) ra[s2] = buf_f32x4_s(xs, aoff[s2], static_cast<uint32_t>(k0 * 4));
-#pragma unroll
-      for (int s2 = 0; s2 < NPB; ++s2) rb[s2] = buf_f32x4_s(ws, boff[s2], static_cast<uint32_t>(k0 * C * 4));
-      return;
-    }
-    // the last, partial slice: features past d read as 0
-#pragma unroll
-    for (int s2 = 0; s2 < NPA; ++s2) {
-      const int k = k0 + 4 * ((tid + s2 * 256) % 4);
-      ra[s2] = buf_f32x4(xs, xrow[s2] >= 0 && k < d ? static_cast<uint32_t>((xrow[s2] * d + k) * 4) : kOutOfRange);
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < NPB; ++s2) {
-      const int q = tid + s2 * 256;
-      const int kb = k0 + q / (BN / 4), nb = 4 * (q % (BN / 4));
-      rb[s2] = buf_f32x4(ws, q < 4 * BN && kb < d && nb < C ? static_cast<uint32_t>(((int64_t)kb * C + nb) * 4)
-                                                             : kOutOfRange);
-    }
-  };
-  auto store = [&](int buf, const float4 (&ra)[NPA], const float4 (&rb)[NPB]) {
-#pragma unroll
-    for (int s2 = 0; s2 < NPA; ++s2) {
-      const int q = tid + s2 * 256;
-      const int r = q / 4, k = 4 * (q % 4);
-      L.A[buf][k + 0][r] = ra[s2].x;
-      L.A[buf][k + 1][r] = ra[s2].y;
-      L.A[buf][k + 2][r] = ra[s2].z;
-      L.A[buf][k + 3][r] = ra[s2].w;
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < NPB; ++s2) {
-      const int q = tid + s2 * 256;
-      if (q < 4 * BN) *reinterpret_cast<float4*>(&L.B[buf][q / (BN / 4)][4 * (q % (BN / 4))]) = rb[s2];
-    }
-  };
-  mfma_f32x4 acc[MT][NT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-  mfma_pipeline_n<MT, NT, RS, 64 * MT + 4, NPA, NPB>(L, (d + MBK - 1) / MBK, load, store, acc);
-
-  // row softmax: lane l holds rows 4 (l / 16) + r of each 16-row tile, class
-  // 16 nt + l % 16; a row's classes are the 16 lanes of one DPP row
-  const float invB = 1.0f / static_cast<float>(a.B);
-  const int cl = lane & 15;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int rl = wm * 16 * MT + mt * 16 + 4 * (lane >> 4) + r;
-      float mx = -INFINITY;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        if (nt * 16 + cl < C) mx = fmaxf(mx, acc[mt][nt][r]);
-      mx = row16_max(mx);
-      float ex[NT];
-      float se = 0.f;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        ex[nt] = nt * 16 + cl < C ? expf(acc[mt][nt][r] - mx) : 0.f;
-        se += ex[nt];
-      }
-      se = row16_sum(se);
-      const int64_t m = m0 + rl;
-      if (m < Mrows) {
-        const int lab = sh_lab[rl];
-        const float inv = 1.0f / se;
-        float* z = a.Z + m * C;
+        for (int nt = 0; nt < NT; ++nt)
+          if (nt * 16 + c < C) mx = fmaxf(mx, acc[nt][t][r]);
+        mx = row16_max(mx);
+        float ex[NT];
+        float se = 0.f;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-          const int c = nt * 16 + cl;
-          if (c < C) z[c] = (ex[nt] * inv - (c == lab ? 1.f : 0.f)) * invB;
-          if (c == lab) a.ce[m] = (logf(se) + mx) - acc[mt][nt][r];
+          ex[nt] = nt * 16 + c < C ? expf(acc[nt][t][r] - mx) : 0.f;
+          se += ex[nt];
+        }
+        se = row16_sum(se);
+        const int lr = __shfl(lab[t], 4 * g + r);
+        const bool ok = b0 + r < B;
+        const float inv = 1.0f / se;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const int cc = nt * 16 + c;
+          if (ok && cc == lr) a.ce[(int64_t)i * B + b0 + r] = (logf(se) + mx) - acc[nt][t][r];
+          acc[nt][t][r] = ok && cc < C ? (ex[nt] * inv - (cc == lr ? 1.f : 0.f)) * invB : 0.f;
+        }
+      }
+      sg_u32x4* rp = a.Rp + (int64_t)i * ((tpw + 1) / 2) * tiles * 3 * 64;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const float v[4] = {acc[nt][t][0], acc[nt][t][1], acc[nt][t][2], acc[nt][t][3]};
+        sg_store4(rp, tiles, b0, nt * 16 + c, v);
+        if (bt + 1 == tpw && (bt & 1) == 0) {   // the slice's other 16 rows do not exist
+          const float z[4] = {0.f, 0.f, 0.f, 0.f};
+          sg_store4(rp, tiles, b0 + 16, nt * 16 + c, z);
         }
       }
     }
+  }
 }
 
-// G_i[j][c] = sum_b X[row(i,b)][j] R_i[b][c] for a block of 64 MT features
-// and all classes; blockIdx.x = feature tile, y = worker.  Block (0, i) also
-// writes loss_i.  RS as for the logits.
-template <int MT, int NT, int RS>
-__global__ __launch_bounds__(256, 4) void k_grads_mfma_n(SoftmaxArgs a) {
-  // A rows 16 mod 64 floats apart: the four k rows of an operand read fall on
-  // disjoint bank quarters (the slice is stored as whole float4 rows)
-  using Lds = MfmaLdsN<MT, NT, 64 * MT + 16>;
-  constexpr int BM = Lds::BM, BN = Lds::BN;
-  constexpr int NPA = BM / 64;                          // A: 16 rows x BM / 4 float4
-  constexpr int NPB = (4 * BN + 255) / 256;             // B: 16 rows x BN / 4 float4
-  __shared__ Lds L;
-  __shared__ int sh_row[FUSED_MAX_ROWS];
-  const int tid = threadIdx.x, lane = tid & 63, wm = tid >> 6;
-  const int i = blockIdx.y;
-  const int j0 = blockIdx.x * BM;
+// Residuals of C > 16 SG_NARROW classes: row softmax of Z, residuals as
+// fragments, ce[m] = CE.  Block (x, i): rows 8 x .. 8 x + 7 of worker i (padded
+// to whole slices of 32), held in LDS; every wave runs two rows' statistics and
+// leaves their exponentials, then packs a quarter of the columns.
+__global__ __launch_bounds__(256) void k_rows_pack(SoftmaxArgs a, int tiles, int kblocks) {
+  extern __shared__ float zrow[];   // [8][C]
+  __shared__ float sh_inv[8];
+  __shared__ int sh_lab[8];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int i = blockIdx.y, b0 = static_cast<int>(blockIdx.x) * 8;
+  const int C = a.C, B = a.B;
+  const int nr = max(0, min(8, B - b0)), nz = nr * C;
+  const float* z0 = a.Z + ((int64_t)i * B + b0) * C;
+  for (int e0 = 0; e0 < nz; e0 += 8 * 256) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = e0 + q * 256 + tid < nz ? z0[e0 + q * 256 + tid] : 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (e0 + q * 256 + tid < nz) zrow[e0 + q * 256 + tid] = v[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int r = 2 * wv + q;
+    if (r >= nr) break;
+    float* z = zrow + r * C;
+    const int lab = sample_label(a, sample_row(a, i, b0 + r, false), lane == 0);
+    float mx = -INFINITY;
+    for (int c = lane; c < C; c += WAVE) mx = fmaxf(mx, z[c]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, WAVE));
+    const float zy = z[lab];
+    float se = 0.f;
+    for (int c = lane; c < C; c += WAVE) {
+      const float ex = expf(z[c] - mx);
+      z[c] = ex;
+      se += ex;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o, WAVE);
+    if (lane == 0) {
+      sh_inv[r] = 1.0f / se;
+      sh_lab[r] = lab;
+      a.ce[(int64_t)i * B + b0 + r] = (logf(se) + mx) - zy;
+    }
+  }
+  __syncthreads();
+  const float invB = 1.0f / static_cast<float>(B);
+  sg_u32x4* rp = a.Rp + (int64_t)i * kblocks * tiles * 3 * 64;
+  for (int c = tid; c < tiles * 16; c += 256) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      v[e] = e < nr && c < C ? (zrow[e * C + c] * sh_inv[e] - (c == sh_lab[e] ? 1.f : 0.f)) * invB : 0.f;
+    sg_store8(rp, tiles, b0, c, v);
+  }
+}
+
+// G_i[j][c] = sum_b X[row(i,b)][j] R_i[b][c] on MT x NT tiles per wave: lane
+// (g, c) loads MT consecutive features (one per tile) of eight rows, which is
+// the A operand.  A linear grid, dealt so that a worker's blocks share an XCD
+// (its residual fragments meet in one L2); within a worker the column chunks
+// of one feature block are neighbours (its rows of X are read once from HBM).
+// The first block of a worker also writes its loss.  Bound by the matrix cores'
+// bf16 rate at the clock they sustain (about 1.1 PFLOP/s of issued products at
+// 256 x 512 x 3072 x 100: 460 us; the fp32 matrix-core form took 651).
+template <int MT, int NT, int NW, int OCC, bool KS>
+__global__ __launch_bounds__(64 * NW, OCC) void k_sg_grads(SoftmaxArgs a, int tiles, int kblocks, int fblocks,
+                                                          int chunks, int64_t per_xcd) {
+  __shared__ std::conditional_t<KS, SgRed<MT, NT, NW>, SgLds<NT, NW>> L;
+  __shared__ __attribute__((aligned(16))) uint32_t srow[FUSED_MAX_ROWS];
+  __shared__ float sh[NW];
+  const int64_t logical = xcd_logical(blockIdx.x, per_xcd);
+  if (logical >= (int64_t)a.n * fblocks * chunks) return;
+  const int i = static_cast<int>(logical / (fblocks * chunks));
+  const int rem = static_cast<int>(logical % (fblocks * chunks));
+  const int fb = rem / chunks, nt0 = rem % chunks * NT;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, c = lane & 15;
   const int d = a.d, C = a.C, B = a.B;
-  const int64_t P = (int64_t)d * C;
   const int64_t xrows = a.rows ? a.S : (int64_t)a.n * B;
   const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.Z + (int64_t)i * B * C, static_cast<uint32_t>((int64_t)B * C * 4));
-  // byte offsets of the worker's rows (the dataset is addressed by one buffer
-  // descriptor, below 2^31 bytes): no multiply per load
-  for (int b = tid; b < B; b += 256) sh_row[b] = static_cast<int>(sample_row(a, i, b, false) * d * 4);
-  __syncthreads();
-  // residual pieces: byte offsets at k0 = 0 (out of range past the classes);
-  // whole slices add k0 rows in the scalar offset
-  uint32_t boff[NPB];
-#pragma unroll
-  for (int s2 = 0; s2 < NPB; ++s2) {
-    const int q = tid + s2 * 256;
-    const int b = q / (BN / 4), c = 4 * (q % (BN / 4));
-    boff[s2] = q < 4 * BN && c < C ? static_cast<uint32_t>((b * C + c) * 4) : kOutOfRange;
-  }
-  auto load = [&](int k0, float4 (&ra)[NPA], float4 (&rb)[NPB]) {
-    const bool whole = k0 + MBK <= B;
-#pragma unroll
-    for (int s2 = 0; s2 < NPA; ++s2) {
-      const int q = tid + s2 * 256;
-      const int b = k0 + q / (BM / 4), j = j0 + 4 * (q % (BM / 4));
-      ra[s2] = buf_f32x4(xs, (whole || b < B) && j < d ? static_cast<uint32_t>(sh_row[b]) + static_cast<uint32_t>(j * 4)
-                                                        : kOutOfRange);
-    }
-    if (whole) {
-#pragma unroll
-      for (int s2 = 0; s2 < NPB; ++s2) rb[s2] = buf_f32x4_s(rs, boff[s2], static_cast<uint32_t>(k0 * C * 4));
-      return;
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < NPB; ++s2) {
-      const int q = tid + s2 * 256;
-      const int b = k0 + q / (BN / 4), c = 4 * (q % (BN / 4));
-      rb[s2] = buf_f32x4(rs, q < 4 * BN && b < B && c < C ? static_cast<uint32_t>(((int64_t)b * C + c) * 4)
-                                                         : kOutOfRange);
-    }
-  };
-  auto store = [&](int buf, const float4 (&ra)[NPA], const float4 (&rb)[NPB]) {
-#pragma unroll
-    for (int s2 = 0; s2 < NPA; ++s2) {
-      const int q = tid + s2 * 256;
-      *reinterpret_cast<float4*>(&L.A[buf][q / (BM / 4)][4 * (q % (BM / 4))]) = ra[s2];
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < NPB; ++s2) {
-      const int q = tid + s2 * 256;
-      if (q < 4 * BN) *reinterpret_cast<float4*>(&L.B[buf][q / (BN / 4)][4 * (q % (BN / 4))]) = rb[s2];
-    }
-  };
-  mfma_f32x4 acc[MT][NT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-  mfma_pipeline_n<MT, NT, RS, 64 * MT + 16, NPA, NPB>(L, (B + MBK - 1) / MBK, load, store, acc);
-  // the G rows of workers outside the row mask are computed but not stored
-  const bool write_g = !a.row_mask || a.row_mask[i];
-  float* Gi = a.G + (int64_t)i * P;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = j0 + wm * 16 * MT + mt * 16 + 4 * (lane >> 4) + r;
-      if (j >= d) continue;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int c = nt * 16 + (lane & 15);
-        if (c < C && write_g) Gi[(int64_t)j * C + c] = acc[mt][nt][r];
-      }
-    }
-  if (blockIdx.x == 0) {
-    // loss_i = mean CE over the worker's rows (fixed order), reduced in the
-    // LDS of the A tiles (free after the pipeline's last barrier)
-    float* sh = &L.A[0][0][0];
-    float s = 0.f;
-    for (int b = tid; b < B; b += 256) s += a.ce[(int64_t)i * B + b];
-    sh[tid] = s;
+  const sg_u32x4* rp = a.Rp + (int64_t)i * kblocks * tiles * 3 * 64;
+  const int f0 = (KS ? fb : fb * NW + wv) * 16 * MT;
+  uint32_t foff;
+  int shift;
+  sg_feature<MT>(f0 + MT * c, d, foff, shift);
+  const bool edge = f0 + 16 * MT > d;
+  sg_f32x4 acc[NT][MT];
+  sg_zero<MT, NT>(acc);
+  for (int c0 = 0; c0 < B; c0 += FUSED_MAX_ROWS) {
+    const int nr = min(B - c0, FUSED_MAX_ROWS), nb = (nr + SG_K - 1) / SG_K;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-      if (tid < st) sh[tid] += sh[tid + st];
-      __syncthreads();
-    }
-    if (tid == 0) a.loss[i] = sh[0] / static_cast<float>(B);
+    for (int b = tid; b < nb * SG_K; b += 64 * NW)
+      srow[b] = b < nr ? static_cast<uint32_t>(sample_row(a, i, c0 + b, false) * d * 4) : kOutOfRange;
+    __syncthreads();
+    auto load = [&](int kb, float (&x)[MT][8]) { sg_load_cols<MT>(xs, srow + (kb * SG_K - c0) + 8 * g, foff, x); };
+    auto prep = [&](int, float (&x)[MT][8]) { sg_shift<MT>(shift, edge, x); };
+    auto frag = [&](int kb) { return rp + sg_frag(kb, tiles, nt0, 0) * 64; };
+    if constexpr (KS)
+      sg_loop_k<MT, NT, NW>(L, c0 / SG_K, c0 / SG_K + nb, load, prep, SgFrags<NT>{frag(0), (int64_t)tiles * 192}, acc);
+    else sg_loop<MT, NT, NW, MT == 1 ? 2 : 1>(L, c0 / SG_K, c0 / SG_K + nb, load, prep, frag, acc);
   }
-}
-
-template <int NT, int RS>
-hipError_t launch_narrow_t(const SoftmaxArgs& a, hipStream_t s) {
-  const int64_t Mrows = (int64_t)a.n * a.B;
-  constexpr int BM = 64 * NARROW_MT;
-  hipLaunchKernelGGL((k_logits_softmax_mfma<NARROW_MT, NT, RS>), dim3(static_cast<unsigned>((Mrows + BM - 1) / BM)),
-                     dim3(256), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_grads_mfma_n<NARROW_MT, NT, RS>), dim3(static_cast<unsigned>((a.d + BM - 1) / BM), a.n),
-                     dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-// Classes per 16-wide MFMA tile for the narrow path (0: not taken).
-int narrow_tiles(int C, int d, int B) {
-  if (C <= 16 || C > 112 || C % 4 != 0 || d % 4 != 0 || B > FUSED_MAX_ROWS) return 0;
-  return (C + 15) / 16;
+  sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
+    const int j = f0 + MT * (4 * g + r) + t, cc = (nt0 + nt) * 16 + c;
+    if (j >= d || cc >= C) return 0.f;
+    float s = 0.f;
+    for (int b = 0; b < B; ++b) s = fmaf(a.X[sample_row(a, i, b, false) * d + j], sg_unpack(rp, tiles, b, cc), s);
+    return s;
+  });
+  // the G rows of workers outside the row mask are computed but not stored
+  if ((!KS || wv == 0) && (!a.row_mask || a.row_mask[i])) {
+    float* Gi = a.G + (int64_t)i * d * C;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        const int j = f0 + MT * (4 * g + r) + t;
+        if (j >= d) continue;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const int cc = (nt0 + nt) * 16 + c;
+          if (cc < C) Gi[(int64_t)j * C + cc] = acc[nt][t][r];
+        }
+      }
+  }
+  if (rem == 0) {
+    // loss_i = mean CE over the worker's rows (fixed order)
+    float s = 0.f;
+    for (int b = tid; b < B; b += 64 * NW) s += a.ce[(int64_t)i * B + b];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0) sh[wv] = s;
+    __syncthreads();
+    if (tid == 0) {
+      float l = 0.f;
+      for (int q = 0; q < NW; ++q) l += sh[q];
+      a.loss[i] = l / static_cast<float>(B);
+    }
+  }
 }
 
 template <int NT>
-hipError_t launch_narrow_nt(const SoftmaxArgs& a, hipStream_t s) {
-  // 4 or 8 classes in the last tile: 4-wide stripes (C = 16 (NT - 1) + 4 RS);
-  // with 12 the saving is small and the third stripe's registers are not
-  // free at 7 tiles, so a full tile is used
-  switch ((a.C % 16) / 4) {
-    case 1: return launch_narrow_t<NT, 1>(a, s);
-    case 2: return launch_narrow_t<NT, 2>(a, s);
-    default: return launch_narrow_t<NT, 0>(a, s);
+hipError_t launch_split_nt(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t s) {
+  const int tiles = p.tiles, tpw = (a.B + 15) / 16, kblocks = (a.B + SG_K - 1) / SG_K;
+  const int chunks = tiles / NT;
+  const int64_t rt = (int64_t)a.n * tpw;
+  auto logits = [&](auto kernel, int per, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rt + per - 1) / per), chunks), dim3(threads), 0, s, a, tiles, tpw);
+  };
+  // Waves per SIMD of the large logits blocks: as many as leave no spills.
+  constexpr int OC8 = NT >= 6 ? 2 : 4;
+  // Logits by the number of row tiles times column chunks: with few, a block's
+  // eight waves split K of one row tile (kSplitK); then one row tile a wave,
+  // four waves a block; from two full rounds of the chip on, 16 row tiles a
+  // block, which reads W half as often.  us of the launch, the large / middle /
+  // K-split form: 256 x 512 x 3072 x 100 (8192 tiles) 934 / 1028 / 1641; 128 x
+  // 512 x 256 x 50 (4096) 51 / 49 / 81; 64 x 256 x 3072 x 100 (1024) 250 / 163 /
+  // 209; 32 x 200 x 1024 x 64 (416) 73 / 40 / 36; 16 x 100 x 785 x 20 (112)
+  // 40 / 25 / 17.
+  enum { kLarge, kMiddle, kSplitK, kTiny };
+  const int lv = a.d < 8 ? kTiny : rt * chunks >= 8192 ? kLarge : rt * chunks > 512 ? kMiddle : kSplitK;
+  if (lv != kSplitK || NT > SG_DIRECT) {
+    const int64_t wtasks = (int64_t)((a.d + SG_K - 1) / SG_K) * tiles;
+    hipLaunchKernelGGL(k_sg_pack, dim3(static_cast<unsigned>((wtasks + 3) / 4)), dim3(256), 0, s, a.W, (int64_t)a.C, a.d,
+                       a.C, tiles, a.Wp);
   }
+  if (chunks == 1) {
+    if (lv == kLarge) logits(k_sg_logits<2, NT, 8, OC8, false, true>, 16, 512);
+    else if (lv == kMiddle) logits(k_sg_logits<1, NT, 4, 2, false, true>, 4, 256);
+    else if (lv == kTiny) logits(k_sg_logits<1, NT, 4, 2, false, true, true>, 4, 256);
+    else logits(k_sg_logits<1, NT, 8, 2, true, true>, 1, 512);
+  } else {
+    if (lv == kLarge) logits(k_sg_logits<2, NT, 8, OC8, false, false>, 16, 512);
+    else if (lv == kMiddle) logits(k_sg_logits<1, NT, 4, 2, false, false>, 4, 256);
+    else if (lv == kTiny) logits(k_sg_logits<1, NT, 4, 2, false, false, true>, 4, 256);
+    else logits(k_sg_logits<1, NT, 8, 2, true, false>, 1, 512);
+    hipLaunchKernelGGL(k_rows_pack, dim3(4 * kblocks, a.n), dim3(256), 8 * sizeof(float) * a.C, s, a, tiles, kblocks);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  auto grads = [&](auto kernel, int feats, int threads) {
+    const int fblocks = (a.d + feats - 1) / feats;
+    const int64_t per_xcd = ((int64_t)a.n * fblocks * chunks + NXCD - 1) / NXCD;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(per_xcd * NXCD)), dim3(threads), 0, s, a, tiles, kblocks, fblocks,
+                       chunks, per_xcd);
+  };
+  // Gradients by the number of 16-feature tiles over all workers: four features
+  // a lane (and half the residual reads) from 32768 tiles on, two from 4096,
+  // else one; with so few that the chip stays idle and many rows, the block's
+  // waves split the rows.  us of the launch, 4 / 2 / 1 features / split: 256 x
+  // 512 x 3072 x 100 (49152 tiles) 1005 / 1021 / 1107 / 2157; 64 x 256 x 3072 x
+  // 100 (12288) 182 / 163 / 165 / 366; 128 x 512 x 256 x 50 (2048) 65 / 49 / 46 /
+  // 67; 4 x 512 x 2000 x 200 (1000) 123 / 97 / 85 / 98; the gradient kernel of 3 x
+  // 1100 x 131 x 301 (81) 41 with one feature, 18 split.  (8 column tiles with
+  // four features a lane spill.)
+  const int64_t w16 = (int64_t)a.n * chunks * ((a.d + 15) / 16);
+  if (w16 <= 256 && kblocks >= 8) grads(k_sg_grads<1, NT, 8, 2, true>, 16, 512);
+  else if (w16 < 4096 || a.d < 4) grads(k_sg_grads<1, NT, 4, 2, false>, 64, 256);
+  else if (w16 < 32768 || NT >= 8) grads(k_sg_grads<2, NT, 4, 3, false>, 128, 256);
+  else grads(k_sg_grads<4, NT, 8, 2, false>, 512, 512);
+  return hipGetLastError();
 }
 
-hipError_t launch_narrow(const SoftmaxArgs& a, hipStream_t s) {
-  switch (narrow_tiles(a.C, a.d, a.B)) {
-    case 2: return launch_narrow_nt<2>(a, s);
-    case 3: return launch_narrow_nt<3>(a, s);
-    case 4: return launch_narrow_nt<4>(a, s);
-    case 5: return launch_narrow_nt<5>(a, s);
-    case 6: return launch_narrow_nt<6>(a, s);
-    case 7: return launch_narrow_nt<7>(a, s);
+hipError_t launch_split(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t s) {
+  switch (p.per_thread) {
+    case 1: return launch_split_nt<1>(p, a, s);
+    case 2: return launch_split_nt<2>(p, a, s);
+    case 3: return launch_split_nt<3>(p, a, s);
+    case 4: return launch_split_nt<4>(p, a, s);
+    case 5: return launch_split_nt<5>(p, a, s);
+    case 6: return launch_split_nt<6>(p, a, s);
+    case 7: return launch_split_nt<7>(p, a, s);
+    case 8: return launch_split_nt<8>(p, a, s);
   }
   return hipErrorInvalidValue;
-}
-
-template <int CP, int M, int T>
-hipError_t launch_fused_t(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t s) {
-  constexpr int R = 4;
-  const int64_t nb = (int64_t)a.n * p.slabs;
-  const int64_t per_xcd = (nb + NXCD - 1) / NXCD;
-  hipLaunchKernelGGL((k_softmax_fused<CP, M, T, R>), dim3(static_cast<unsigned>(per_xcd * NXCD)), dim3(T), 0, s,
-                     a, p.slabs, p.rows_per_slab, per_xcd);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p.slabs == 1 || a.keep_slabs) return e;
-  const int64_t P = (int64_t)a.d * a.C;
-  const dim3 g2(static_cast<unsigned>((P + 1023) / 1024), static_cast<unsigned>(a.n));
-  hipLaunchKernelGGL(k_slab_reduce, g2, dim3(256), 0, s, a, p.slabs);
-  return hipGetLastError();
 }
 
 template <int U, int CW>
@@ -1276,89 +861,62 @@ hipError_t launch_mfma_c(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t
   return hipErrorInvalidValue;
 }
 
-template <int CP>
-hipError_t launch_fused_c(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t s) {
-  if (p.threads == 256) {
-    switch (p.per_thread) {
-      case 1: return launch_fused_t<CP, 1, 256>(p, a, s);
-      case 2: return launch_fused_t<CP, 2, 256>(p, a, s);
-      case 4: return launch_fused_t<CP, 4, 256>(p, a, s);
-    }
-  } else {
-    switch (p.per_thread) {
-      case 2: return launch_fused_t<CP, 2, 512>(p, a, s);
-      case 4: return launch_fused_t<CP, 4, 512>(p, a, s);
-      case 6: return launch_fused_t<CP, 6, 512>(p, a, s);
-      case 8: return launch_fused_t<CP, 8, 512>(p, a, s);
-    }
-  }
-  return hipErrorInvalidValue;
+// GEMM path: column tiles of a wave (per_thread) and of all classes.  Up to
+// SG_NARROW tiles a wave holds all of them; else chunks of equal width.
+constexpr int SG_NARROW = 8;
+SoftmaxPlan split_plan(int n, int B, int d, int C) {
+  SoftmaxPlan p;
+  const int need = (C + 15) / 16, chunks = (need + SG_NARROW - 1) / SG_NARROW;
+  p.per_thread = (need + chunks - 1) / chunks;
+  p.tiles = p.per_thread * chunks;
+  p.w_bytes = sg_frag_bytes((d + SG_K - 1) / SG_K, p.tiles);
+  p.r_bytes = sg_frag_bytes((int64_t)n * ((B + SG_K - 1) / SG_K), p.tiles);
+  p.z_floats = chunks > 1 ? (int64_t)n * B * C : 0;
+  return p;
 }
 
 }  // namespace
 
+// Single pass or GEMM path for up to 16 classes: the single pass reads X once
+// and runs near the memory rate once there is enough of it, but a block is a
+// chain of latencies (prologue, chunks of 8 rows, a barrier each) and pads the
+// features to 512 a wave row; the two products of the GEMM path spread a small
+// problem over the chip and X stays in the caches between them.  Measured
+// (us per step, single pass / GEMM path, rows = n x B): 4 x 32 x 784 23.5 /
+// 21.0; 16 x 128 x 784 26.6 / 23.1; 16 x 128 x 3072 38.9 / 32.9; 32 x 256 x
+// 784 30.0 / 28.4; 64 x 256 x 784 37.6 / 40.4; 64 x 256 x 3072 65 / 110; but
+// 128 x 200 x 200 42 / 33 and 256 x 512 x 200 123 / 66.
+constexpr int64_t kSinglePassMin = 6500000;   // elements of the minibatches
+constexpr int kSinglePassMinD = 256;
+
 SoftmaxPlan softmax_plan(int n, int B, int d, int C) {
   SoftmaxPlan p;
-  {
-    // matrix-core single pass: 8 waves x 64U features, W staged in LDS
-    const int cw = C <= 4 ? 4 : C <= 10 ? 10 : C <= 16 ? 16 : 0;
-    const int U = (d + MF_T - 1) / MF_T;
-    const bool fits = cw == 16 ? U <= 4 : U <= 6;
-    if (cw && d % 4 == 0 && fits) {
-      p.fused = 2;
-      p.threads = MF_T;
-      p.per_thread = U;
-      p.cpad = cw;
-      // about 256 blocks, at least four 8-row chunks per slab
-      int slabs = 256 / n, max_slabs = B / (4 * MF_ROWS);
-      slabs = slabs < 1 ? 1 : slabs;
-      max_slabs = max_slabs < 1 ? 1 : max_slabs;
-      slabs = slabs > max_slabs ? max_slabs : slabs;
-      int rps = (B + slabs - 1) / slabs;
-      rps = (rps + MF_ROWS - 1) / MF_ROWS * MF_ROWS;
-      if (rps > FUSED_MAX_ROWS) rps = FUSED_MAX_ROWS;
-      p.rows_per_slab = rps;
-      p.slabs = (B + rps - 1) / rps;
-      p.part = (int64_t)MF_T * U * C;   // tile-order partial
-      if ((int64_t)p.slabs * p.part * 4 <= kMaxBufferBytes) return p;
-      p = SoftmaxPlan{};
-    }
-  }
-  int cp = C <= 4 ? 4 : C <= 10 ? 10 : C <= 16 ? 16 : 0;
-  int T = d <= 1024 ? 256 : 512;
-  int M = (d + T - 1) / T;
-  if (T == 256) M = M <= 1 ? 1 : M <= 2 ? 2 : M <= 4 ? 4 : 0;
-  else M = M <= 2 ? 2 : M <= 4 ? 4 : M <= 6 ? 6 : M <= 8 ? 8 : 0;
-  // register budget: no spills for M <= 6 (C <= 10) and M <= 4 (C <= 16)
-  if ((cp == 16 && M > 4) || (cp == 10 && M > 6)) M = 0;
-  if (cp == 0 || M == 0) {
-    p.fused = 0;
-    return p;
-  }
+  const int cw = C <= 4 ? 4 : C <= 10 ? 10 : C <= 16 ? 16 : 0;
+  const int U = (d + MF_T - 1) / MF_T;
+  const bool fits = cw == 16 ? U <= 4 : U <= 6;
+  if (!cw || d % 4 != 0 || !fits || (int64_t)n * B * d < kSinglePassMin || d < kSinglePassMinD)
+    return split_plan(n, B, d, C);
+  // 8 waves x 64U features, W staged in LDS
   p.fused = 1;
-  p.threads = T;
-  p.per_thread = M;
-  p.cpad = cp;
-  // fill the chip: about 256 blocks, at least two 4-row chunks per slab
-  int slabs = 256 / n;
-  int max_slabs = B / 8;
+  p.per_thread = U;
+  p.cpad = cw;
+  // about 256 blocks, at least four 8-row chunks per slab
+  int slabs = 256 / n, max_slabs = B / (4 * MF_ROWS);
   slabs = slabs < 1 ? 1 : slabs;
   max_slabs = max_slabs < 1 ? 1 : max_slabs;
   slabs = slabs > max_slabs ? max_slabs : slabs;
-  p.slabs = slabs;
-  p.rows_per_slab = (B + slabs - 1) / slabs;
-  // round rows per slab up to the 4-row chunk
-  p.rows_per_slab = (p.rows_per_slab + 3) / 4 * 4;
-  if (p.rows_per_slab > 1024) p.rows_per_slab = 1024;   // rows staged in LDS
-  p.slabs = (B + p.rows_per_slab - 1) / p.rows_per_slab;
-  p.part = (int64_t)d * C;
+  int rps = (B + slabs - 1) / slabs;
+  rps = (rps + MF_ROWS - 1) / MF_ROWS * MF_ROWS;
+  if (rps > FUSED_MAX_ROWS) rps = FUSED_MAX_ROWS;
+  p.rows_per_slab = rps;
+  p.slabs = (B + rps - 1) / rps;
+  p.part = (int64_t)MF_T * U * C;   // tile-order partial
   // one worker's partials are read through one buffer resource
-  if ((int64_t)p.slabs * d * C * 4 > kMaxBufferBytes) p.fused = 0;
-  return p;
+  return (int64_t)p.slabs * p.part * 4 <= kMaxBufferBytes ? p : split_plan(n, B, d, C);
 }
 
 hipError_t launch_softmax_grads(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t s) {
-  if (p.fused == 2) {
+  if (p.fused) {
     switch (p.cpad) {
       case 4: return launch_mfma_c<4>(p, a, s);
       case 10: return launch_mfma_c<10>(p, a, s);
@@ -1366,51 +924,7 @@ hipError_t launch_softmax_grads(const SoftmaxPlan& p, const SoftmaxArgs& a, hipS
     }
     return hipErrorInvalidValue;
   }
-  if (p.fused) {
-    switch (p.cpad) {
-      case 4: return launch_fused_c<4>(p, a, s);
-      case 10: return launch_fused_c<10>(p, a, s);
-      case 16: return launch_fused_c<16>(p, a, s);
-    }
-    return hipErrorInvalidValue;
-  }
-  if (narrow_tiles(a.C, a.d, a.B)) return launch_narrow(a, s);
-  const int64_t Mrows = (int64_t)a.n * a.B;
-  // matrix cores when float4 pieces tile the rows of X, W and R exactly
-  // (and a worker's row indices fit the LDS stage)
-  const bool mfma = a.C % 4 == 0 && a.d % 4 == 0 && a.B <= FUSED_MAX_ROWS;
-  if (mfma) {
-    const int64_t tiles = (int64_t)((a.C + 127) / 128) * ((Mrows + 127) / 128);
-    if (tiles >= kMfmaBigTiles) {
-      dim3 g1((a.C + 127) / 128, static_cast<unsigned>((Mrows + 127) / 128));
-      hipLaunchKernelGGL(k_logits_mfma<4>, g1, dim3(256), 0, s, a);
-    } else {
-      dim3 g1((a.C + 63) / 64, static_cast<unsigned>((Mrows + 63) / 64));
-      hipLaunchKernelGGL(k_logits_mfma<2>, g1, dim3(256), 0, s, a);
-    }
-  } else {
-    dim3 g1((a.C + GBN - 1) / GBN, static_cast<unsigned>((Mrows + GBM - 1) / GBM));
-    hipLaunchKernelGGL(k_logits_gemm, g1, dim3(256), 0, s, a);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_rows_softmax, dim3(static_cast<unsigned>((Mrows + 3) / 4)), dim3(256), 0, s, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (mfma) {
-    const int64_t tiles = (int64_t)((a.C + 127) / 128) * ((a.d + 127) / 128) * a.n;
-    if (tiles >= kMfmaBigTiles) {
-      dim3 g3((a.C + 127) / 128, (a.d + 127) / 128, a.n);
-      hipLaunchKernelGGL(k_grads_mfma<4>, g3, dim3(256), 0, s, a);
-    } else {
-      dim3 g3((a.C + 63) / 64, (a.d + 63) / 64, a.n);
-      hipLaunchKernelGGL(k_grads_mfma<2>, g3, dim3(256), 0, s, a);
-    }
-  } else {
-    dim3 g3((a.C + GBN - 1) / GBN, (a.d + GBM - 1) / GBM, a.n);
-    hipLaunchKernelGGL(k_grads_gemm, g3, dim3(256), 0, s, a);
-  }
-  return hipGetLastError();
+  return launch_split(p, a, s);
 }
 
 }  // namespace dbw

@@ -71,6 +71,77 @@ def test_worker_grads_softmax(n, B, d, C):
     assert rel_err(host(loss), lo) <= RTOL
 
 
+# Edges of the split products: K tails of 1 .. 31 after whole slices of 32 and
+# fewer than 8 features, feature counts off the 2- and 4-wide loads, rows off
+# the tiles of 16 and slices of 32 and beyond the 1024 staged row offsets,
+# classes around the tiles, the chunks and the widest row softmax, and sizes
+# on both sides of each launch rule.  (n, B, d, C, S)
+SPLIT_SHAPES = [
+    (2, 5, 1, 17, 9), (3, 16, 2, 16, 7), (2, 17, 3, 33, 40), (2, 31, 7, 113, 40), (5, 33, 8, 2, 3),
+    (4, 15, 9, 21, 30), (3, 32, 31, 129, 64), (3, 64, 33, 48, 5), (2, 48, 63, 112, 100), (2, 100, 65, 128, 300),
+    (1, 1025, 37, 19, 600), (2, 1100, 785, 10, 900), (16, 100, 785, 10, 2000), (9, 200, 190, 37, 0),
+    (40, 512, 97, 20, 0), (300, 16, 515, 100, 4000), (130, 1024, 10, 97, 5000), (64, 40, 1030, 130, 0),
+    (3, 24, 130, 4096, 100), (256, 16, 1027, 7, 900), (200, 12, 3070, 11, 0), (600, 32, 2051, 20, 700),
+]
+
+
+@pytest.mark.parametrize("n,B,d,C,S", SPLIT_SHAPES)
+def test_worker_grads_softmax_split_products(n, B, d, C, S):
+    g = torch.Generator(device="cuda").manual_seed(n * 31 + B * 7 + d * 3 + C)
+    X = torch.randn((S, d) if S else (n, B, d), generator=g, device="cuda")
+    y = torch.randint(0, C, X.shape[:-1], generator=g, device="cuda", dtype=torch.int32)
+    rows = torch.randint(0, S, (n, B), generator=g, device="cuda", dtype=torch.int32) if S else None
+    if S:
+        rows[0, 0], rows[-1, -1] = 0, S - 1   # the first and the last row of the dataset
+    W = 0.3 / d ** 0.5 * torch.randn(d * C, generator=g, device="cuda")
+    ctx = _ctx(n, B, d, C, S=S)
+    G, loss = ctx.worker_grads(W, X, y, rows=rows)
+    ctx.sync()
+    # rounding of fp32 sums of d (logits) and B (gradient) terms that grow
+    # like their square roots, in units of the largest gradient of the worker
+    tol = 2.0 ** -23 * (8 + d ** 0.5 + B ** 0.5)
+    for i in sorted({0, n // 2, n - 1}):
+        Xi, yi = (X[rows[i].long()], y[rows[i].long()]) if S else (X[i], y[i])
+        Gi, li = omodel.softmax_worker_grads(host(W).astype(np.float64), host(Xi)[None].astype(np.float64),
+                                             host(yi)[None], C)
+        assert rel_err(host(G)[i], Gi[0]) <= tol
+        assert rel_err(host(loss)[i], li[0]) <= tol
+
+
+@pytest.mark.parametrize("n,B,d,C", [(3, 20, 40, 20), (2, 33, 77, 130), (40, 300, 45, 12)])
+def test_worker_grads_softmax_non_finite_inputs(n, B, d, C):
+    # Infinite and nearly overflowing inputs give what fp32 arithmetic gives:
+    # a class whose weights are -inf has probability 0 where the features are
+    # positive, values near the largest float stay finite, and a NaN or an
+    # infinite feature makes its own worker's results NaN and no other's.
+    rng = np.random.default_rng(5)
+    X = rng.random((n, B, d), dtype=np.float32) + np.float32(0.1)
+    X[0, 0, 1] = 3.4e38
+    W = (0.1 * rng.standard_normal((d, C))).astype(np.float32)
+    W[:, 3] = -np.inf
+    W[1] = np.where(np.isinf(W[1]), W[1], 0)
+    y = rng.integers(4, C, size=(n, B), dtype=np.int32)
+    X[1, 2, 0] = np.nan
+    X[1, B - 1, d - 1] = np.inf
+    ctx = _ctx(n, B, d, C)
+    G, loss = ctx.worker_grads(to_dev(torch, W.ravel()), to_dev(torch, X), to_dev(torch, y))
+    ctx.sync()
+    G, loss = host(G).reshape(n, d, C), host(loss)
+    keep = [c for c in range(C) if c != 3]
+    Wf, yf = W[:, keep], y - (y > 3)
+    for i in range(n):
+        if i == 1:
+            assert np.isnan(loss[i]) and np.isnan(G[i]).any()
+            continue
+        Go, lo = omodel.softmax_worker_grads(Wf.astype(np.float64).ravel(), X[i:i + 1].astype(np.float64),
+                                             yf[i:i + 1], C - 1)
+        Go = Go.reshape(d, C - 1)
+        assert np.all(G[i][:, 3] == 0), i
+        assert abs(loss[i] - lo[0]) <= 1e-5 * abs(lo[0])
+        err = np.abs(G[i][:, keep] - Go)
+        assert np.all(err <= 1e-5 * np.max(np.abs(Go), axis=1, keepdims=True)), i
+
+
 @pytest.mark.parametrize("n,B,d,C,S", [(4, 32, 784, 10, 500), (6, 40, 3072, 10, 300), (3, 20, 200, 100, 90)])
 def test_worker_grads_gather_equals_materialised(n, B, d, C, S):
     rng = np.random.default_rng(77 + d)
