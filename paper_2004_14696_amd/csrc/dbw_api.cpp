@@ -477,14 +477,14 @@ dbw_status launch_grads(dbw_ctx* c, const float* w, const float* X, const int32_
     a.G = G; a.loss = loss;
     a.H1 = c->cH1; a.code1 = c->cCode1; a.F = c->cF; a.code2 = c->cCode2; a.ylab = c->cYlab;
     a.dP2 = c->cdP2; a.dP1 = c->cdP1; a.part1 = c->cPart1; a.part2 = c->cPart2; a.chunk = dbw::kCnnChunk;
-    a.Hh = c->Hh; a.dA = c->dA; a.Gp = c->Gp; a.lossp = c->lossp; a.err = c->err; a.row_mask = row_mask;
+    a.Hh = c->Hh; a.Wp = c->Wp; a.Dp = c->Rp; a.dA = c->dA; a.Gp = c->Gp; a.lossp = c->lossp; a.err = c->err; a.row_mask = row_mask;
     e = dbw::launch_cnn_grads(c->mplan, a, c->stream);
   } else {
     dbw::MlpArgs a{};
     a.w = w; a.X = X; a.y = y; a.rows = rows; a.S = cf.S;
     a.n = cf.n; a.B = cf.B; a.d = cf.d; a.H = cf.H; a.C = cf.C;
     a.G = G; a.loss = loss;
-    a.Hh = c->Hh; a.dA = c->dA; a.Gp = c->Gp; a.lossp = c->lossp; a.err = c->err; a.row_mask = row_mask;
+    a.Hh = c->Hh; a.Wp = c->Wp; a.Dp = c->Rp; a.dA = c->dA; a.Gp = c->Gp; a.lossp = c->lossp; a.err = c->err; a.row_mask = row_mask;
     e = dbw::launch_mlp_grads(c->mplan, a, c->stream);
   }
   if (e != hipSuccess) return fail(c, DBW_EHIP, "gradient kernels: %s", hipGetErrorString(e));
@@ -605,7 +605,9 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
     }
   } else {
     sH = take(sizeof(float) * rowsN * cf.H);
-    sdA = take(sizeof(float) * rowsN * cf.H);
+    sWp = take(c->mplan.w_bytes);
+    sRp = take(c->mplan.d_bytes);
+    if (cf.model == DBW_CNN) sdA = take(sizeof(float) * rowsN * cf.H);
     sGp = take(sizeof(float) * n * c->mplan.slabs * c->mplan.tail);
     sLp = take(sizeof(float) * n * c->mplan.slabs);
     if (cf.model == DBW_CNN) {

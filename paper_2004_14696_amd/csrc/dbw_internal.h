@@ -51,6 +51,11 @@ struct MlpPlan {
   int slabs = 1;          // row slabs per worker in the head kernel
   int rows_per_slab = 0;
   int64_t tail = 0;       // H + H*C + C: the [b1 | W2 | b2] segment of G
+  int nt = 0;             // 16-column tiles of a dW1 wave, and of all hidden units (a multiple)
+  int tiles = 0;
+  int wtiles = 0;         // column tiles of the W1 fragments
+  int64_t w_bytes = 0;    // W1 and dA as product fragments
+  int64_t d_bytes = 0;
 };
 
 // Softmax regression: G = per-worker gradient of the mean CE of softmax(X W).
@@ -89,10 +94,10 @@ struct MlpArgs {
   int64_t ldG;           // row stride of G (0: P)
   float* loss;           // [n]
   // workspace
-  float* Hh;             // [n*B][H] hidden activations (with ksplit 2: the first
-                         // K half's pre-activation sums, dA the second's)
-  float* dA;             // [n*B][H] gradient w.r.t. pre-activations
-  int ksplit;            // set by launch_mlp_grads
+  float* Hh;             // [n*B][H] hidden activations
+  sg_u32x4* Wp;          // W1 as product fragments
+  sg_u32x4* Dp;          // dA as product fragments, by worker (zero past the B rows and H columns)
+  float* dA;             // nullable [n*B][H] gradient w.r.t. pre-activations
   float* Gp;             // [n*slabs][H + H*C + C] head slab partials
   float* lossp;          // [n*slabs]
   int32_t* err;
@@ -129,6 +134,8 @@ struct CnnArgs {
   float* part2;          // [n][chunks][25050] conv2 weight-gradient partials
   int chunk;             // images per partial
   float* Hh;             // MLP workspace
+  sg_u32x4* Wp;
+  sg_u32x4* Dp;
   float* dA;
   float* Gp;
   float* lossp;

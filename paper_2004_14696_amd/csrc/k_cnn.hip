@@ -715,7 +715,7 @@ hipError_t launch_cnn_grads(const MlpPlan& mplan, const CnnArgs& a, hipStream_t 
   m.w = a.w; m.X = a.F; m.y = a.ylab; m.rows = nullptr; m.S = 0;
   m.n = a.n; m.B = a.B; m.d = FEAT; m.H = a.H; m.C = a.C;
   m.G = a.G; m.ldG = a.P; m.loss = a.loss;
-  m.Hh = a.Hh; m.dA = a.dA; m.Gp = a.Gp; m.lossp = a.lossp; m.err = a.err; m.row_mask = a.row_mask;
+  m.Hh = a.Hh; m.Wp = a.Wp; m.Dp = a.Dp; m.dA = a.dA; m.Gp = a.Gp; m.lossp = a.lossp; m.err = a.err; m.row_mask = a.row_mask;
   e = launch_mlp_grads(mplan, m, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_cnn_dfeat, dim3((FEAT + 63) / 64, static_cast<unsigned>((nB + 63) / 64)), dim3(256), 0, s, a);

@@ -6,32 +6,33 @@
 //   dW1 = X^T dA,  db1 = sum_b dA,  loss = mean_b CE.
 // ReLU'(0) = 0; [A > 0] is read from Hh > 0, which is the same predicate.
 //
-// Kernels (one stream, in order):
-//  k_mlp_hidden  Hh for all n*B rows: an fp32 MFMA GEMM (v_mfma_f32_16x16x4f32)
-//                over 64 x 64 output tiles, bias + ReLU in the epilogue.
+// Kernels (one stream, in order); the two products run on the bf16 matrix
+// cores with every fp32 operand in three parts (split_gemm.h):
+//  k_mlp_hidden  Hh for all n*B rows, bias + ReLU in the epilogue.
 //  k_mlp_head    per (worker, slab of rows): logits from Hh and W2 held in
 //                registers (thread = hidden unit), LDS reduction, softmax in
-//                wave 0, then dA rows and the slab partials of db1 | dW2 | db2.
-//  k_mlp_dw1     per worker: dW1 = X_i^T dA_i, fp32 MFMA GEMM, K = B; an
-//                extra grid row sums the head's slab partials into
-//                G[i][d*H ...] (fixed order) and the loss.
+//                wave 0, then dA as fragments of the next product and the
+//                slab partials of db1 | dW2 | db2.
+//  k_mlp_dw1     per worker: dW1 = X_i^T dA_i, K = B; extra blocks sum the head's
+//                slab partials into G[i][d*H ...] (fixed order) and the loss.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
 #include "dbw_buffer.h"
 #include "dbw_internal.h"
-#include "mfma_gemm.h"
+#include "split_gemm.h"
 
 namespace dbw {
 namespace {
 
 constexpr int WAVE = 64;
-typedef float floatx4 __attribute__((ext_vector_type(4)));
+constexpr int NXCD = 8;
+constexpr int DW1_ROWS = 1024;   // row offsets staged in LDS at a time
 
-__device__ __forceinline__ int64_t mlp_row(const MlpArgs& a, int i, int b, bool report) {
-  const int64_t m = (int64_t)i * a.B + b;
+__device__ __forceinline__ int64_t mlp_row(const MlpArgs& a, int64_t m, bool report) {
   if (!a.rows) return m;
   const int64_t r = a.rows[m];
   if (r < 0 || r >= a.S) {
@@ -39,6 +40,10 @@ __device__ __forceinline__ int64_t mlp_row(const MlpArgs& a, int i, int b, bool 
     return 0;
   }
   return r;
+}
+
+__device__ __forceinline__ int64_t mlp_row(const MlpArgs& a, int i, int b, bool report) {
+  return mlp_row(a, (int64_t)i * a.B + b, report);
 }
 
 // A label loaded by the caller, range-checked (bad labels are reported and
@@ -52,129 +57,71 @@ __device__ __forceinline__ int checked_label(const MlpArgs& a, int lab) {
 }
 
 // ---------------------------------------------------------------------------
-// MFMA tile: block 256 threads = 4 waves in 2 x 2, each wave 32 x 32 output
-// (2 x 2 MFMA 16 x 16 tiles); K staged through LDS 16 at a time.
-// Lane layout of v_mfma_f32_16x16x4f32 (wave64): A operand lane l holds
-// A[l % 16][l / 16]; B operand lane l holds B[l / 16][l % 16]; accumulator
-// element e of lane l is D[4 (l / 16) + e][l % 16].
-constexpr int TM = 64, TN = 64, TK = 16;
-
-__device__ __forceinline__ void mfma_tile_step(const float (&As)[TK][TM + 4], const float (&Bs)[TK][TN + 4],
-                                               int wm, int wn, int lane, floatx4 (&acc)[2][2]) {
-#pragma unroll
-  for (int kk = 0; kk < TK; kk += 4) {
-    float av[2], bv[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      av[t] = As[kk + lane / 16][wm * 32 + t * 16 + lane % 16];
-      bv[t] = Bs[kk + lane / 16][wn * 32 + t * 16 + lane % 16];
-    }
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[mi], bv[ni], acc[mi][ni], 0, 0, 0);
-  }
-}
-
-// Hh[m][h] = relu(sum_j X[row(m)][j] W1[j][h] + b1[h]), m < n*B.
-__global__ __launch_bounds__(256) void k_mlp_hidden(MlpArgs a) {
-  __shared__ float As[TK][TM + 4];
-  __shared__ float Bs[TK][TN + 4];
-  const int tid = threadIdx.x, lane = tid % WAVE, wv = tid / WAVE;
-  const int wm = wv / 2, wn = wv % 2;
-  const int64_t Mrows = (int64_t)a.n * a.B;
-  const int64_t m0 = (int64_t)blockIdx.y * TM;
-  const int n0 = blockIdx.x * TN;
+// Hh[m][h] = relu(sum_j X[row(m)][j] W1[j][h] + b1[h]), m < n*B, on MT x NT tiles
+// of 16 x 16 per wave (split_gemm.h); blockIdx.x = NW MT row tiles, y = NT
+// column tiles.  KS: the block's waves share MT row tiles, split K and read W1
+// itself; else W1 comes as fragments (`tiles` column tiles).  4096 x 3072 x
+// 1024: 135 us, 1.15 PFLOP/s of issued bf16 products (fp32 matrix cores 230
+// us); 2048 x 784 x 512: 18 us, of which 8 are there with one slice of K
+// (launch, first loads, stores).
+template <int MT, int NT, int NW, int OCC, bool KS, bool TINY = false>
+__global__ __launch_bounds__(64 * NW, OCC) void k_mlp_hidden(MlpArgs a, int tiles) {
+  __shared__ std::conditional_t<KS, SgRed<MT, NT, NW>, SgLds<NT, NW>> L;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Mrows = a.n * a.B;   // below 2^30
   const int d = a.d, H = a.H;
   const int64_t xrows = a.rows ? a.S : Mrows;
   const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t ws = make_rsrc(a.w, static_cast<uint32_t>((int64_t)d * H * 4));
-  // loaders: A tile 64 rows x 16 k (row tid/4, k (tid%4)*4..+3); B tile 16 k x 64 (k tid/16, n (tid%16)*4..)
-  const int la_m = tid / 4, la_k = (tid % 4) * 4;
-  const int64_t am = m0 + la_m;
-  int64_t arow = -1;
-  if (am < Mrows) arow = mlp_row(a, static_cast<int>(am / a.B), static_cast<int>(am % a.B), la_k == 0);
-  const int lb_k = tid / 16, lb_n = (tid % 16) * 4;
-  floatx4 acc[2][2];
+  const int m0 = (KS ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * NW + wv) * MT * 16;
+  const int nt0 = static_cast<int>(blockIdx.y) * NT;
+  SgRows<MT, TINY> X(xs, d);
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < d; k0 += TK) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int kk = k0 + la_k + e;
-      As[la_k + e][la_m] = buf_f32(xs, (arow >= 0 && kk < d) ? static_cast<uint32_t>((arow * d + kk) * 4) : kOutOfRange);
-      const int kb = k0 + lb_k, nn = n0 + lb_n + e;
-      Bs[lb_k][lb_n + e] = buf_f32(ws, (kb < d && nn < H) ? static_cast<uint32_t>(((int64_t)kb * H + nn) * 4) : kOutOfRange);
+  for (int t = 0; t < MT; ++t) {
+    const int m = m0 + 16 * t + c;
+    X.roff[t] = kOutOfRange;
+    if (m < Mrows) {
+      const bool report = blockIdx.y == 0 && g == 0 && (!KS || wv == 0);
+      const int64_t row = mlp_row(a, m, report);
+      X.roff[t] = static_cast<uint32_t>(row * d * 4) + 32 * g;
     }
-    __syncthreads();
-    mfma_tile_step(As, Bs, wm, wn, lane, acc);
-    __syncthreads();
   }
   const float* b1 = a.w + (int64_t)d * H;
+  float bias[NT];
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-      const int nn = n0 + wn * 32 + ni * 16 + lane % 16;
-      if (nn >= H) continue;
-      const float bias = b1[nn];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t m = m0 + wm * 32 + mi * 16 + 4 * (lane / 16) + e;
-        if (m < Mrows) a.Hh[m * H + nn] = fmaxf(acc[mi][ni][e] + bias, 0.f);
-      }
-    }
-}
-
-// Matrix-core versions on (32 WT)^2 tiles (mfma_gemm.h), used when d and H
-// are multiples of 4 and a worker's rows fit the LDS stage.
-template <int WT>
-__global__ __launch_bounds__(256) void k_mlp_hidden_mfma(MlpArgs a) {
-  constexpr int BM = 32 * WT, NP = mfma_pieces<WT>();
-  __shared__ MfmaLds<WT> L;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wm = wv >> 1, wn = wv & 1;
-  const int64_t Mrows = (int64_t)a.n * a.B;
-  const int64_t m0 = (int64_t)blockIdx.y * BM;
-  const int n0 = blockIdx.x * BM;
-  const int d = a.d, H = a.H;
-  const int64_t xrows = a.rows ? a.S : Mrows;
-  const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t ws = make_rsrc(a.w, static_cast<uint32_t>((int64_t)d * H * 4));
-  int64_t xrow[NP];
-#pragma unroll
-  for (int s2 = 0; s2 < NP; ++s2) {
-    const int q = tid + s2 * 256;
-    const int64_t m = m0 + q / 4;
-    xrow[s2] = -1;
-    if (m < Mrows) xrow[s2] = mlp_row(a, static_cast<int>(m / a.B), static_cast<int>(m % a.B), (q % 4) == 0);
+  for (int nt = 0; nt < NT; ++nt) {
+    const int h = (nt0 + nt) * 16 + c;
+    bias[nt] = h < H ? b1[h] : 0.f;
   }
-  mfma_f32x4 acc[WT][WT];
-  mfma_zero<WT>(acc);
-  // with ksplit 2, block z takes one half of K (a multiple of 16) and leaves
-  // its raw sums in Hh (z = 0) or dA (z = 1); the head adds them, b1 and the
-  // ReLU (two addends: the same sum in either order)
-  const int kh = a.ksplit == 2 ? (d / 2 + MBK - 1) / MBK * MBK : d;
-  const int kbeg = static_cast<int>(blockIdx.z) * kh;
-  // two slices in flight: hidden layer 23.2 -> 22.0 us at 2048 x 784 x 512,
-  // 69.8 -> 61.9 us at 8000 x 800 x 500 (the X^T dA product, K = B, is
-  // slower that way and keeps one)
-  mfma_gemm_rows_w<WT, 2>(L, xs, xrow, d, ws, H, n0, acc, kbeg, min(d, kbeg + kh));
-  const float* b1 = a.w + (int64_t)d * H;
-  float* out = blockIdx.z == 0 ? a.Hh : a.dA;
+  sg_f32x4 acc[NT][MT];
+  sg_zero<MT, NT>(acc);
+  {
+    auto prep = [&](int kb, float (&x)[MT][8]) { X.prep(kb, x); };
+    const __amdgpu_buffer_rsrc_t ws = make_rsrc(a.w, static_cast<uint32_t>((int64_t)d * H * 4));
+    if constexpr (KS)
+      sg_loop_k<true, MT, NT, NW>(L, 0, X.slices(), X, prep, SgMatrix<NT>(ws, H, nt0 * 16), acc);
+    else
+      sg_loop<true, MT, NT, NW, 2>(L, 0, X.slices(), X, prep, [&](int kb) { return a.Wp + sg_frag(kb, tiles, nt0, 0) * 64; }, acc);
+  }
+  if (KS && wv > 0) return;
+  sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
+    const int m = m0 + 16 * t + 4 * g + r, h = (nt0 + nt) * 16 + c;
+    if (m >= Mrows || h >= H) return 0.f;
+    const float* x = a.X + mlp_row(a, m, false) * d;
+    float s = 0.f;
+    for (int j = 0; j < d; ++j) s = fmaf(x[j], a.w[(int64_t)j * H + h], s);
+    return s;
+  });
 #pragma unroll
-  for (int nt = 0; nt < WT; ++nt) {
-    const int h = n0 + wn * 16 * WT + nt * 16 + (lane & 15);
+  for (int nt = 0; nt < NT; ++nt) {
+    const int h = (nt0 + nt) * 16 + c;
     if (h >= H) continue;
-    const float bias = b1[h];
 #pragma unroll
-    for (int mt = 0; mt < WT; ++mt)
+    for (int t = 0; t < MT; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t m = m0 + wm * 16 * WT + mt * 16 + 4 * (lane >> 4) + r;
-        if (m < Mrows) out[m * H + h] = a.ksplit == 2 ? acc[mt][nt][r] : fmaxf(acc[mt][nt][r] + bias, 0.f);
+        const int m = m0 + 16 * t + 4 * g + r;
+        if (m < Mrows) a.Hh[(int64_t)m * H + h] = fmaxf(acc[nt][t][r] + bias[nt], 0.f);
       }
   }
 }
@@ -207,39 +154,73 @@ __device__ __forceinline__ void mlp_tail_sum(const MlpArgs& a, int slabs, int64_
   }
 }
 
-template <int WT>
-__global__ __launch_bounds__(256) void k_mlp_dw1_mfma(MlpArgs a, int slabs, int64_t tail) {
-  if (blockIdx.y == gridDim.y - 1) {
-    mlp_tail_sum(a, slabs, tail, static_cast<int>(blockIdx.z), static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+// dW1[j][h] = sum_b X[row(i,b)][j] dA_i[b][h] on MT x NT tiles per wave (lane
+// (g, c) loads MT consecutive features of eight rows), dA as fragments from the
+// head.  A linear grid, a worker's blocks on one XCD (its fragments of dA meet
+// in one L2), the column chunks of one feature block neighbours; the last
+// n * parts blocks sum the head's slab partials.
+template <int MT, int NT, int NW, int OCC>
+__global__ __launch_bounds__(64 * NW, OCC) void k_mlp_dw1(MlpArgs a, int slabs, int64_t tail, int tiles, int kblocks,
+                                                         int fblocks, int chunks, int64_t per_xcd, int parts) {
+  static_assert(NW == 4, "the tail sum takes blocks of 256 threads");
+  if (blockIdx.x >= per_xcd * NXCD) {
+    const int q = static_cast<int>(blockIdx.x - per_xcd * NXCD);
+    mlp_tail_sum(a, slabs, tail, q / parts, q % parts, parts);
     return;
   }
-  constexpr int BM = 32 * WT;
-  __shared__ MfmaLds<WT> L;
-  __shared__ int sh_row[1024];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wm = wv >> 1, wn = wv & 1;
-  const int i = blockIdx.z;
-  const int j0 = blockIdx.y * BM, n0 = blockIdx.x * BM;
+  __shared__ SgLds<NT, NW> L;
+  __shared__ __attribute__((aligned(16))) uint32_t srow[DW1_ROWS];
+  const int64_t logical = (int64_t)(blockIdx.x % NXCD) * per_xcd + blockIdx.x / NXCD;
+  if (logical >= (int64_t)a.n * fblocks * chunks) return;
+  const int i = static_cast<int>(logical / (fblocks * chunks));
+  const int rem = static_cast<int>(logical % (fblocks * chunks));
+  const int fb = rem / chunks, nt0 = rem % chunks * NT;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int d = a.d, H = a.H, B = a.B;
-  const int64_t P = a.ldG ? a.ldG : (int64_t)d * H + H + (int64_t)H * a.C + a.C;   // row stride of G
+  const int64_t P = a.ldG ? a.ldG : (int64_t)d * H + tail;   // row stride of G
   const int64_t xrows = a.rows ? a.S : (int64_t)a.n * B;
   const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t das = make_rsrc(a.dA + (int64_t)i * B * H, static_cast<uint32_t>((int64_t)B * H * 4));
-  for (int b = tid; b < B; b += 256) sh_row[b] = static_cast<int>(mlp_row(a, i, b, false));
-  __syncthreads();
-  mfma_f32x4 acc[WT][WT];
-  mfma_zero<WT>(acc);
-  mfma_gemm_xt_r<WT>(L, xs, sh_row, d, j0, das, B, H, n0, acc);
+  const sg_u32x4* dp = a.Dp + (int64_t)i * kblocks * tiles * 192;
+  const int f0 = (fb * NW + wv) * 16 * MT;
+  uint32_t foff;
+  int shift;
+  sg_feature<MT>(f0 + MT * c, d, foff, shift);
+  const bool edge = f0 + 16 * MT > d;
+  sg_f32x4 acc[NT][MT];
+  sg_zero<MT, NT>(acc);
+  for (int c0 = 0; c0 < B; c0 += DW1_ROWS) {
+    const int nr = min(B - c0, DW1_ROWS), nb = (nr + SG_K - 1) / SG_K;
+    __syncthreads();
+    for (int b = tid; b < nb * SG_K; b += 64 * NW)
+      srow[b] = b < nr ? static_cast<uint32_t>(mlp_row(a, i, c0 + b, false) * d * 4) : kOutOfRange;
+    __syncthreads();
+    sg_loop<MT == 1, MT, NT, NW, 1>(
+        L, c0 / SG_K, c0 / SG_K + nb,
+        [&](int kb, float (&x)[MT][8]) { sg_load_cols<MT>(xs, srow + (kb * SG_K - c0) + 8 * g, foff, x); },
+        [&](int, float (&x)[MT][8]) { sg_shift<MT>(shift, edge, x); },
+        [&](int kb) { return dp + sg_frag(kb, tiles, nt0, 0) * 64; }, acc);
+  }
+  sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
+    const int j = f0 + MT * (4 * g + r) + t, h = (nt0 + nt) * 16 + c;
+    if (j >= d || h >= H) return 0.f;
+    float s = 0.f;
+    for (int b = 0; b < B; ++b) s = fmaf(a.X[mlp_row(a, i, b, false) * d + j], sg_unpack(dp, tiles, b, h), s);
+    return s;
+  });
+  // the G rows of workers outside the row mask are computed but not stored
+  if (a.row_mask && !a.row_mask[i]) return;
   float* Gi = a.G + (int64_t)i * P;
 #pragma unroll
-  for (int mt = 0; mt < WT; ++mt)
+  for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = j0 + wm * 16 * WT + mt * 16 + 4 * (lane >> 4) + r;
+    for (int t = 0; t < MT; ++t) {
+      const int j = f0 + MT * (4 * g + r) + t;
       if (j >= d) continue;
 #pragma unroll
-      for (int nt = 0; nt < WT; ++nt) {
-        const int h = n0 + wn * 16 * WT + nt * 16 + (lane & 15);
-        if (h < H && (!a.row_mask || a.row_mask[i])) Gi[(int64_t)j * H + h] = acc[mt][nt][r];
+      for (int nt = 0; nt < NT; ++nt) {
+        const int h = (nt0 + nt) * 16 + c;
+        if (h < H) Gi[(int64_t)j * H + h] = acc[nt][t][r];
       }
     }
 }
@@ -268,7 +249,7 @@ __device__ __forceinline__ float row16_sum(float v) {
 // Head: thread j < H owns hidden unit j (T == H rounded up to a wave multiple
 // is handled by the plan: T threads cover H with M units each).
 template <int CP, int M, int T>
-__global__ __launch_bounds__(T) void k_mlp_head(MlpArgs a, int slabs, int rps, int64_t L) {
+__global__ __launch_bounds__(T) void k_mlp_head(MlpArgs a, int slabs, int rps, int64_t L, int tiles, int kblocks) {
   constexpr int R = 4;
   constexpr int V = R * CP;
   constexpr int G = T / V;
@@ -295,35 +276,28 @@ __global__ __launch_bounds__(T) void k_mlp_head(MlpArgs a, int slabs, int rps, i
     rowv[k] = r < nrows ? mlp_row(a, i, b0 + r, false) : 0;
   }
   const int64_t hrow0 = (int64_t)i * a.B;
-  // rows cb .. cb + R - 1 as loaded: the activations, or with ksplit 2 the
-  // two K halves' sums (the second half sits in dA; this thread writes a
-  // row's dA entries only after it has read them).  The next rows are
-  // loaded one step ahead, so their latency overlaps a step's reductions.
-  auto load_rows = [&](int cb, float (&h1)[R][M], float (&h2)[R][M]) {
+  // rows cb .. cb + R - 1.  The next rows are loaded one step ahead, so their
+  // latency overlaps a step's reductions.
+  auto load_rows = [&](int cb, float (&h1)[R][M]) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const bool ok = cb + r < nrows;
       const int64_t hoff = (hrow0 + b0 + (ok ? cb + r : 0)) * H;
       const __amdgpu_buffer_rsrc_t hs = make_rsrc(a.Hh + hoff, ok ? static_cast<uint32_t>(H * 4) : 0u);
-      const __amdgpu_buffer_rsrc_t hd = make_rsrc(a.dA + hoff, ok && a.ksplit == 2 ? static_cast<uint32_t>(H * 4) : 0u);
 #pragma unroll
-      for (int m = 0; m < M; ++m) {
-        h1[r][m] = buf_f32(hs, static_cast<uint32_t>((tid + m * T) * 4));
-        h2[r][m] = buf_f32(hd, static_cast<uint32_t>((tid + m * T) * 4));
-      }
+      for (int m = 0; m < M; ++m) h1[r][m] = buf_f32(hs, static_cast<uint32_t>((tid + m * T) * 4));
     }
   };
-  float h1[R][M], h2[R][M];
-  load_rows(0, h1, h2);
+  float h1[R][M];
+  load_rows(0, h1);
   const float* W2 = a.w + (int64_t)d * H + H;
   const float* bias2 = W2 + (int64_t)H * C;
   const __amdgpu_buffer_rsrc_t w2s = make_rsrc(W2, static_cast<uint32_t>((int64_t)H * C * 4));
-  float wr[M][CP], gw2[M][CP], gb1[M], b1v[M];
+  float wr[M][CP], gw2[M][CP], gb1[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     const int j = tid + m * T;
     gb1[m] = 0.f;
-    b1v[m] = j < H ? a.w[(int64_t)d * H + j] : 0.f;
 #pragma unroll
     for (int c = 0; c < CP; ++c) {
       wr[m][c] = buf_f32(w2s, c < C ? static_cast<uint32_t>((j * C + c) * 4) : kOutOfRange);
@@ -340,8 +314,8 @@ __global__ __launch_bounds__(T) void k_mlp_head(MlpArgs a, int slabs, int rps, i
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int m = 0; m < M; ++m) x[r][m] = a.ksplit == 2 ? fmaxf(h1[r][m] + h2[r][m] + b1v[m], 0.f) : h1[r][m];
-    if (cb + R < nrows) load_rows(cb + R, h1, h2);
+      for (int m = 0; m < M; ++m) x[r][m] = h1[r][m];
+    if (cb + R < nrows) load_rows(cb + R, h1);
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -395,6 +369,7 @@ __global__ __launch_bounds__(T) void k_mlp_head(MlpArgs a, int slabs, int rps, i
       if (c == 0 && row_ok) loss_acc += logf(se) - zy;
     }
     __syncthreads();
+    float da[M][R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       float rv[CP];
@@ -410,10 +385,17 @@ __global__ __launch_bounds__(T) void k_mlp_head(MlpArgs a, int slabs, int rps, i
           dh = fmaf(rv[c], wr[m][c], dh);
           gw2[m][c] = fmaf(x[r][m], rv[c], gw2[m][c]);
         }
-        const float da = x[r][m] > 0.f ? dh : 0.f;
-        gb1[m] += da;
-        if (ok && j < H) a.dA[(hrow0 + b0 + cb + r) * H + j] = da;
+        da[m][r] = ok && x[r][m] > 0.f ? dh : 0.f;
+        gb1[m] += da[m][r];
+        if (a.dA && ok && j < H) a.dA[(hrow0 + b0 + cb + r) * H + j] = da[m][r];
       }
+    }
+    // the step's four rows of dA as fragments of the dW1 product (slabs start
+    // at multiples of 4 rows; rows past B stay as they were created, zero)
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int j = tid + m * T;
+      if (j < H) sg_store4(a.Dp + (int64_t)i * kblocks * tiles * 192, tiles, b0 + cb, j, da[m]);
     }
   }
   if (tid < WAVE) {
@@ -461,64 +443,29 @@ __global__ __launch_bounds__(T) void k_mlp_head(MlpArgs a, int slabs, int rps, i
   }
 }
 
-// dW1[j][h] = sum_b X[row(i,b)][j] dA[i*B + b][h]; blockIdx.z = worker; the
-// last grid row sums the head's slab partials.
-__global__ __launch_bounds__(256) void k_mlp_dw1(MlpArgs a, int slabs, int64_t tail) {
-  if (blockIdx.y == gridDim.y - 1) {
-    mlp_tail_sum(a, slabs, tail, static_cast<int>(blockIdx.z), static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
-    return;
-  }
-  __shared__ float As[TK][TM + 4];
-  __shared__ float Bs[TK][TN + 4];
-  const int tid = threadIdx.x, lane = tid % WAVE, wv = tid / WAVE;
-  const int wm = wv / 2, wn = wv % 2;
-  const int i = blockIdx.z;
-  const int j0 = blockIdx.y * TM;
-  const int n0 = blockIdx.x * TN;
-  const int d = a.d, H = a.H, B = a.B;
-  const int64_t P = a.ldG ? a.ldG : (int64_t)d * H + H + (int64_t)H * a.C + a.C;   // row stride of G
-  const int64_t xrows = a.rows ? a.S : (int64_t)a.n * B;
-  const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
-  const __amdgpu_buffer_rsrc_t das = make_rsrc(a.dA + (int64_t)i * B * H, static_cast<uint32_t>((int64_t)B * H * 4));
-  const int l_k = tid / 16, l_x = (tid % 16) * 4;
-  floatx4 acc[2][2];
-#pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < B; k0 += TK) {
-    const int b = k0 + l_k;
-    const int64_t xrow = b < B ? mlp_row(a, i, b, false) : -1;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int j = j0 + l_x + e;
-      As[l_k][l_x + e] = buf_f32(xs, (xrow >= 0 && j < d) ? static_cast<uint32_t>((xrow * d + j) * 4) : kOutOfRange);
-      const int nn = n0 + l_x + e;
-      Bs[l_k][l_x + e] = buf_f32(das, (b < B && nn < H) ? static_cast<uint32_t>(((int64_t)b * H + nn) * 4) : kOutOfRange);
-    }
-    __syncthreads();
-    mfma_tile_step(As, Bs, wm, wn, lane, acc);
-    __syncthreads();
-  }
-  float* Gi = a.G + (int64_t)i * P;
-#pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-      const int nn = n0 + wn * 32 + ni * 16 + lane % 16;
-      if (nn >= H) continue;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = j0 + wm * 32 + mi * 16 + 4 * (lane / 16) + e;
-        if (j < d && (!a.row_mask || a.row_mask[i])) Gi[(int64_t)j * H + nn] = acc[mi][ni][e];
-      }
-    }
-}
-
 template <int CP, int M, int T>
 hipError_t launch_head(const MlpPlan& p, const MlpArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((k_mlp_head<CP, M, T>), dim3(static_cast<unsigned>(a.n * p.slabs)), dim3(T), 0, s, a,
-                     p.slabs, p.rows_per_slab, p.tail);
+                     p.slabs, p.rows_per_slab, p.tail, p.tiles, (a.B + SG_K - 1) / SG_K);
+  return hipGetLastError();
+}
+
+template <int NT>
+hipError_t launch_dw1(const MlpPlan& p, const MlpArgs& a, hipStream_t s) {
+  const int kblocks = (a.B + SG_K - 1) / SG_K, chunks = p.tiles / NT;
+  const int parts = static_cast<int>(std::min<int64_t>(8, (p.tail + 1023) / 1024));
+  auto go = [&](auto kernel, int feats) {
+    const int fblocks = (a.d + feats - 1) / feats;
+    const int64_t per_xcd = ((int64_t)a.n * fblocks * chunks + NXCD - 1) / NXCD;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(per_xcd * NXCD + (int64_t)a.n * parts)), dim3(256), 0, s, a,
+                       p.slabs, p.tail, p.tiles, kblocks, fblocks, chunks, per_xcd, parts);
+  };
+  const int64_t w16 = (int64_t)a.n * chunks * ((a.d + 15) / 16);
+  // one feature a lane, or two (half the reads of dA) from 16384 tiles of 16
+  // features on: 32 x 64 x 784 x 512 (6272 tiles) 19.5 / 21.9 us, 16 x 256 x 3072 x
+  // 1024 (24576) 135 / 119, 16 x 500 x 800 x 500 (3200) 44.7 / 42.3
+  if (a.d < 2 || (w16 < 16384 && kblocks < 8)) go(k_mlp_dw1<1, NT, 4, 2>, 64);
+  else go(k_mlp_dw1<2, NT, 4, 3>, 128);
   return hipGetLastError();
 }
 
@@ -540,29 +487,49 @@ MlpPlan mlp_plan(int n, int B, int d, int H, int C) {
   p.rows_per_slab = (p.rows_per_slab + 3) / 4 * 4;
   if (p.rows_per_slab > 1024) p.rows_per_slab = 1024;
   p.slabs = (B + p.rows_per_slab - 1) / p.rows_per_slab;
+  // column tiles: of the hidden layer's W1 fragments, and of dA's (chunks of
+  // equal width, up to 8 tiles)
+  const int need = (H + 15) / 16, chunks = (need + 7) / 8;
+  p.nt = (need + chunks - 1) / chunks;
+  p.tiles = p.nt * chunks;
+  p.wtiles = (need + 7) / 8 * 8;
+  p.w_bytes = sg_frag_bytes((d + SG_K - 1) / SG_K, p.wtiles);
+  p.d_bytes = sg_frag_bytes((int64_t)n * ((B + SG_K - 1) / SG_K), p.tiles);
   p.ok = 1;
   return p;
 }
 
-hipError_t launch_mlp_grads(const MlpPlan& p, const MlpArgs& args, hipStream_t s) {
+hipError_t launch_mlp_grads(const MlpPlan& p, const MlpArgs& a, hipStream_t s) {
   if (!p.ok) return hipErrorNotSupported;
-  MlpArgs a = args;
-  a.ksplit = 1;
-  const int64_t Mrows = (int64_t)a.n * a.B;
-  const bool big = a.d % 4 == 0 && a.H % 4 == 0 && a.B <= 1024;
-  const int64_t small_tiles = (int64_t)((a.H + 63) / 64) * ((Mrows + 63) / 64);
-  if (big && (int64_t)((a.H + 127) / 128) * ((Mrows + 127) / 128) >= kMfmaBigTiles) {
-    hipLaunchKernelGGL(k_mlp_hidden_mfma<4>, dim3((a.H + 127) / 128, static_cast<unsigned>((Mrows + 127) / 128)),
-                       dim3(256), 0, s, a);
-  } else if (big) {
-    // too few 64 x 64 tiles for two blocks per CU: split K in two halves
-    if (small_tiles < kMfmaBigTiles && a.d >= 2 * MBK) a.ksplit = 2;
-    hipLaunchKernelGGL(k_mlp_hidden_mfma<2>,
-                       dim3((a.H + 63) / 64, static_cast<unsigned>((Mrows + 63) / 64), a.ksplit), dim3(256), 0, s, a);
+  const int64_t rt = ((int64_t)a.n * a.B + 15) / 16;
+  const int ct = (a.H + 15) / 16;
+  auto hidden = [&](auto kernel, int rows, int cols, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rt + rows - 1) / rows), (ct + cols - 1) / cols), dim3(threads), 0,
+                       s, a, p.wtiles);
+  };
+  auto pack = [&]() {
+    const int64_t tasks = (int64_t)((a.d + SG_K - 1) / SG_K) * p.wtiles;
+    hipLaunchKernelGGL(k_sg_pack, dim3(static_cast<unsigned>((tasks + 3) / 4)), dim3(256), 0, s, a.w, (int64_t)a.H, a.d, a.H,
+                       p.wtiles, a.Wp);
+  };
+  // Hidden layer by the number of row tiles times column chunks: with few, a
+  // block's eight waves split K of one row tile and read W1 itself; then 32
+  // columns a wave (512 blocks of 64 x 32 at 2048 x 512), from two blocks of 64
+  // x 128 per CU on those.  us, K-split / 32 / 64 / 128 columns: 114 x 836 x 784
+  // 11.8 / - / 20 / -; 2048 x 784 x 512 30.6 / 17.9 / 19.4 / 29.7; 8000 x 800 x
+  // 500 - / 69 / 46 / 43; 4096 x 3072 x 1024 - / - / 149 / 136.
+  if (a.d < 8) {
+    pack();
+    hidden(k_mlp_hidden<1, 4, 4, 2, false, true>, 4, 4, 256);
+  } else if (rt * ((ct + 3) / 4) <= 512) {
+    hidden(k_mlp_hidden<1, 4, 8, 2, true>, 1, 4, 512);
+  } else if (rt * ((ct + 7) / 8) < 1024) {
+    pack();
+    hidden(k_mlp_hidden<1, 2, 4, 2, false>, 4, 2, 256);
+  } else {
+    pack();
+    hidden(k_mlp_hidden<1, 8, 4, 2, false>, 4, 8, 256);
   }
-  else
-    hipLaunchKernelGGL(k_mlp_hidden, dim3((a.H + TN - 1) / TN, static_cast<unsigned>((Mrows + TM - 1) / TM)),
-                       dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   switch (p.cpad * 100 + p.per_thread * 10 + (p.threads == 512)) {
@@ -579,21 +546,17 @@ hipError_t launch_mlp_grads(const MlpPlan& p, const MlpArgs& args, hipStream_t s
     default: return hipErrorNotSupported;
   }
   if (e != hipSuccess) return e;
-  // X_i^T dA_i contracts over the worker's B rows only: with few rows the
-  // large tile's operand reuse buys little, and the short blocks of 64 x 64
-  // tiles overlap one another's stores with their matrix work (MLP 32 x 64:
-  // 75.7 -> 73.0 us per launch)
-  // (one extra grid row sums the head's slab partials into the tail of G)
-  if (big && a.B >= 256 && (int64_t)((a.H + 127) / 128) * ((a.d + 127) / 128) * a.n >= kMfmaBigTiles)
-    hipLaunchKernelGGL(k_mlp_dw1_mfma<4>, dim3((a.H + 127) / 128, (a.d + 127) / 128 + 1, a.n), dim3(256), 0, s, a,
-                       p.slabs, p.tail);
-  else if (big)
-    hipLaunchKernelGGL(k_mlp_dw1_mfma<2>, dim3((a.H + 63) / 64, (a.d + 63) / 64 + 1, a.n), dim3(256), 0, s, a,
-                       p.slabs, p.tail);
-  else
-    hipLaunchKernelGGL(k_mlp_dw1, dim3((a.H + TN - 1) / TN, (a.d + TM - 1) / TM + 1, a.n), dim3(256), 0, s, a,
-                       p.slabs, p.tail);
-  return hipGetLastError();
+  switch (p.nt) {
+    case 1: return launch_dw1<1>(p, a, s);
+    case 2: return launch_dw1<2>(p, a, s);
+    case 3: return launch_dw1<3>(p, a, s);
+    case 4: return launch_dw1<4>(p, a, s);
+    case 5: return launch_dw1<5>(p, a, s);
+    case 6: return launch_dw1<6>(p, a, s);
+    case 7: return launch_dw1<7>(p, a, s);
+    case 8: return launch_dw1<8>(p, a, s);
+  }
+  return hipErrorNotSupported;
 }
 
 }  // namespace dbw

@@ -516,7 +516,8 @@ constexpr int SG_DIRECT = 4;   // up to so many column tiles a K-split wave read
 template <int MT, int NT, int NW, int OCC, bool KS, bool NARROW, bool TINY = false>
 __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int tiles, int tpw) {
   __shared__ std::conditional_t<KS, SgRed<MT, NT, NW>, SgLds<NT, NW>> L;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, c = lane & 15;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int d = a.d, C = a.C, B = a.B;
   const int64_t xrows = a.rows ? a.S : (int64_t)a.n * B;
   const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
@@ -542,10 +543,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
     auto prep = [&](int kb, float (&x)[MT][8]) { X.prep(kb, x); };
     auto frag = [&](int kb) { return a.Wp + sg_frag(kb, tiles, nt0, 0) * 64; };
     if constexpr (KS && NT <= SG_DIRECT)
-      sg_loop_k<MT, NT, NW>(L, 0, X.slices(), X, prep, SgMatrix<NT>(make_rsrc(a.W, static_cast<uint32_t>((int64_t)d * C * 4)), C, nt0 * 16), acc);
+      sg_loop_k<true, MT, NT, NW>(L, 0, X.slices(), X, prep, SgMatrix<NT>(make_rsrc(a.W, static_cast<uint32_t>((int64_t)d * C * 4)), C, nt0 * 16), acc);
     else if constexpr (KS)
-      sg_loop_k<MT, NT, NW>(L, 0, X.slices(), X, prep, SgFrags<NT>{frag(0), (int64_t)tiles * 192}, acc);
-    else sg_loop<MT, NT, NW, MT == 1 ? 2 : 1>(L, 0, X.slices(), X, prep, frag, acc);
+      sg_loop_k<true, MT, NT, NW>(L, 0, X.slices(), X, prep, SgFrags<NT>{frag(0), (int64_t)tiles * 192}, acc);
+    else
+      sg_loop<(MT == 1 && NT <= 4), MT, NT, NW, MT == 1 ? 2 : 1>(L, 0, X.slices(), X, prep, frag, acc);
   }
   if (KS && wv > 0) return;
   sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
@@ -695,7 +697,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_grads(SoftmaxArgs a, int ti
   const int i = static_cast<int>(logical / (fblocks * chunks));
   const int rem = static_cast<int>(logical % (fblocks * chunks));
   const int fb = rem / chunks, nt0 = rem % chunks * NT;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, c = lane & 15;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int d = a.d, C = a.C, B = a.B;
   const int64_t xrows = a.rows ? a.S : (int64_t)a.n * B;
   const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
@@ -717,8 +720,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_grads(SoftmaxArgs a, int ti
     auto prep = [&](int, float (&x)[MT][8]) { sg_shift<MT>(shift, edge, x); };
     auto frag = [&](int kb) { return rp + sg_frag(kb, tiles, nt0, 0) * 64; };
     if constexpr (KS)
-      sg_loop_k<MT, NT, NW>(L, c0 / SG_K, c0 / SG_K + nb, load, prep, SgFrags<NT>{frag(0), (int64_t)tiles * 192}, acc);
-    else sg_loop<MT, NT, NW, MT == 1 ? 2 : 1>(L, c0 / SG_K, c0 / SG_K + nb, load, prep, frag, acc);
+      sg_loop_k<(NT < 8), MT, NT, NW>(L, c0 / SG_K, c0 / SG_K + nb, load, prep, SgFrags<NT>{frag(0), (int64_t)tiles * 192}, acc);
+    else
+      sg_loop<MT == 1, MT, NT, NW, MT == 1 ? 2 : 1>(L, c0 / SG_K, c0 / SG_K + nb, load, prep, frag, acc);
   }
   sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
     const int j = f0 + MT * (4 * g + r) + t, cc = (nt0 + nt) * 16 + c;
@@ -768,7 +772,7 @@ hipError_t launch_split_nt(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rt + per - 1) / per), chunks), dim3(threads), 0, s, a, tiles, tpw);
   };
   // Waves per SIMD of the large logits blocks: as many as leave no spills.
-  constexpr int OC8 = NT >= 6 ? 2 : 4;
+  constexpr int OC8 = NT >= 4 ? 2 : 4;
   // Logits by the number of row tiles times column chunks: with few, a block's
   // eight waves split K of one row tile (kSplitK); then one row tile a wave,
   // four waves a block; from two full rounds of the chip on, 16 row tiles a

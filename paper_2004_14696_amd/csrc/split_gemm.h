@@ -108,22 +108,35 @@ __device__ __forceinline__ sg_f32x4 sg_mfma(const sg_u32x4& a, const sg_u32x4& b
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(sg_op(a), sg_op(b), c, 0, 0, 0);
 }
 
-// acc[mt] += A[mt] B for one column tile: the six products, small ones first.
-template <int MT>
-__device__ __forceinline__ void sg_products(const SgParts (&a)[MT], const sg_u32x4& bh, const sg_u32x4& bm, const sg_u32x4& bl,
-                                            sg_f32x4 (&acc)[MT]) {
+// acc[mt] += A[mt] B for one column tile.  APART: the five small products are
+// summed by themselves (their roundings are some 2^-8 of the accumulator's) and
+// added with the large one, so an accumulator is rounded twice a slice of 32 K
+// instead of six times.  Gradient error against 64 bits, together / apart / fp32
+// instruction: MLP 32 x 64 x 784-512-10 1.7e-7 / 0.8e-7 / 1.4e-7, MLP 16 x 256 x
+// 3072-1024-10 5.7e-7 / 2.9e-7 / 6.1e-7, softmax 20 x 300 x 1200 x 60 2.5e-7 /
+// 1.3e-7 / 3.1e-7, 256 x 512 x 3072 x 100 3.2e-7 / 1.7e-7 / 4.1e-7.  It takes
+// registers and 6 - 10% of the time of a kernel that is bound by its products,
+// so the wide tiles of the softmax keep one sum.
+template <bool APART, int MT>
+__device__ __forceinline__ void sg_products(const SgParts (&a)[MT], const sg_u32x4& bh, const sg_u32x4& bm,
+                                            const sg_u32x4& bl, sg_f32x4 (&acc)[MT]) {
+  sg_f32x4 small[MT];
 #pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t] = sg_mfma(a[t].l, bh, acc[t]);
+  for (int t = 0; t < MT; ++t) small[t] = APART ? sg_f32x4{0.f, 0.f, 0.f, 0.f} : acc[t];
 #pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t] = sg_mfma(a[t].h, bl, acc[t]);
+  for (int p = 0; p < 5; ++p)
 #pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t] = sg_mfma(a[t].m, bm, acc[t]);
+    for (int t = 0; t < MT; ++t) {
+      const sg_u32x4& x = p == 0 ? a[t].l : p == 2 || p == 3 ? a[t].m : a[t].h;
+      const sg_u32x4& y = p == 1 ? bl : p == 2 || p == 4 ? bm : bh;
+      small[t] = sg_mfma(x, y, small[t]);
+    }
 #pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t] = sg_mfma(a[t].m, bh, acc[t]);
+  for (int t = 0; t < MT; ++t) acc[t] = sg_mfma(a[t].h, bh, APART ? acc[t] : small[t]);
+  if constexpr (APART) {
 #pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t] = sg_mfma(a[t].h, bm, acc[t]);
-#pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t] = sg_mfma(a[t].h, bh, acc[t]);
+    for (int t = 0; t < MT; ++t) acc[t] += small[t];
+  }
 }
 
 // Two slices' B fragments; padded to whole rounds of the block's NW waves.
@@ -152,10 +165,11 @@ __device__ __forceinline__ void sg_barrier() {
 // slice's first B fragment (NT * 3 of them, consecutive), prep(kb, x) runs just
 // before a slice's values are split.  PD slices are on their way in registers
 // (PD = 2 where a block's matrix work per slice is shorter than a memory
-// latency); a slice's B fragments are loaded before its A values, so that
-// storing them to LDS does not wait for the A values.  Loads past the last
-// slice repeat it, so that the number in flight is the same at every step.
-template <int MT, int NT, int NW, int PD, class Load, class Prep, class Frag>
+// latency; 4 gained nothing more, nor did two teams of waves that split K); a
+// slice's B fragments are loaded before its A values, so that storing them to
+// LDS does not wait for the A values.  Loads past the last slice repeat it, so
+// that the number in flight is the same at every step.
+template <bool APART, int MT, int NT, int NW, int PD, class Load, class Prep, class Frag>
 __device__ __forceinline__ void sg_loop(SgLds<NT, NW>& L, int kb0, int kb1, Load&& load, Prep&& prep, Frag&& frag,
                                         sg_f32x4 (&acc)[NT][MT]) {
   static_assert(PD == 1 || PD == 2, "register slots");
@@ -195,7 +209,7 @@ __device__ __forceinline__ void sg_loop(SgLds<NT, NW>& L, int kb0, int kb1, Load
     __builtin_amdgcn_sched_barrier(0);   // the loads go out before the products
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
-      sg_products<MT>(a, L.B[u][3 * nt][lane], L.B[u][3 * nt + 1][lane], L.B[u][3 * nt + 2][lane], acc[nt]);
+      sg_products<APART, MT>(a, L.B[u][3 * nt][lane], L.B[u][3 * nt + 1][lane], L.B[u][3 * nt + 2][lane], acc[nt]);
     // a column tile's fragments are read while the previous tile's products run
     __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
 #pragma unroll
@@ -207,10 +221,14 @@ __device__ __forceinline__ void sg_loop(SgLds<NT, NW>& L, int kb0, int kb1, Load
     stage(u ^ 1, rb[next]);
     sg_barrier();
   };
-  for (int kb = kb0; kb < kb1; kb += 2) {
+  // (whole pairs in the loop: a way round the second slice would make the
+  // compiler wait for every load at the loop's head)
+  int kb = kb0;
+  for (; kb + 1 < kb1; kb += 2) {
     slice(kb, std::integral_constant<int, 0>{});
-    if (kb + 1 < kb1) slice(kb + 1, std::integral_constant<int, 1>{});
+    slice(kb + 1, std::integral_constant<int, 1>{});
   }
+  if (kb < kb1) slice(kb, std::integral_constant<int, 0>{});
 }
 
 // The loop for products with few tiles: the block's NW waves work on the same
@@ -271,7 +289,7 @@ template <int MT, int NT, int NW>
 struct SgRed {
   sg_f32x4 v[NW - 1][NT * MT][64];
 };
-template <int MT, int NT, int NW, class Load, class Prep, class Bsrc>
+template <bool APART, int MT, int NT, int NW, class Load, class Prep, class Bsrc>
 __device__ __forceinline__ void sg_loop_k(SgRed<MT, NT, NW>& R, int kb0, int kb1, Load&& load, Prep&& prep,
                                           const Bsrc& bsrc, sg_f32x4 (&acc)[NT][MT]) {
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -296,7 +314,7 @@ __device__ __forceinline__ void sg_loop_k(SgRed<MT, NT, NW>& R, int kb0, int kb1
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) sg_products<MT>(a, bp[nt][0], bp[nt][1], bp[nt][2], acc[nt]);
+    for (int nt = 0; nt < NT; ++nt) sg_products<APART, MT>(a, bp[nt][0], bp[nt][1], bp[nt][2], acc[nt]);
   }
   if (wv > 0) {
 #pragma unroll

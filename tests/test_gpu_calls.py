@@ -108,6 +108,50 @@ def test_worker_grads_softmax_split_products(n, B, d, C, S):
         assert rel_err(host(loss)[i], li[0]) <= tol
 
 
+# The MLP's products at the same kinds of edges: features and hidden units off
+# the tiles and load widths, rows off 4, 16 and 32 and beyond the 1024 staged
+# offsets, and sizes on both sides of each launch rule.  (n, B, d, H, C, S)
+MLP_SPLIT_SHAPES = [
+    (2, 5, 1, 17, 3, 9), (2, 30, 7, 33, 10, 40), (3, 33, 8, 16, 2, 7), (2, 17, 31, 130, 16, 0), (1, 1030, 65, 48, 4, 500),
+    (6, 19, 836, 784, 8, 0), (10, 499, 381, 135, 10, 3000), (40, 100, 1023, 1001, 3, 900), (32, 64, 784, 512, 10, 2000),
+    (16, 256, 515, 1024, 10, 0), (200, 12, 130, 100, 5, 300),
+]
+
+
+@pytest.mark.parametrize("n,B,d,H,C,S", MLP_SPLIT_SHAPES)
+def test_worker_grads_mlp_split_products(n, B, d, H, C, S):
+    g = torch.Generator(device="cuda").manual_seed(n * 31 + B * 7 + d * 3 + H)
+    X = torch.randn((S, d) if S else (n, B, d), generator=g, device="cuda")
+    y = torch.randint(0, C, X.shape[:-1], generator=g, device="cuda", dtype=torch.int32)
+    rows = torch.randint(0, S, (n, B), generator=g, device="cuda", dtype=torch.int32) if S else None
+    if S:
+        rows[0, 0], rows[-1, -1] = 0, S - 1
+    W1 = (2.0 / d) ** 0.5 * torch.randn((d, H), generator=g, device="cuda")
+    W2 = (2.0 / H) ** 0.5 * torch.randn((H, C), generator=g, device="cuda")
+    # offsets that keep every pre-activation away from the ReLU's kink (within
+    # rounding of it either decision is right)
+    A = (X[rows.reshape(-1).long()] if S else X.reshape(-1, d)).double() @ W1.double()
+    cand = torch.linspace(-0.2, 0.2, 129, device="cuda", dtype=torch.float64)
+    gap = torch.stack([(A + c).abs().amin(dim=0) for c in cand])
+    b1 = cand[gap.argmax(dim=0)].float()
+    w = torch.cat([W1.reshape(-1), b1, W2.reshape(-1), 0.1 * torch.ones(C, device="cuda")])
+    ctx = _ctx(n, B, d, C, S=S, model="mlp", H=H)
+    G, loss = ctx.worker_grads(w, X, y, rows=rows)
+    ctx.sync()
+    # rounding of fp32 sums of d, H and B terms, in units of the largest entry
+    # of a parameter block; db2 is a sum of B residuals (p - onehot) / B that
+    # may cancel: in units of their magnitudes' sum, which is below 1
+    tol = 2.0 ** -23 * (16 + d ** 0.5 + H ** 0.5 + B ** 0.5)
+    bounds = np.cumsum([0, d * H, H, H * C, C])
+    for i in sorted({0, n // 2, n - 1}):
+        Xi, yi = (X[rows[i].long()], y[rows[i].long()]) if S else (X[i], y[i])
+        Go, lo = omodel.mlp_worker_grads(host(w).astype(np.float64), host(Xi)[None].astype(np.float64), host(yi)[None], H, C)
+        for a, b in zip(bounds[:-2], bounds[1:-1]):
+            assert rel_err(host(G)[i][a:b], Go[0][a:b]) <= tol, (i, a)
+        assert np.max(np.abs(host(G)[i][-C:] - Go[0][-C:])) <= tol, i
+        assert rel_err(host(loss)[i], lo[0]) <= tol
+
+
 @pytest.mark.parametrize("n,B,d,C", [(3, 20, 40, 20), (2, 33, 77, 130), (40, 300, 45, 12)])
 def test_worker_grads_softmax_non_finite_inputs(n, B, d, C):
     # Infinite and nearly overflowing inputs give what fp32 arithmetic gives:
