@@ -89,6 +89,7 @@ struct dbw_ctx {
   dbw::sg_u32x4* Rp = nullptr;
   float* Z = nullptr;
   float* ce = nullptr;
+  float* ce_row = nullptr;
   float* sqpart = nullptr;
   double* part = nullptr;
   float* Hh = nullptr;
@@ -464,7 +465,7 @@ dbw_status launch_grads(dbw_ctx* c, const float* w, const float* X, const int32_
     a.W = w; a.X = X; a.y = y; a.rows = rows; a.S = cf.S;
     a.n = cf.n; a.B = cf.B; a.d = cf.d; a.C = cf.C;
     a.G = G; a.loss = loss;
-    a.Gp = c->Gp; a.lossp = c->lossp; a.Wp = c->Wp; a.Rp = c->Rp; a.Z = c->Z; a.ce = c->ce;
+    a.Gp = c->Gp; a.lossp = c->lossp; a.Wp = c->Wp; a.Rp = c->Rp; a.Z = c->Z; a.ce = c->ce; a.ce_row = c->ce_row;
     a.err = c->err;
     a.keep_slabs = keep_slabs ? 1 : 0;
     a.row_mask = row_mask;
@@ -553,7 +554,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
   const dbw_config& cf = c->cfg;
   const int64_t n = cf.n, P = c->P, rowsN = (int64_t)cf.n * cf.B;
   if (cf.model == DBW_SOFTMAX) {
-    c->splan = dbw::softmax_plan(cf.n, cf.B, cf.d, cf.C);
+    c->splan = dbw::softmax_plan(cf.n, cf.B, cf.d, cf.C, cf.S);
   } else {
     // the CNN's fully connected part is the MLP on its 800 features
     c->mplan = dbw::mlp_plan(cf.n, cf.B, cf.model == DBW_CNN ? dbw::CNN_FEAT : cf.d, cf.H, cf.C);
@@ -590,7 +591,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
        sSqp = take(sizeof(float) * n * part_blocks), sPart = take(sizeof(double) * 2 * part_blocks);
   Span sGa;
   if (c->copy_rows) sGa = take(sizeof(float) * n * P);
-  Span sGp, sLp, sWp, sRp, sZ, sCe, sH, sdA, sH1, sC1, sF, sC2, sYl, sdP2, sdP1, sPa1, sPa2;
+  Span sGp, sLp, sWp, sRp, sZ, sCe, sCr, sH, sdA, sH1, sC1, sF, sC2, sYl, sdP2, sdP1, sPa1, sPa2;
   if (cf.model == DBW_SOFTMAX) {
     if (c->splan.fused) {
       if (c->splan.slabs > 1) {
@@ -602,10 +603,14 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
       sRp = take(c->splan.r_bytes);
       sZ = take(sizeof(float) * c->splan.z_floats);
       sCe = take(sizeof(float) * rowsN);
+      sCr = take(sizeof(float) * c->splan.row_floats);
     }
   } else {
     sH = take(sizeof(float) * rowsN * cf.H);
-    sWp = take(c->mplan.w_bytes);
+    // (the CNN packs Wf1 and then its transpose)
+    sWp = take(cf.model == DBW_CNN ? std::max(c->mplan.w_bytes,
+                                              dbw::sg_frag_bytes((cf.H + dbw::SG_K - 1) / dbw::SG_K, dbw::CNN_FEAT / 16))
+                                   : c->mplan.w_bytes);
     sRp = take(c->mplan.d_bytes);
     if (cf.model == DBW_CNN) sdA = take(sizeof(float) * rowsN * cf.H);
     sGp = take(sizeof(float) * n * c->mplan.slabs * c->mplan.tail);
@@ -636,7 +641,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
   c->Ga = c->copy_rows ? (float*)at(sGa) : c->G;
   c->Gp = (float*)at(sGp); c->lossp = (float*)at(sLp);
   c->Wp = (dbw::sg_u32x4*)at(sWp); c->Rp = (dbw::sg_u32x4*)at(sRp);
-  c->Z = (float*)at(sZ); c->ce = (float*)at(sCe); c->Hh = (float*)at(sH); c->dA = (float*)at(sdA);
+  c->Z = (float*)at(sZ); c->ce = (float*)at(sCe); c->ce_row = (float*)at(sCr); c->Hh = (float*)at(sH); c->dA = (float*)at(sdA);
   c->cH1 = (float*)at(sH1); c->cCode1 = (uint8_t*)at(sC1); c->cF = (float*)at(sF); c->cCode2 = (uint8_t*)at(sC2);
   c->cYlab = (int32_t*)at(sYl); c->cdP2 = (float*)at(sdP2); c->cdP1 = (float*)at(sdP1);
   c->cPart1 = (float*)at(sPa1); c->cPart2 = (float*)at(sPa2);

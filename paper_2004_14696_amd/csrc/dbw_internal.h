@@ -40,7 +40,8 @@ struct SoftmaxPlan {
   int tiles = 0;          // 16-column tiles of all classes, a multiple of per_thread
   int64_t w_bytes = 0;    // W and the residuals as product fragments
   int64_t r_bytes = 0;
-  int64_t z_floats = 0;   // logits, where a wave does not hold all classes
+  int64_t z_floats = 0;   // logits, where a wave does not hold all classes, or rows of the dataset
+  int64_t row_floats = 0; // cross entropy of the dataset's rows
 };
 
 struct MlpPlan {
@@ -73,14 +74,17 @@ struct SoftmaxArgs {
   float* lossp;          // [n*slabs]
   sg_u32x4* Wp;             // W as product fragments (GEMM path)
   sg_u32x4* Rp;             // the residuals as product fragments, by worker (GEMM path)
-  float* Z;              // [n*B][C] logits (GEMM path, more than one column chunk)
+  float* Z;              // [n*B][C] logits (GEMM path, more than one column chunk), or
+                         // [S][C] logits or residuals of the dataset's rows
   float* ce;             // [n*B] per-row CE (GEMM path)
+  float* ce_row;         // [S] CE of the dataset's rows
+  int B_mean;            // rows of a minibatch, where B is the dataset's rows
   int32_t* err;
   int keep_slabs;        // 1: leave the slab partials for the PS kernel (no slab reduction)
   const uint8_t* row_mask;  // nullable [n]: G rows only of workers with a nonzero entry
 };
 
-SoftmaxPlan softmax_plan(int n, int B, int d, int C);
+SoftmaxPlan softmax_plan(int n, int B, int d, int C, int64_t S);
 hipError_t launch_softmax_grads(const SoftmaxPlan& plan, const SoftmaxArgs& a, hipStream_t s);
 
 struct MlpArgs {

@@ -44,10 +44,12 @@
 
 #include "dbw_buffer.h"
 #include "dbw_internal.h"
-#include "mfma_gemm.h"
+#include "split_gemm.h"
 
 namespace dbw {
 namespace {
+
+typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int IMG = CNN_IMG, KS = 5, NC1 = CNN_C1, NC2 = CNN_C2;
 constexpr int Q1 = 12, NPOS1 = Q1 * Q1, H1LEN = NC1 * NPOS1;   // 2880 per image
@@ -218,58 +220,45 @@ __global__ __launch_bounds__(256, 2) void k_cnn_conv2_pool(CnnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// dP2[m][f] = sum_h dA[m][h] Wf1[f][h]; 64 x 64 tiles.
-__global__ __launch_bounds__(256) void k_cnn_dfeat(CnnArgs a) {
-  __shared__ MfmaLds<2> L;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wm = wv >> 1, wn = wv & 1;
-  const int64_t nB = (int64_t)a.n * a.B;
-  const int H = a.H;
-  const int n0 = blockIdx.x * 64;
-  const int64_t m0 = (int64_t)blockIdx.y * 64;
-  const float* Wf1 = a.w;     // [800][H]
-  auto load = [&](int k0, float (&ra)[4], float (&rb)[4]) {
+// dP2[m][f] = sum_h dA[m][h] Wf1[f][h] on MT x DF_NT tiles of 16 x 16 per wave
+// (split_gemm.h), Wf1^T as fragments; blockIdx.x = 4 MT row tiles, y = DF_NT
+// column tiles.  8000 x 800 x 500: 92 us on the fp32 matrix cores.
+constexpr int DF_NT = 5, DF_TILES = FEAT / 16;
+static_assert(DF_TILES % DF_NT == 0, "whole column chunks");
+template <int MT, bool TINY>
+__global__ __launch_bounds__(256, 2) void k_cnn_dfeat(CnnArgs a) {
+  __shared__ SgLds<DF_NT, 4> L;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nB = a.n * a.B, H = a.H;   // nB below 2^30
+  const int m0 = (static_cast<int>(blockIdx.x) * 4 + wv) * MT * 16, nt0 = static_cast<int>(blockIdx.y) * DF_NT;
+  SgRows<MT, TINY> A(make_rsrc(a.dA, static_cast<uint32_t>((int64_t)nB * H * 4)), H);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int e = tid + 256 * s;
-      const int k = k0 + e % 16, i = e / 16;
-      const int64_t m = m0 + i;
-      ra[s] = k < H && m < nB ? a.dA[m * H + k] : 0.f;
-      const int f = n0 + i;
-      rb[s] = k < H && f < FEAT ? Wf1[(int64_t)f * H + k] : 0.f;
-    }
-  };
-  auto store = [&](int buf, const float (&ra)[4], const float (&rb)[4]) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int e = tid + 256 * s;
-      L.A[buf][e % 16][e / 16] = ra[s];
-      L.B[buf][e % 16][e / 16] = rb[s];
-    }
-  };
-  mfma_f32x4 acc[2][2];
-  mfma_zero<2>(acc);
-  float ra[4], rb[4];
-  load(0, ra, rb);
-  store(0, ra, rb);
-  __syncthreads();
-  const int nk = (H + MBK - 1) / MBK;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cbuf = kt & 1;
-    if (kt + 1 < nk) load((kt + 1) * MBK, ra, rb);
-    mfma_slice<2>(L, cbuf, wm, wn, lane, acc);
-    if (kt + 1 < nk) store(cbuf ^ 1, ra, rb);
-    __syncthreads();
+  for (int t = 0; t < MT; ++t) {
+    const int m = m0 + 16 * t + c;
+    A.roff[t] = m < nB ? static_cast<uint32_t>((int64_t)m * H * 4) + 32 * g : kOutOfRange;
   }
+  sg_f32x4 acc[DF_NT][MT];
+  sg_zero<MT, DF_NT>(acc);
+  sg_loop<true, MT, DF_NT, 4, 2>(
+      L, 0, A.slices(), A, [&](int kb, float (&x)[MT][8]) { A.prep(kb, x); },
+      [&](int kb) { return a.Wp + sg_frag(kb, DF_TILES, nt0, 0) * 64; }, acc);
+  sg_redo<MT, DF_NT>(acc, [&](int t, int r, int nt) {
+    const int m = m0 + 16 * t + 4 * g + r, f = (nt0 + nt) * 16 + c;
+    if (m >= nB) return 0.f;
+    float s = 0.f;
+    for (int h = 0; h < H; ++h) s = fmaf(a.dA[(int64_t)m * H + h], a.w[(int64_t)f * H + h], s);
+    return s;
+  });
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
+  for (int t = 0; t < MT; ++t)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + 16 * t + 4 * g + r;
+      if (m >= nB) continue;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t m = m0 + wm * 32 + mt * 16 + 4 * (lane >> 4) + r;
-        const int f = n0 + wn * 32 + nt * 16 + (lane & 15);
-        if (m < nB && f < FEAT) a.dP2[m * FEAT + f] = acc[mt][nt][r];
-      }
+      for (int nt = 0; nt < DF_NT; ++nt) a.dP2[(int64_t)m * FEAT + (nt0 + nt) * 16 + c] = acc[nt][t][r];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -718,7 +707,16 @@ hipError_t launch_cnn_grads(const MlpPlan& mplan, const CnnArgs& a, hipStream_t 
   m.Hh = a.Hh; m.Wp = a.Wp; m.Dp = a.Dp; m.dA = a.dA; m.Gp = a.Gp; m.lossp = a.lossp; m.err = a.err; m.row_mask = a.row_mask;
   e = launch_mlp_grads(mplan, m, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_cnn_dfeat, dim3((FEAT + 63) / 64, static_cast<unsigned>((nB + 63) / 64)), dim3(256), 0, s, a);
+  // Wf1's own fragments are no longer needed: its transpose takes their place
+  const int64_t tasks = (int64_t)((a.H + SG_K - 1) / SG_K) * DF_TILES;
+  hipLaunchKernelGGL(k_sg_pack, dim3(static_cast<unsigned>((tasks + 3) / 4)), dim3(256), 0, s, a.w, int64_t{1}, (int64_t)a.H,
+                     a.H, FEAT, DF_TILES, a.Wp);
+  auto dfeat = [&](auto kernel, int rows) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((nB + rows - 1) / rows), DF_TILES / DF_NT), dim3(256), 0, s, a);
+  };
+  if (a.H < 8) dfeat(k_cnn_dfeat<1, true>, 64);
+  else if (nB < 4096) dfeat(k_cnn_dfeat<1, false>, 64);
+  else dfeat(k_cnn_dfeat<2, false>, 128);
   const int64_t dg_blocks = nB < kDgradBlocks ? nB : kDgradBlocks;
   hipLaunchKernelGGL(k_cnn_conv2_dgrad, dim3(static_cast<unsigned>(dg_blocks)), dim3(256), 0, s, a);
   const int chunks = cnn_chunks(a.B);

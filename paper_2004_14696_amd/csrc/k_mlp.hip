@@ -509,7 +509,7 @@ hipError_t launch_mlp_grads(const MlpPlan& p, const MlpArgs& a, hipStream_t s) {
   };
   auto pack = [&]() {
     const int64_t tasks = (int64_t)((a.d + SG_K - 1) / SG_K) * p.wtiles;
-    hipLaunchKernelGGL(k_sg_pack, dim3(static_cast<unsigned>((tasks + 3) / 4)), dim3(256), 0, s, a.w, (int64_t)a.H, a.d, a.H,
+    hipLaunchKernelGGL(k_sg_pack, dim3(static_cast<unsigned>((tasks + 3) / 4)), dim3(256), 0, s, a.w, (int64_t)a.H, int64_t{1}, a.d, a.H,
                        p.wtiles, a.Wp);
   };
   // Hidden layer by the number of row tiles times column chunks: with few, a

@@ -19,6 +19,7 @@
 // index from a resident dataset; both read each sample once per pass.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <type_traits>
@@ -510,10 +511,14 @@ constexpr int SG_DIRECT = 4;   // up to so many column tiles a K-split wave read
 // blockIdx.x = NW MT row tiles, blockIdx.y = NT column tiles.  NARROW: all
 // classes are in the wave: softmax, residuals (p - onehot(y)) / B as
 // fragments and the rows' cross entropy.  Otherwise Z is stored.  KS: the
-// block's waves share MT row tiles and split K (sg_loop_k).  256 x 512 x 3072 x
+// block's waves share MT row tiles and split K (sg_loop_k).  PER_ROW: the rows
+// are those of the dataset (n = 1, B = S), the residuals stay as rows in Z and
+// the cross entropy in ce_row; labels are not reported here (a row may be in no
+// minibatch).  256 x 512 x 3072 x
 // 100: 430 - 475 us (fp32 matrix-core form 629), 1.6 GB of X at 3.4 - 3.7 TB/s
 // and 1.1 - 1.3 PFLOP/s of issued bf16 products, both near what the chip holds.
-template <int MT, int NT, int NW, int OCC, bool KS, bool NARROW, bool TINY = false>
+template <int MT, int NT, int NW, int OCC, bool KS, bool NARROW, bool TINY = false,
+          bool PER_ROW = false>
 __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int tiles, int tpw) {
   __shared__ std::conditional_t<KS, SgRed<MT, NT, NW>, SgLds<NT, NW>> L;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -523,7 +528,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
   const __amdgpu_buffer_rsrc_t xs = make_rsrc(a.X, static_cast<uint32_t>(xrows * d * 4));
   const int t0 = (KS ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * NW + wv) * MT;
   const int nt0 = static_cast<int>(blockIdx.y) * NT;
-  const bool report = blockIdx.y == 0 && g == 0 && (!KS || wv == 0);
+  const bool report = !PER_ROW && blockIdx.y == 0 && g == 0 && (!KS || wv == 0);
   SgRows<MT, TINY> X(xs, d);
   int lab[MT];
 #pragma unroll
@@ -561,9 +566,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
 
   if (NARROW) {
 #pragma unroll
-    for (int t = 0; t < MT; ++t) lab[t] = checked_label(a, lab[t]);
+    for (int t = 0; t < MT; ++t) {
+      if (PER_ROW) lab[t] = lab[t] < 0 || lab[t] >= C ? 0 : lab[t];
+      else lab[t] = checked_label(a, lab[t]);
+    }
   }
-  const float invB = 1.0f / static_cast<float>(B);
+  const float invB = 1.0f / static_cast<float>(PER_ROW ? a.B_mean : B);
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
     const int i = (t0 + t) / tpw, bt = (t0 + t) % tpw;
@@ -601,9 +609,18 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
           const int cc = nt * 16 + c;
-          if (ok && cc == lr) a.ce[(int64_t)i * B + b0 + r] = (logf(se) + mx) - acc[nt][t][r];
+          if (ok && cc == lr) (PER_ROW ? a.ce_row : a.ce)[(int64_t)i * B + b0 + r] = (logf(se) + mx) - acc[nt][t][r];
           acc[nt][t][r] = ok && cc < C ? (ex[nt] * inv - (cc == lr ? 1.f : 0.f)) * invB : 0.f;
         }
+      }
+      if constexpr (PER_ROW) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (b0 + r < B)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+              if (nt * 16 + c < C) a.Z[(int64_t)(b0 + r) * C + nt * 16 + c] = acc[nt][t][r];
+        continue;
       }
       sg_u32x4* rp = a.Rp + (int64_t)i * ((tpw + 1) / 2) * tiles * 3 * 64;
 #pragma unroll
@@ -619,61 +636,90 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
   }
 }
 
-// Residuals of C > 16 SG_NARROW classes: row softmax of Z, residuals as
-// fragments, ce[m] = CE.  Block (x, i): rows 8 x .. 8 x + 7 of worker i (padded
-// to whole slices of 32), held in LDS; every wave runs two rows' statistics and
-// leaves their exponentials, then packs a quarter of the columns.
+// Residuals as fragments and ce[m] = CE from rows in Z: logits of the
+// minibatches' rows (ZROWS_BATCH) or of the dataset's rows (ZROWS_DATASET: the
+// row of sample m is its dataset row), of which the row softmax is taken here,
+// or the dataset rows' residuals (ZROWS_RESIDUAL, with ce_row).  Block (x, i):
+// rows 8 x .. 8 x + 7 of worker i (padded to whole slices of 32), held in LDS;
+// every wave runs two rows' statistics and leaves their exponentials, then
+// packs a quarter of the columns.
+enum ZRows { ZROWS_BATCH, ZROWS_DATASET, ZROWS_RESIDUAL };
+template <int FROM>
 __global__ __launch_bounds__(256) void k_rows_pack(SoftmaxArgs a, int tiles, int kblocks) {
   extern __shared__ float zrow[];   // [8][C]
   __shared__ float sh_inv[8];
-  __shared__ int sh_lab[8];
+  __shared__ int sh_lab[8], sh_row[8];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int i = blockIdx.y, b0 = static_cast<int>(blockIdx.x) * 8;
   const int C = a.C, B = a.B;
   const int nr = max(0, min(8, B - b0)), nz = nr * C;
-  const float* z0 = a.Z + ((int64_t)i * B + b0) * C;
-  for (int e0 = 0; e0 < nz; e0 += 8 * 256) {
-    float v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = e0 + q * 256 + tid < nz ? z0[e0 + q * 256 + tid] : 0.f;
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      if (e0 + q * 256 + tid < nz) zrow[e0 + q * 256 + tid] = v[q];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int r = 2 * wv + q;
-    if (r >= nr) break;
-    float* z = zrow + r * C;
-    const int lab = sample_label(a, sample_row(a, i, b0 + r, false), lane == 0);
-    float mx = -INFINITY;
-    for (int c = lane; c < C; c += WAVE) mx = fmaxf(mx, z[c]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, WAVE));
-    const float zy = z[lab];
-    float se = 0.f;
-    for (int c = lane; c < C; c += WAVE) {
-      const float ex = expf(z[c] - mx);
-      z[c] = ex;
-      se += ex;
+  if (FROM != ZROWS_BATCH) {
+    if (tid < nr) {
+      const int64_t row = sample_row(a, i, b0 + tid, true);
+      sh_row[tid] = static_cast<int>(row);
+      (void)sample_label(a, row, true);
+      if (FROM == ZROWS_RESIDUAL) a.ce[(int64_t)i * B + b0 + tid] = a.ce_row[row];
     }
+    __syncthreads();
+    // a wave copies two rows
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o, WAVE);
-    if (lane == 0) {
-      sh_inv[r] = 1.0f / se;
-      sh_lab[r] = lab;
-      a.ce[(int64_t)i * B + b0 + r] = (logf(se) + mx) - zy;
+    for (int q = 0; q < 2; ++q) {
+      const int r = 2 * wv + q;
+      if (r >= nr) break;
+      const float* z = a.Z + (int64_t)sh_row[r] * C;
+      for (int c = lane; c < C; c += WAVE) zrow[r * C + c] = z[c];
+    }
+  } else {
+    const float* z0 = a.Z + ((int64_t)i * B + b0) * C;
+    for (int e0 = 0; e0 < nz; e0 += 8 * 256) {
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = e0 + q * 256 + tid < nz ? z0[e0 + q * 256 + tid] : 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (e0 + q * 256 + tid < nz) zrow[e0 + q * 256 + tid] = v[q];
     }
   }
   __syncthreads();
+  if (FROM != ZROWS_RESIDUAL) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int r = 2 * wv + q;
+      if (r >= nr) break;
+      float* z = zrow + r * C;
+      const int lab = sample_label(a, sample_row(a, i, b0 + r, false), FROM == ZROWS_BATCH && lane == 0);
+      float mx = -INFINITY;
+      for (int c = lane; c < C; c += WAVE) mx = fmaxf(mx, z[c]);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, WAVE));
+      const float zy = z[lab];
+      float se = 0.f;
+      for (int c = lane; c < C; c += WAVE) {
+        const float ex = expf(z[c] - mx);
+        z[c] = ex;
+        se += ex;
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o, WAVE);
+      if (lane == 0) {
+        sh_inv[r] = 1.0f / se;
+        sh_lab[r] = lab;
+        a.ce[(int64_t)i * B + b0 + r] = (logf(se) + mx) - zy;
+      }
+    }
+    __syncthreads();
+  }
   const float invB = 1.0f / static_cast<float>(B);
   sg_u32x4* rp = a.Rp + (int64_t)i * kblocks * tiles * 3 * 64;
   for (int c = tid; c < tiles * 16; c += 256) {
     float v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      v[e] = e < nr && c < C ? (zrow[e * C + c] * sh_inv[e] - (c == sh_lab[e] ? 1.f : 0.f)) * invB : 0.f;
+    for (int e = 0; e < 8; ++e) {
+      v[e] = 0.f;
+      if (e < nr && c < C)
+        v[e] = FROM == ZROWS_RESIDUAL ? zrow[e * C + c]
+                                      : (zrow[e * C + c] * sh_inv[e] - (c == sh_lab[e] ? 1.f : 0.f)) * invB;
+    }
     sg_store8(rp, tiles, b0, c, v);
   }
 }
@@ -763,32 +809,63 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_grads(SoftmaxArgs a, int ti
   }
 }
 
+// Whether the logits run over the dataset's rows (see launch_split_nt).  Below
+// 1.5 samples a row the gather costs what the shared rows save; below 8192
+// rows (two row tiles a CU) there is nothing to save.
+bool split_per_row(int n, int B, int d, int64_t S) {
+  return S >= 8192 && d >= 8 && 2 * (int64_t)n * B >= 3 * S;
+}
+
 template <int NT>
 hipError_t launch_split_nt(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t s) {
   const int tiles = p.tiles, tpw = (a.B + 15) / 16, kblocks = (a.B + SG_K - 1) / SG_K;
   const int chunks = tiles / NT;
-  const int64_t rt = (int64_t)a.n * tpw;
+  // With (well) more samples than dataset rows, the logits, residuals and cross
+  // entropy of every dataset row are computed once and gathered by the
+  // minibatches (they depend on the row and w alone): 256 x 512 samples of a
+  // 50000 x 3072 dataset, 100 classes, 470 us of logits -> 216 and 38 of gathering;
+  // 100 x 300 of 20000 x 500, 60 classes, 65 -> 51 the launch.
+  const bool per_row = split_per_row(a.n, a.B, a.d, a.rows ? a.S : 0);
+  SoftmaxArgs al = a;   // the rows of the logits product
+  if (per_row) {
+    al.rows = nullptr;
+    al.n = 1;
+    al.B = static_cast<int>(a.S);
+    al.B_mean = a.B;
+  }
+  const int ltpw = per_row ? (al.B + 15) / 16 : tpw;
+  const int64_t rt = (int64_t)al.n * ltpw;
   auto logits = [&](auto kernel, int per, int threads) {
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rt + per - 1) / per), chunks), dim3(threads), 0, s, a, tiles, tpw);
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rt + per - 1) / per), chunks), dim3(threads), 0, s, al, tiles, ltpw);
+  };
+  auto pack = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(4 * kblocks, a.n), dim3(256), 8 * sizeof(float) * a.C, s, a, tiles, kblocks);
   };
   // Waves per SIMD of the large logits blocks: as many as leave no spills.
   constexpr int OC8 = NT >= 4 ? 2 : 4;
   // Logits by the number of row tiles times column chunks: with few, a block's
   // eight waves split K of one row tile (kSplitK); then one row tile a wave,
-  // four waves a block; from two full rounds of the chip on, 16 row tiles a
-  // block, which reads W half as often.  us of the launch, the large / middle /
-  // K-split form: 256 x 512 x 3072 x 100 (8192 tiles) 934 / 1028 / 1641; 128 x
+  // four waves a block; from two full rounds of the chip on (or one of wide
+  // tiles), 16 row tiles a block, which reads its fragments half as often.  us
+  // of the launch, the large / middle / K-split form: 256 x 512 x 3072 x 100
+  // (8192 tiles) 934 / 1028 / 1641; its logits over 50000 dataset rows (3125
+  // tiles of 7 columns) 216 / 289 / -; 20000 x 500 x 60 (1250) 28 / 17 / -; 128 x
   // 512 x 256 x 50 (4096) 51 / 49 / 81; 64 x 256 x 3072 x 100 (1024) 250 / 163 /
   // 209; 32 x 200 x 1024 x 64 (416) 73 / 40 / 36; 16 x 100 x 785 x 20 (112)
   // 40 / 25 / 17.
   enum { kLarge, kMiddle, kSplitK, kTiny };
-  const int lv = a.d < 8 ? kTiny : rt * chunks >= 8192 ? kLarge : rt * chunks > 512 ? kMiddle : kSplitK;
+  const int lv = a.d < 8 ? kTiny : rt * chunks >= 8192 || rt * chunks * NT >= 20000 ? kLarge
+                 : rt * chunks > 512 || per_row ? kMiddle : kSplitK;
   if (lv != kSplitK || NT > SG_DIRECT) {
     const int64_t wtasks = (int64_t)((a.d + SG_K - 1) / SG_K) * tiles;
-    hipLaunchKernelGGL(k_sg_pack, dim3(static_cast<unsigned>((wtasks + 3) / 4)), dim3(256), 0, s, a.W, (int64_t)a.C, a.d,
+    hipLaunchKernelGGL(k_sg_pack, dim3(static_cast<unsigned>((wtasks + 3) / 4)), dim3(256), 0, s, a.W, (int64_t)a.C, int64_t{1}, a.d,
                        a.C, tiles, a.Wp);
   }
-  if (chunks == 1) {
+  if (chunks == 1 && per_row) {
+    if (lv == kLarge) logits(k_sg_logits<2, NT, 8, OC8, false, true, false, true>, 16, 512);
+    else logits(k_sg_logits<1, NT, 4, 2, false, true, false, true>, 4, 256);
+    pack(k_rows_pack<ZROWS_RESIDUAL>);
+  } else if (chunks == 1) {
     if (lv == kLarge) logits(k_sg_logits<2, NT, 8, OC8, false, true>, 16, 512);
     else if (lv == kMiddle) logits(k_sg_logits<1, NT, 4, 2, false, true>, 4, 256);
     else if (lv == kTiny) logits(k_sg_logits<1, NT, 4, 2, false, true, true>, 4, 256);
@@ -798,7 +875,8 @@ hipError_t launch_split_nt(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream
     else if (lv == kMiddle) logits(k_sg_logits<1, NT, 4, 2, false, false>, 4, 256);
     else if (lv == kTiny) logits(k_sg_logits<1, NT, 4, 2, false, false, true>, 4, 256);
     else logits(k_sg_logits<1, NT, 8, 2, true, false>, 1, 512);
-    hipLaunchKernelGGL(k_rows_pack, dim3(4 * kblocks, a.n), dim3(256), 8 * sizeof(float) * a.C, s, a, tiles, kblocks);
+    if (per_row) pack(k_rows_pack<ZROWS_DATASET>);
+    else pack(k_rows_pack<ZROWS_BATCH>);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -868,7 +946,7 @@ hipError_t launch_mfma_c(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t
 // GEMM path: column tiles of a wave (per_thread) and of all classes.  Up to
 // SG_NARROW tiles a wave holds all of them; else chunks of equal width.
 constexpr int SG_NARROW = 8;
-SoftmaxPlan split_plan(int n, int B, int d, int C) {
+SoftmaxPlan split_plan(int n, int B, int d, int C, int64_t S) {
   SoftmaxPlan p;
   const int need = (C + 15) / 16, chunks = (need + SG_NARROW - 1) / SG_NARROW;
   p.per_thread = (need + chunks - 1) / chunks;
@@ -876,6 +954,10 @@ SoftmaxPlan split_plan(int n, int B, int d, int C) {
   p.w_bytes = sg_frag_bytes((d + SG_K - 1) / SG_K, p.tiles);
   p.r_bytes = sg_frag_bytes((int64_t)n * ((B + SG_K - 1) / SG_K), p.tiles);
   p.z_floats = chunks > 1 ? (int64_t)n * B * C : 0;
+  if (split_per_row(n, B, d, S)) {
+    p.z_floats = std::max(p.z_floats, S * C);
+    p.row_floats = S;
+  }
   return p;
 }
 
@@ -893,13 +975,13 @@ SoftmaxPlan split_plan(int n, int B, int d, int C) {
 constexpr int64_t kSinglePassMin = 6500000;   // elements of the minibatches
 constexpr int kSinglePassMinD = 256;
 
-SoftmaxPlan softmax_plan(int n, int B, int d, int C) {
+SoftmaxPlan softmax_plan(int n, int B, int d, int C, int64_t S) {
   SoftmaxPlan p;
   const int cw = C <= 4 ? 4 : C <= 10 ? 10 : C <= 16 ? 16 : 0;
   const int U = (d + MF_T - 1) / MF_T;
   const bool fits = cw == 16 ? U <= 4 : U <= 6;
   if (!cw || d % 4 != 0 || !fits || (int64_t)n * B * d < kSinglePassMin || d < kSinglePassMinD)
-    return split_plan(n, B, d, C);
+    return split_plan(n, B, d, C, S);
   // 8 waves x 64U features, W staged in LDS
   p.fused = 1;
   p.per_thread = U;
@@ -916,7 +998,7 @@ SoftmaxPlan softmax_plan(int n, int B, int d, int C) {
   p.slabs = (B + rps - 1) / rps;
   p.part = (int64_t)MF_T * U * C;   // tile-order partial
   // one worker's partials are read through one buffer resource
-  return (int64_t)p.slabs * p.part * 4 <= kMaxBufferBytes ? p : split_plan(n, B, d, C);
+  return (int64_t)p.slabs * p.part * 4 <= kMaxBufferBytes ? p : split_plan(n, B, d, C, S);
 }
 
 hipError_t launch_softmax_grads(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t s) {

@@ -504,10 +504,10 @@ __device__ __forceinline__ void sg_store8(sg_u32x4* frags, int64_t tiles, int k0
   p[128] = l;
 }
 
-// A K x N matrix (row-major, rows ld apart) into fragments, zeros past K and
-// N; one wave per slice and column tile, `tiles` column tiles.
-__global__ __launch_bounds__(256) inline void k_sg_pack(const float* src, int64_t ld, int K, int N, int tiles,
-                                                        sg_u32x4* frags) {
+// A K x N matrix (element (k, n) at k ldk + n ldn) into fragments, zeros past K
+// and N; one wave per slice and column tile, `tiles` column tiles.
+__global__ __launch_bounds__(256) inline void k_sg_pack(const float* src, int64_t ldk, int64_t ldn, int K, int N,
+                                                        int tiles, sg_u32x4* frags) {
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int64_t kblocks = (K + SG_K - 1) / SG_K;
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(256) inline void k_sg_pack(const float* src, int64_
   const int k0 = kb * SG_K + 8 * (lane >> 4), n = 16 * nt + (lane & 15);
   float v[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = k0 + e < K && n < N ? src[(int64_t)(k0 + e) * ld + n] : 0.f;
+  for (int e = 0; e < 8; ++e) v[e] = k0 + e < K && n < N ? src[(k0 + e) * ldk + n * ldn] : 0.f;
   sg_store8(frags, tiles, k0, n, v);
 }
 

@@ -108,6 +108,48 @@ def test_worker_grads_softmax_split_products(n, B, d, C, S):
         assert rel_err(host(loss)[i], li[0]) <= tol
 
 
+# More samples than 2/3 of the dataset's rows: logits and residuals are formed
+# per dataset row and gathered.  On both sides of the rule, with all classes in
+# a wave and in chunks.
+@pytest.mark.parametrize("n,B,d,C,S", [(24, 512, 40, 20, 8192), (23, 534, 40, 20, 8192), (25, 500, 9, 130, 8200),
+                                       (40, 300, 515, 100, 8000), (30, 1100, 77, 7, 20001)])
+def test_worker_grads_softmax_shared_dataset_rows(n, B, d, C, S):
+    g = torch.Generator(device="cuda").manual_seed(n + B + d + C)
+    X = torch.randn((S, d), generator=g, device="cuda")
+    y = torch.randint(0, C, (S,), generator=g, device="cuda", dtype=torch.int32)
+    rows = torch.randint(1, S - 1, (n, B), generator=g, device="cuda", dtype=torch.int32)
+    rows[0, 0], rows[-1, -1] = 0, S - 1
+    W = 0.3 / d ** 0.5 * torch.randn(d * C, generator=g, device="cuda")
+    # a row of no minibatch may hold anything
+    free = int((torch.bincount(rows.reshape(-1).long(), minlength=S) == 0).nonzero()[0])
+    X[free], y[free] = float("nan"), C + 5
+    ctx = _ctx(n, B, d, C, S=S)
+    G, loss = ctx.worker_grads(W, X, y, rows=rows)
+    ctx.sync()
+    tol = 2.0 ** -23 * (8 + d ** 0.5 + B ** 0.5)
+    for i in (0, n // 2, n - 1):
+        Xi, yi = X[rows[i].long()], y[rows[i].long()]
+        Gi, li = omodel.softmax_worker_grads(host(W).astype(np.float64), host(Xi)[None].astype(np.float64),
+                                             host(yi)[None], C)
+        assert rel_err(host(G)[i], Gi[0]) <= tol
+        assert rel_err(host(loss)[i], li[0]) <= tol
+    # the same minibatches passed materialised
+    Gm, lm = ctx.worker_grads(W, X[rows.long()], y[rows.long()])
+    ctx.sync()
+    assert rel_err(host(G), host(Gm)) <= 2 * tol and rel_err(host(loss), host(lm)) <= 2 * tol
+    # a bad label or row index is reported once it is in a minibatch
+    rows[1, 3] = free
+    ctx.worker_grads(W, X, y, rows=rows)
+    with pytest.raises(pb.DBWError) as e:
+        ctx.sync()
+    assert e.value.status == pb.DBW_EINVAL
+    rows[1, 3] = S
+    ctx.worker_grads(W, X, y, rows=rows)
+    with pytest.raises(pb.DBWError) as e:
+        ctx.sync()
+    assert e.value.status == pb.DBW_ERANGE
+
+
 # The MLP's products at the same kinds of edges: features and hidden units off
 # the tiles and load widths, rows off 4, 16 and 32 and beyond the 1024 staged
 # offsets, and sizes on both sides of each launch rule.  (n, B, d, H, C, S)
