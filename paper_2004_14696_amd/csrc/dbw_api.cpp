@@ -95,6 +95,7 @@ struct dbw_ctx {
   float* Hh = nullptr;
   float* dA = nullptr;
   // CNN workspace
+  dbw::sg_u32x4* cW2p = nullptr;
   float* cH1 = nullptr;
   uint8_t* cCode1 = nullptr;
   float* cF = nullptr;
@@ -476,7 +477,7 @@ dbw_status launch_grads(dbw_ctx* c, const float* w, const float* X, const int32_
     a.n = cf.n; a.B = cf.B; a.H = cf.H; a.C = cf.C;
     a.P = c->P; a.off_c1 = c->P - dbw::CNN_CONV_PARAMS; a.off_c2 = a.off_c1 + dbw::CNN_C1 * 25 + dbw::CNN_C1;
     a.G = G; a.loss = loss;
-    a.H1 = c->cH1; a.code1 = c->cCode1; a.F = c->cF; a.code2 = c->cCode2; a.ylab = c->cYlab;
+    a.W2p = c->cW2p; a.H1 = c->cH1; a.code1 = c->cCode1; a.F = c->cF; a.code2 = c->cCode2; a.ylab = c->cYlab;
     a.dP2 = c->cdP2; a.dP1 = c->cdP1; a.part1 = c->cPart1; a.part2 = c->cPart2; a.chunk = dbw::kCnnChunk;
     a.Hh = c->Hh; a.Wp = c->Wp; a.Dp = c->Rp; a.dA = c->dA; a.Gp = c->Gp; a.lossp = c->lossp; a.err = c->err; a.row_mask = row_mask;
     e = dbw::launch_cnn_grads(c->mplan, a, c->stream);
@@ -591,7 +592,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
        sSqp = take(sizeof(float) * n * part_blocks), sPart = take(sizeof(double) * 2 * part_blocks);
   Span sGa;
   if (c->copy_rows) sGa = take(sizeof(float) * n * P);
-  Span sGp, sLp, sWp, sRp, sZ, sCe, sCr, sH, sdA, sH1, sC1, sF, sC2, sYl, sdP2, sdP1, sPa1, sPa2;
+  Span sGp, sLp, sWp, sRp, sZ, sCe, sCr, sH, sdA, sW2, sH1, sC1, sF, sC2, sYl, sdP2, sdP1, sPa1, sPa2;
   if (cf.model == DBW_SOFTMAX) {
     if (c->splan.fused) {
       if (c->splan.slabs > 1) {
@@ -617,6 +618,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
     sLp = take(sizeof(float) * n * c->mplan.slabs);
     if (cf.model == DBW_CNN) {
       const int64_t h1 = rowsN * dbw::CNN_C1 * 144, ch = dbw::cnn_chunks(cf.B);
+      sW2 = take(dbw::kCnnW2Bytes);
       sH1 = take(sizeof(float) * h1);
       sC1 = take(h1);
       sF = take(sizeof(float) * rowsN * dbw::CNN_FEAT);
@@ -642,6 +644,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
   c->Gp = (float*)at(sGp); c->lossp = (float*)at(sLp);
   c->Wp = (dbw::sg_u32x4*)at(sWp); c->Rp = (dbw::sg_u32x4*)at(sRp);
   c->Z = (float*)at(sZ); c->ce = (float*)at(sCe); c->ce_row = (float*)at(sCr); c->Hh = (float*)at(sH); c->dA = (float*)at(sdA);
+  c->cW2p = (dbw::sg_u32x4*)at(sW2);
   c->cH1 = (float*)at(sH1); c->cCode1 = (uint8_t*)at(sC1); c->cF = (float*)at(sF); c->cCode2 = (uint8_t*)at(sC2);
   c->cYlab = (int32_t*)at(sYl); c->cdP2 = (float*)at(sdP2); c->cdP1 = (float*)at(sdP1);
   c->cPart1 = (float*)at(sPa1); c->cPart2 = (float*)at(sPa2);

@@ -115,6 +115,7 @@ hipError_t launch_mlp_grads(const MlpPlan& plan, const MlpArgs& a, hipStream_t s
 // 800-H-C.  Parameters [MLP (800-H-C) | Wc1 (20x1x5x5) | bc1 | Wc2 (50x20x5x5) | bc2].
 constexpr int CNN_IMG = 28, CNN_C1 = 20, CNN_C2 = 50, CNN_FEAT = 800;
 constexpr int64_t CNN_CONV_PARAMS = CNN_C1 * 25 + CNN_C1 + CNN_C2 * CNN_C1 * 25 + CNN_C2;
+constexpr int64_t kCnnW2Bytes = 17 * 4 * 3 * 1024;   // Wc2 as product fragments
 constexpr int kCnnChunk = 16;   // images per weight-gradient partial
 struct CnnArgs {
   const float* w;        // [P]
@@ -127,6 +128,7 @@ struct CnnArgs {
   float* G;              // [n][P]
   float* loss;           // [n]
   // workspace
+  sg_u32x4* W2p;         // Wc2 as product fragments
   float* H1;             // [n*B][20][12][12] pooled, ReLU'd conv1 output
   uint8_t* code1;        // [n*B][20][12][12] window code of each pooled value (4: ReLU off)
   float* F;              // [n*B][800] pooled, ReLU'd conv2 output (the features)

@@ -14,11 +14,10 @@
 //                     conv outputs of its window for all 20 filters (vector
 //                     ALU, filters in LDS), the pooled value, its ReLU and the
 //                     window code; also gathers the image's label.
-//  k_cnn_conv2_pool   the conv as a 64 x 64 x 500 GEMM per image on the fp32
-//                     matrix cores (positions x filters x (channel, row,
-//                     column) of the 5 x 5 patches), filter fragments held in
-//                     registers by a persistent grid, the image's H1 in LDS;
-//                     pooling and ReLU in the epilogue.
+//  k_cnn_conv2_pool   the conv as a 64 x 64 x 500 GEMM per image (positions x
+//                     filters x patches) on the split products of
+//                     split_gemm.h, one image a wave, W2's fragments shared
+//                     through LDS; pooling and ReLU in the epilogue.
 //  k_cnn_dfeat        dF = dA Wf1^T on the matrix cores (the ReLU mask of F is
 //                     in the window codes).
 //  k_cnn_conv2_dgrad  gradient at H1: per image and input channel the GEMM
@@ -40,6 +39,7 @@
 // Everything runs in a fixed order: results are bitwise reproducible.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "dbw_buffer.h"
@@ -125,96 +125,216 @@ __global__ __launch_bounds__(256) void k_cnn_conv1_pool(CnnArgs a) {
 
 // ---------------------------------------------------------------------------
 // Conv2 as a GEMM per image: Z[m][o] = sum_k A[m][k] W2[o][k], m = output
-// position (y, x) of the 8 x 8, k = (c, u, v), A[m][k] = H1[c][y+u][x+v].
-// The K steps of 4 run over (tap t, channel quad): step 5 t + cq takes
-// channels 4 cq .. 4 cq + 3 at tap t, so that every A read is the lane's own
-// LDS offset plus a constant.  Wave w owns filters 16 w .. 16 w + 15 and holds
-// their 125 W2 fragments in registers for the whole (persistent) launch; the
-// next image's H1 is loaded while the current one is multiplied.  Bias, 2 x 2
-// pooling and ReLU run from an LDS copy of Z.
-constexpr int FW_KS = K2 / 4;            // 125 K steps
-constexpr int kConvBlocks = 512;         // two blocks per CU
-struct Conv2Lds {
-  float h1[2][H1LEN];
-  float z[2][NPOS2][NC2 + 1];
-};
+// position (y, x) of the 8 x 8, k = (channel, tap), A[m][k] = H1[c][y+u][x+v], on
+// the split products (split_gemm.h).  A wave takes one image at a time, all 64
+// positions x 64 filters (4 x 4 tiles; 50 filters), so that every im2col value
+// is read from LDS once a wave.  The image lies in the wave's LDS as its three
+// bf16 parts, channels innermost; K is ordered so that a lane's eight values
+// are two runs of four channels at constant offsets from the lane's own
+// address:
+//   slices 0 .. 12   taps 2 s and 2 s + 1, channels 4 g .. 4 g + 3 (g = lane / 16)
+//   slices 13 .. 15  channels 16 .. 19, row g of the taps, columns 2 s, 2 s + 1
+//   slice 16         channels 16 .. 19, row 4, columns g and (g = 0) 4
+// (entries past the 5 x 5 taps have zero weights).  W2's fragments pass through
+// LDS a slice at a time, shared by the block's four waves; the next image's
+// values are on their way in registers meanwhile.  Bias, 2 x 2 pooling and ReLU
+// run in registers: a window's two rows are in lanes 32 apart.  With few images
+// (SHARED) the block's waves take the same one, a column tile each.  8000
+// images: 167 us (fp32 matrix cores 294), 0.95 PFLOP/s of issued bf16 products;
+// one wave a SIMD, so the LDS reads are placed by hand between the products of
+// the column tile before (202 us left to the compiler).
+constexpr int C2_SLICES = 17, C2_TILES = 4;
+constexpr int C2_POS = 148;                        // positions of a part (144; reads with zero weights pass the end)
+constexpr int C2_PART = C2_POS * NC1;              // bf16 values of one part
+constexpr int C2_TASKS = (NPOS1 * 5 + 63) / 64;    // (position, four channels) pieces of a lane
+constexpr int kConvBlocks = 256;                   // one block of four waves per CU
+static_assert(NC1 == 20 && KS == 5, "slice layout");
+static_assert(kCnnW2Bytes == C2_SLICES * C2_TILES * 3 * 1024, "fragments of Wc2");
 
-__global__ __launch_bounds__(256, 2) void k_cnn_conv2_pool(CnnArgs a) {
-  __shared__ __align__(16) Conv2Lds L;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, j = lane & 15;
-  const float* W2 = a.w + a.off_c2;
-  const float* b2 = W2 + NC2 * K2;
-  const int o_mine = 16 * wv + j;
-  float wb[FW_KS];
-#pragma unroll
-  for (int t = 0; t < 25; ++t)
-#pragma unroll
-    for (int cq = 0; cq < 5; ++cq)
-      wb[5 * t + cq] = o_mine < NC2 ? W2[o_mine * K2 + (4 * cq + g) * 25 + t] : 0.f;
-  const float bias = o_mine < NC2 ? b2[o_mine] : 0.f;
-  // A operand of lane (g, j): channel 4 cq + g, position m = 16 mt + j
-  const int abase = g * NPOS1 + (j >> 3) * Q1 + (j & 7);
-  const int64_t nB = (int64_t)a.n * a.B;
-  float4 rh[3];
-  auto fetch = [&](int64_t b) {
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      const int e = tid + 256 * s;
-      rh[s] = e < H1LEN / 4 ? reinterpret_cast<const float4*>(a.H1 + b * H1LEN)[e] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  auto stage = [&](float* h) {
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      const int e = tid + 256 * s;
-      if (e < H1LEN / 4) reinterpret_cast<float4*>(h)[e] = rh[s];
-    }
-  };
-  int64_t b = blockIdx.x;
-  if (b < nB) {
-    fetch(b);
-    stage(L.h1[0]);
+// Tap and first channel of run j (of two) of lane group g in a slice; tap -1:
+// no such tap.
+__device__ __forceinline__ void c2_run(int kb, int g, int j, int& tap, int& ch) {
+  if (kb < 13) {
+    tap = 2 * kb + j;
+    ch = 4 * g;
+  } else {
+    const int u = kb < 16 ? g : 4, v = kb < 16 ? 2 * (kb - 13) + j : g + 4 * j;
+    tap = v < KS ? u * KS + v : -1;
+    ch = 16;
   }
+  if (tap >= KS * KS) tap = -1;
+}
+
+__global__ __launch_bounds__(256) void k_cnn_pack_w2(CnnArgs a) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int t = static_cast<int>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (t >= C2_SLICES * C2_TILES) return;
+  const int kb = t / C2_TILES, o = 16 * (t % C2_TILES) + c;
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    int tap, ch;
+    c2_run(kb, g, j, tap, ch);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      v[4 * j + q] = o < NC2 && tap >= 0 ? a.w[a.off_c2 + o * K2 + (ch + q) * 25 + tap] : 0.f;
+  }
+  sg_store8(a.W2p, C2_TILES, kb * SG_K + 8 * g, o, v);
+}
+
+template <bool SHARED>
+__global__ __launch_bounds__(256, 1) void k_cnn_conv2_pool(CnnArgs a) {
+  constexpr int NT = SHARED ? 1 : C2_TILES;         // column tiles of a wave
+  constexpr int IMAGES = SHARED ? 1 : 4;            // images of a block
+  __shared__ __align__(16) uint16_t img[4][3][C2_PART];
+  __shared__ SgLds<C2_TILES, 4> L;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const float* b2 = a.w + a.off_c2 + NC2 * K2;
+  const int nt0 = SHARED ? wv : 0;
+  float bias[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) bias[nt] = 16 * (nt0 + nt) + c < NC2 ? b2[16 * (nt0 + nt) + c] : 0.f;
+  for (int e = lane; e < 3 * C2_PART; e += 64) (&img[wv][0][0])[e] = 0;
+  const int nB = a.n * a.B;
+  float4 h[C2_TASKS];
+  auto fetch = [&](int b) {
+#pragma unroll
+    for (int s = 0; s < C2_TASKS; ++s) {
+      const int e = lane + 64 * s, cq = e / NPOS1, pos = e - cq * NPOS1;
+      const bool ok = b < nB && e < NPOS1 * 5;
+      const float* src = a.H1 + (int64_t)(ok ? b : 0) * H1LEN + (ok ? 4 * cq * NPOS1 + pos : 0);
+      h[s] = make_float4(src[0], src[NPOS1], src[2 * NPOS1], src[3 * NPOS1]);
+    }
+  };
+  auto put = [&]() {
+#pragma unroll
+    for (int s = 0; s < C2_TASKS; ++s) {
+      const int e = lane + 64 * s, cq = e / NPOS1, pos = e - cq * NPOS1;
+      if (e >= NPOS1 * 5) break;
+      const SgPair u = sg_split2(h[s].x, h[s].y), v = sg_split2(h[s].z, h[s].w);
+      uint16_t* p = &img[wv][0][pos * NC1 + 4 * cq];
+      *reinterpret_cast<sg_u32x2*>(p) = sg_u32x2{u.h, v.h};
+      *reinterpret_cast<sg_u32x2*>(p + C2_PART) = sg_u32x2{u.m, v.m};
+      *reinterpret_cast<sg_u32x2*>(p + 2 * C2_PART) = sg_u32x2{u.l, v.l};
+    }
+  };
+  sg_u32x4 rb[3];
+  auto fetch_w = [&](int kb) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) rb[q] = a.W2p[(sg_frag(kb, C2_TILES, 0, 0) + wv + 4 * q) * 64 + lane];
+  };
+  auto stage_w = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) L.B[buf][wv + 4 * q][lane] = rb[q];
+  };
+  // position of tile row c (m = 16 mt + c: y = 2 mt + c / 8, x = c % 8)
+  const int pos0 = (c >> 3) * Q1 + (c & 7);
+  const uint16_t* im = &img[wv][0][0];
+  const uint16_t* base1 = im + pos0 * NC1 + 4 * g;
+  const uint16_t* base2 = im + (pos0 + g * Q1) * NC1 + 16;
+  const uint16_t* base3 = im + (pos0 + 4 * Q1 + g) * NC1 + 16;
+  const int stride = static_cast<int>(gridDim.x) * IMAGES;
+  int b = static_cast<int>(blockIdx.x) * IMAGES + (SHARED ? 0 : wv);
+  fetch_w(0);
+  fetch(b);
+  stage_w(0);
   __syncthreads();
-  for (int it = 0; b < nB; b += gridDim.x, ++it) {
-    const int cur = it & 1;
-    if (b + gridDim.x < nB) fetch(b + gridDim.x);
-    mfma_f32x4 acc[4];
+  int buf = 0;
+  for (int b0 = static_cast<int>(blockIdx.x) * IMAGES; b0 < nB; b0 += stride, b += stride) {
+    put();
+    asm volatile("" ::: "memory");   // the wave's LDS writes precede its reads
+    fetch(b + stride);
+    sg_f32x4 acc[NT][4];
+    sg_zero<4, NT>(acc);
+    // tile mt of a slice's A operand
+    auto operand = [&](int kb, int mt, SgParts& A) {
+      sg_u32x4 v[3];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) acc[mt] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-    const float* h = L.h1[cur] + abase;
+      for (int part = 0; part < 3; ++part) {
+        sg_u32x2 run[2];
 #pragma unroll
-    for (int t = 0; t < 25; ++t)
-#pragma unroll
-      for (int cq = 0; cq < 5; ++cq) {
-        const int off = 4 * cq * NPOS1 + (t / 5) * Q1 + t % 5;
-        float av[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) av[mt] = h[off + 2 * mt * Q1];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-          acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[mt], wb[5 * t + cq], acc[mt], 0, 0, 0);
-        if (cq == 4) __builtin_amdgcn_sched_barrier(0);   // bounds how far LDS reads run ahead
+        for (int j = 0; j < 2; ++j) {
+          const uint16_t* p;
+          if (kb < 13) {
+            const int t = 2 * kb + j < 25 ? 2 * kb + j : 24;
+            p = base1 + (t / KS * Q1 + t % KS) * NC1;
+          } else if (kb < 16) {
+            p = base2 + (2 * (kb - 13) + j) * NC1;
+          } else {
+            p = base3 + 4 * j * NC1;
+          }
+          run[j] = *reinterpret_cast<const sg_u32x2*>(p + part * C2_PART + 2 * mt * Q1 * NC1);
+        }
+        v[part] = sg_u32x4{run[0].x, run[0].y, run[1].x, run[1].y};
       }
-    // acc[mt][r] = Z[m = 16 mt + 4 g + r][o = 16 wv + j]
-    if (o_mine < NC2)
+      A.h = v[0];
+      A.m = v[1];
+      A.l = v[2];
+    };
+    SgParts A[2][4];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < 4; ++mt) operand(0, mt, A[0][mt]);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) L.z[cur][16 * mt + 4 * g + r][o_mine] = acc[mt][r] + bias;
-    if (b + gridDim.x < nB) stage(L.h1[cur ^ 1]);
-    __syncthreads();
-    for (int f = tid; f < FEAT; f += 256) {
-      const int o = f / NQ2, q = f % NQ2, y = 2 * (q / Q2), x = 2 * (q % Q2);
-      float best = L.z[cur][y * O2 + x][o];
-      int code = 0;
-      const float z1 = L.z[cur][y * O2 + x + 1][o], z2 = L.z[cur][(y + 1) * O2 + x][o],
-                  z3 = L.z[cur][(y + 1) * O2 + x + 1][o];
-      if (z1 > best) { best = z1; code = 1; }
-      if (z2 > best) { best = z2; code = 2; }
-      if (z3 > best) { best = z3; code = 3; }
-      a.F[b * FEAT + f] = best > 0.f ? best : 0.f;
-      a.code2[b * FEAT + f] = static_cast<uint8_t>(best > 0.f ? code : 4);
+    for (int kb = 0; kb < C2_SLICES; ++kb) {
+      // while a column tile is multiplied, the next one's fragments and a
+      // quarter of the next slice's A operand are read
+      sg_u32x4 w[2][3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) w[0][q] = L.B[buf][3 * nt0 + q][lane];
+      fetch_w(kb + 1 < C2_SLICES ? kb + 1 : 0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        if (nt + 1 < NT)
+#pragma unroll
+          for (int q = 0; q < 3; ++q) w[(nt + 1) & 1][q] = L.B[buf][3 * (nt + 1) + q][lane];
+        if (kb + 1 < C2_SLICES)
+#pragma unroll
+          for (int mt = nt; mt < (SHARED ? 4 : nt + 1); ++mt) operand(kb + 1, mt, A[(kb + 1) & 1][mt]);
+        __builtin_amdgcn_sched_barrier(0);
+        sg_products<false, 4>(A[kb & 1], w[nt & 1][0], w[nt & 1][1], w[nt & 1][2], acc[nt]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      stage_w(buf ^ 1);
+      sg_barrier();
+      buf ^= 1;
+    }
+    const bool have = b < nB;
+    sg_redo<4, NT>(acc, [&](int mt, int r, int nt) {
+      const int m = 16 * mt + 4 * g + r, o = 16 * (nt0 + nt) + c;
+      if (!have || o >= NC2) return 0.f;
+      const float* x = a.H1 + (int64_t)b * H1LEN + (m / O2) * Q1 + m % O2;
+      const float* w = a.w + a.off_c2 + o * K2;
+      float s = 0.f;
+      for (int ch = 0; ch < NC1; ++ch)
+        for (int t = 0; t < 25; ++t) s = fmaf(x[ch * NPOS1 + t / KS * Q1 + t % KS], w[ch * 25 + t], s);
+      return s;
+    });
+    // acc[nt][mt][r] = Z[y = 2 mt + g / 2][x = 4 (g % 2) + r]: lanes g and g ^ 2 hold
+    // the two rows of the windows; the lower pair finishes the left window, the
+    // upper pair the right one
+    const int s = g >> 1, px = 2 * (g & 1) + s;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const int o = 16 * (nt0 + nt) + c;
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        float z[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[r] = acc[nt][mt][r] + bias[nt];
+        const float r0 = __shfl_xor(s ? z[0] : z[2], 32), r1 = __shfl_xor(s ? z[1] : z[3], 32);
+        const float w0 = s ? r0 : z[0], w1 = s ? r1 : z[1], w2 = s ? z[2] : r0, w3 = s ? z[3] : r1;
+        float best = w0;
+        int code = 0;
+        if (w1 > best) { best = w1; code = 1; }
+        if (w2 > best) { best = w2; code = 2; }
+        if (w3 > best) { best = w3; code = 3; }
+        if (have && o < NC2) {
+          const int64_t f = (int64_t)b * FEAT + o * NQ2 + mt * Q2 + px;
+          a.F[f] = best > 0.f ? best : 0.f;
+          a.code2[f] = static_cast<uint8_t>(best > 0.f ? code : 4);
+        }
+      }
     }
   }
 }
@@ -694,8 +814,14 @@ int cnn_chunks(int B) { return (B + kCnnChunk - 1) / kCnnChunk; }
 hipError_t launch_cnn_grads(const MlpPlan& mplan, const CnnArgs& a, hipStream_t s) {
   const int64_t nB = (int64_t)a.n * a.B;
   hipLaunchKernelGGL(k_cnn_conv1_pool, dim3(static_cast<unsigned>((nB * NPOS1 + 255) / 256)), dim3(256), 0, s, a);
-  const int64_t cv_blocks = nB < kConvBlocks ? nB : kConvBlocks;
-  hipLaunchKernelGGL(k_cnn_conv2_pool, dim3(static_cast<unsigned>(cv_blocks)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_cnn_pack_w2, dim3((C2_SLICES * C2_TILES + 3) / 4), dim3(256), 0, s, a);
+  // up to two images a CU the four waves of a block share one (a wave takes
+  // about 20 us over an image of its own)
+  if (nB <= 2 * kConvBlocks)
+    hipLaunchKernelGGL(k_cnn_conv2_pool<true>, dim3(static_cast<unsigned>(std::min<int64_t>(nB, kConvBlocks))), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_cnn_conv2_pool<false>, dim3(static_cast<unsigned>(std::min<int64_t>((nB + 3) / 4, kConvBlocks))),
+                       dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the fully connected part: the MLP 800-H-C on the features, its G block

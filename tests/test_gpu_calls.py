@@ -150,6 +150,36 @@ def test_worker_grads_softmax_shared_dataset_rows(n, B, d, C, S):
     assert e.value.status == pb.DBW_ERANGE
 
 
+# conv2 with one image a block (up to 512 images) and one a wave, with blocks
+# that hold fewer than four images; losses are continuous in every pooling and
+# ReLU decision, so they need no care for ties.
+@pytest.mark.parametrize("n,B", [(1, 1), (3, 17), (2, 256), (3, 171), (5, 203)])
+def test_worker_loss_cnn_image_counts(n, B):
+    g = torch.Generator(device="cuda").manual_seed(n * B)
+    X = torch.rand((n, B, 784), generator=g, device="cuda")
+    y = torch.randint(0, 10, (n, B), generator=g, device="cuda", dtype=torch.int32)
+    ctx = _ctx(n, B, 784, 10, model="cnn", H=40)
+    w = 0.1 * torch.randn(ctx.P, generator=g, device="cuda")
+    def run(X):
+        _, loss = ctx.worker_grads(w, X, y)
+        ctx.sync()
+        return loss
+    F = torch.nn.functional
+    v = w.double().cpu()
+    W1, b1, W2, b2, K1, c1, K2, c2 = v.split([800 * 40, 40, 400, 10, 500, 20, 25000, 50])
+    h = F.relu(F.max_pool2d(F.conv2d(X.double().cpu().reshape(-1, 1, 28, 28), K1.reshape(20, 1, 5, 5), c1), 2))
+    h = F.relu(F.max_pool2d(F.conv2d(h, K2.reshape(50, 20, 5, 5), c2), 2)).reshape(n * B, 800)
+    z = F.relu(h @ W1.reshape(800, 40) + b1) @ W2.reshape(40, 10) + b2
+    want = F.cross_entropy(z, y.reshape(-1).long().cpu(), reduction="none").reshape(n, B).mean(1)
+    # rounding through sums of 25, 500, 800 and 40 terms
+    tol = 2.0 ** -23 * (8 + 25 ** 0.5 + 500 ** 0.5 + 800 ** 0.5 + 40 ** 0.5)
+    assert rel_err(host(run(X)), want.numpy()) <= tol
+    # an infinite pixel stays in its own worker
+    X[-1, B // 2, 300] = float("inf")
+    loss = host(run(X))
+    assert not np.isfinite(loss[-1]) and rel_err(loss[:-1], want.numpy()[:-1]) <= tol if n > 1 else True
+
+
 # The MLP's products at the same kinds of edges: features and hidden units off
 # the tiles and load widths, rows off 4, 16 and 32 and beyond the 1024 staged
 # offsets, and sizes on both sides of each launch rule.  (n, B, d, H, C, S)
