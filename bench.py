@@ -11,7 +11,7 @@ interface defines them.  Prints one JSON line.
 
 Default workload: softmax regression with 256 workers x 512 rows, 3072
 features (32x32x3-shaped) and 100 classes, the largest of the five workloads
-(fp32 matrix-core bound).  The same line carries, under "hbm_roofline", the
+(matrix-core bound).  The same line carries, under "hbm_roofline", the
 bandwidth-bound workload (64 workers x 256 rows, 3072 features, 10 classes)
 that the metric's %-of-peak-HBM figure refers to, and under "ps_kernels" the
 aggregation and statistics calls at fixed k = n and ceil(n/2).
@@ -38,7 +38,9 @@ if ROOT not in sys.path:
 
 METRIC = "worker-gradient samples/sec per DBW iteration (1 MI355X); % peak HBM GB/s"
 HBM_PEAK_GBS = 8000.0
-MFMA_F32_PEAK_TFLOPS = 157.3   # dense fp32 matrix-core peak of the MI355X
+# fp32 products on the bf16 matrix cores (dense 2.5 PFLOP/s), six products of
+# bf16 parts each; the fp32 matrix instruction's own peak is 157.3
+MFMA_F32_PEAK_TFLOPS = 2500.0 / 6
 FUSED_MAX_CLASSES = 16         # the single-pass softmax kernel covers C <= 16
 FLUSH_BYTES = 1 << 30          # touched between launches for the cold figures (MALL is 256 MB)
 SETTLE_S = 0.1                 # untimed gradient launches before the timed ones (clock settling)
@@ -103,7 +105,7 @@ def grads_flops(cfg) -> float:
 
 def roofline_bound(cfg) -> str:
     """The single-pass softmax kernel streams each row once and is bounded by
-    HBM; the two-GEMM large-class path and the MLP are fp32 matrix-core work."""
+    HBM; the two-product GEMM path and the MLP are matrix-core work."""
     if cfg.model == "softmax" and cfg.C <= FUSED_MAX_CLASSES:
         return "hbm"
     return "mfma"
@@ -114,11 +116,9 @@ def grads_kernels(cfg) -> str:
     if cfg.model == "softmax":
         if cfg.C <= FUSED_MAX_CLASSES:
             return "k_softmax_mfma + k_slab_reduce_tiles"
-        if cfg.C <= 112 and cfg.C % 4 == 0 and cfg.d % 4 == 0:
-            return "k_logits_softmax_mfma + k_grads_mfma_n"
-        return "k_logits_mfma + k_rows_softmax + k_grads_mfma"
+        return "k_sg_pack + k_sg_logits + k_rows_pack + k_sg_grads"
     if cfg.model == "mlp":
-        return "k_mlp_hidden_mfma + k_mlp_head + k_mlp_dw1_mfma (with the head's slab sums)"
+        return "k_sg_pack + k_mlp_hidden + k_mlp_head + k_mlp_dw1 (with the head's slab sums)"
     return "k_cnn_* + MLP kernels on the 800 features"
 
 
@@ -320,6 +320,16 @@ def time_grads_cold(wl, first: int, steps: int, G, Lb):
     return cold
 
 
+def grads_flops_executed(cfg) -> float:
+    """grads_flops less the logits of samples that repeat a dataset row: with
+    1.5 samples a row or more the softmax GEMM path forms every row's logits
+    once."""
+    f = grads_flops(cfg)
+    if cfg.model == "softmax" and cfg.C > FUSED_MAX_CLASSES and cfg.S >= 8192 and 2 * cfg.n * cfg.B >= 3 * cfg.S:
+        f -= 2.0 * (cfg.n * cfg.B - cfg.S) * cfg.d * cfg.C
+    return f
+
+
 def roofline_block(cfg, P: int, warm_ms: float, cold_ms: float, launches: int) -> dict:
     gb = grads_bytes(cfg, P, True)
     bound = roofline_bound(cfg)
@@ -333,6 +343,7 @@ def roofline_block(cfg, P: int, warm_ms: float, cold_ms: float, launches: int) -
         "kernel": f"worker-gradient launch dbw_worker_grads ({grads_kernels(cfg)}); every G row written",
         "bound": bound, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
         "traffic": measured_traffic(cfg), "bytes_per_launch": gb, "flops_per_launch": grads_flops(cfg),
+        "flops_executed": grads_flops_executed(cfg),
         "avg_launch_ms": warm_ms, "launches": launches,
         "cold": {"avg_launch_ms": cold_ms, "achieved": achieved_cold, "frac": achieved_cold / peak,
                  "flush": "1 GiB device buffer read before each launch (untimed)"},

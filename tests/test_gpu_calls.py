@@ -174,10 +174,12 @@ def test_worker_loss_cnn_image_counts(n, B):
     # rounding through sums of 25, 500, 800 and 40 terms
     tol = 2.0 ** -23 * (8 + 25 ** 0.5 + 500 ** 0.5 + 800 ** 0.5 + 40 ** 0.5)
     assert rel_err(host(run(X)), want.numpy()) <= tol
-    # an infinite pixel stays in its own worker
+    # an infinite pixel stays in its own worker (whose loss may be anything: a
+    # pooled NaN passes the ReLU as 0)
     X[-1, B // 2, 300] = float("inf")
     loss = host(run(X))
-    assert not np.isfinite(loss[-1]) and rel_err(loss[:-1], want.numpy()[:-1]) <= tol if n > 1 else True
+    if n > 1:
+        assert rel_err(loss[:-1], want.numpy()[:-1]) <= tol
 
 
 # The MLP's products at the same kinds of edges: features and hidden units off
