@@ -100,6 +100,7 @@ struct dbw_ctx {
   uint8_t* cCode1 = nullptr;
   float* cF = nullptr;
   uint8_t* cCode2 = nullptr;
+  uint64_t* cClose2 = nullptr;
   int32_t* cYlab = nullptr;
   float* cdP2 = nullptr;
   float* cdP1 = nullptr;
@@ -477,7 +478,7 @@ dbw_status launch_grads(dbw_ctx* c, const float* w, const float* X, const int32_
     a.n = cf.n; a.B = cf.B; a.H = cf.H; a.C = cf.C;
     a.P = c->P; a.off_c1 = c->P - dbw::CNN_CONV_PARAMS; a.off_c2 = a.off_c1 + dbw::CNN_C1 * 25 + dbw::CNN_C1;
     a.G = G; a.loss = loss;
-    a.W2p = c->cW2p; a.H1 = c->cH1; a.code1 = c->cCode1; a.F = c->cF; a.code2 = c->cCode2; a.ylab = c->cYlab;
+    a.W2p = c->cW2p; a.H1 = c->cH1; a.code1 = c->cCode1; a.F = c->cF; a.code2 = c->cCode2; a.close2 = c->cClose2; a.ylab = c->cYlab;
     a.dP2 = c->cdP2; a.dP1 = c->cdP1; a.part1 = c->cPart1; a.part2 = c->cPart2; a.chunk = dbw::kCnnChunk;
     a.Hh = c->Hh; a.Wp = c->Wp; a.Dp = c->Rp; a.dA = c->dA; a.Gp = c->Gp; a.lossp = c->lossp; a.err = c->err; a.row_mask = row_mask;
     e = dbw::launch_cnn_grads(c->mplan, a, c->stream);
@@ -592,7 +593,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
        sSqp = take(sizeof(float) * n * part_blocks), sPart = take(sizeof(double) * 2 * part_blocks);
   Span sGa;
   if (c->copy_rows) sGa = take(sizeof(float) * n * P);
-  Span sGp, sLp, sWp, sRp, sZ, sCe, sCr, sH, sdA, sW2, sH1, sC1, sF, sC2, sYl, sdP2, sdP1, sPa1, sPa2;
+  Span sGp, sLp, sWp, sRp, sZ, sCe, sCr, sH, sdA, sW2, sH1, sC1, sF, sC2, sCl, sYl, sdP2, sdP1, sPa1, sPa2;
   if (cf.model == DBW_SOFTMAX) {
     if (c->splan.fused) {
       if (c->splan.slabs > 1) {
@@ -623,6 +624,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
       sC1 = take(h1);
       sF = take(sizeof(float) * rowsN * dbw::CNN_FEAT);
       sC2 = take(rowsN * dbw::CNN_FEAT);
+      sCl = take(sizeof(uint64_t) * rowsN);
       sYl = take(sizeof(int32_t) * rowsN);
       sdP2 = take(sizeof(float) * rowsN * dbw::CNN_FEAT);
       sdP1 = take(sizeof(float) * h1);
@@ -645,7 +647,7 @@ DBW_API dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out
   c->Wp = (dbw::sg_u32x4*)at(sWp); c->Rp = (dbw::sg_u32x4*)at(sRp);
   c->Z = (float*)at(sZ); c->ce = (float*)at(sCe); c->ce_row = (float*)at(sCr); c->Hh = (float*)at(sH); c->dA = (float*)at(sdA);
   c->cW2p = (dbw::sg_u32x4*)at(sW2);
-  c->cH1 = (float*)at(sH1); c->cCode1 = (uint8_t*)at(sC1); c->cF = (float*)at(sF); c->cCode2 = (uint8_t*)at(sC2);
+  c->cH1 = (float*)at(sH1); c->cCode1 = (uint8_t*)at(sC1); c->cF = (float*)at(sF); c->cCode2 = (uint8_t*)at(sC2); c->cClose2 = (uint64_t*)at(sCl);
   c->cYlab = (int32_t*)at(sYl); c->cdP2 = (float*)at(sdP2); c->cdP1 = (float*)at(sdP1);
   c->cPart1 = (float*)at(sPa1); c->cPart2 = (float*)at(sPa2);
 

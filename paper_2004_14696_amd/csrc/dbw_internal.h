@@ -115,7 +115,7 @@ hipError_t launch_mlp_grads(const MlpPlan& plan, const MlpArgs& a, hipStream_t s
 // 800-H-C.  Parameters [MLP (800-H-C) | Wc1 (20x1x5x5) | bc1 | Wc2 (50x20x5x5) | bc2].
 constexpr int CNN_IMG = 28, CNN_C1 = 20, CNN_C2 = 50, CNN_FEAT = 800;
 constexpr int64_t CNN_CONV_PARAMS = CNN_C1 * 25 + CNN_C1 + CNN_C2 * CNN_C1 * 25 + CNN_C2;
-constexpr int64_t kCnnW2Bytes = 17 * 4 * 3 * 1024;   // Wc2 as product fragments
+constexpr int64_t kCnnW2Bytes = 17 * 4 * 3 * 1024 + 64 * 4;   // Wc2 as product fragments, the norms of its filters
 constexpr int kCnnChunk = 16;   // images per weight-gradient partial
 struct CnnArgs {
   const float* w;        // [P]
@@ -128,10 +128,11 @@ struct CnnArgs {
   float* G;              // [n][P]
   float* loss;           // [n]
   // workspace
-  sg_u32x4* W2p;         // Wc2 as product fragments
+  sg_u32x4* W2p;         // Wc2 as product fragments, then the norms of its filters
   float* H1;             // [n*B][20][12][12] pooled, ReLU'd conv1 output
   uint8_t* code1;        // [n*B][20][12][12] window code of each pooled value (4: ReLU off)
   float* F;              // [n*B][800] pooled, ReLU'd conv2 output (the features)
+  uint64_t* close2;      // [n*B] windows of conv2 decided within rounding (a bit a lane group and tile)
   uint8_t* code2;        // [n*B][800] window codes of the features (4: ReLU off)
   int32_t* ylab;         // [n*B] gathered labels
   float* dP2;            // [n*B][800] gradient at the features (before their ReLU)

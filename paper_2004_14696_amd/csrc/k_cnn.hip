@@ -18,6 +18,8 @@
 //                     filters x patches) on the split products of
 //                     split_gemm.h, one image a wave, W2's fragments shared
 //                     through LDS; pooling and ReLU in the epilogue.
+//  k_cnn_conv2_close  the pooling and ReLU decisions of conv2 that lie within
+//                     rounding, taken again on fp32 matrix-core sums.
 //  k_cnn_dfeat        dF = dA Wf1^T on the matrix cores (the ReLU mask of F is
 //                     in the window codes).
 //  k_cnn_conv2_dgrad  gradient at H1: per image and input channel the GEMM
@@ -140,7 +142,8 @@ __global__ __launch_bounds__(256) void k_cnn_conv1_pool(CnnArgs a) {
 // values are on their way in registers meanwhile.  Bias, 2 x 2 pooling and ReLU
 // run in registers: a window's two rows are in lanes 32 apart.  With few images
 // (SHARED) the block's waves take the same one, a column tile each.  8000
-// images: 167 us (fp32 matrix cores 294), 0.95 PFLOP/s of issued bf16 products;
+// images: 173 - 181 us, of which 8 - 14 are the test for decisions within rounding
+// (fp32 matrix cores 294), 1.2 PFLOP/s of issued bf16 products;
 // one wave a SIMD, so the LDS reads are placed by hand between the products of
 // the column tile before (202 us left to the compiler).
 constexpr int C2_SLICES = 17, C2_TILES = 4;
@@ -149,7 +152,8 @@ constexpr int C2_PART = C2_POS * NC1;              // bf16 values of one part
 constexpr int C2_TASKS = (NPOS1 * 5 + 63) / 64;    // (position, four channels) pieces of a lane
 constexpr int kConvBlocks = 256;                   // one block of four waves per CU
 static_assert(NC1 == 20 && KS == 5, "slice layout");
-static_assert(kCnnW2Bytes == C2_SLICES * C2_TILES * 3 * 1024, "fragments of Wc2");
+constexpr int C2_FRAGS = C2_SLICES * C2_TILES * 3 * 64;   // pieces of Wc2's fragments; its filters' norms follow
+static_assert(kCnnW2Bytes == C2_FRAGS * 16 + C2_TILES * 16 * 4, "fragments of Wc2 and the norms of its filters");
 
 // Tap and first channel of run j (of two) of lane group g in a slice; tap -1:
 // no such tap.
@@ -168,7 +172,22 @@ __device__ __forceinline__ void c2_run(int kb, int g, int j, int& tap, int& ch) 
 __global__ __launch_bounds__(256) void k_cnn_pack_w2(CnnArgs a) {
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int t = static_cast<int>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (t >= C2_SLICES * C2_TILES) return;
+  if (t >= C2_SLICES * C2_TILES) {
+    // then a wave a filter: its norm
+    const int o = t - C2_SLICES * C2_TILES;
+    if (o >= C2_TILES * 16) return;
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < (K2 + 63) / 64; ++q) {
+      const int k = lane + 64 * q;
+      const float v = o < NC2 && k < K2 ? a.w[a.off_c2 + o * K2 + k] : 0.f;
+      s = fmaf(v, v, s);
+    }
+#pragma unroll
+    for (int q = 32; q > 0; q >>= 1) s += __shfl_xor(s, q);
+    if (lane == 0) reinterpret_cast<float*>(a.W2p + C2_FRAGS)[o] = sqrtf(s);
+    return;
+  }
   const int kb = t / C2_TILES, o = 16 * (t % C2_TILES) + c;
   float v[8];
 #pragma unroll
@@ -180,6 +199,131 @@ __global__ __launch_bounds__(256) void k_cnn_pack_w2(CnnArgs a) {
       v[4 * j + q] = o < NC2 && tap >= 0 ? a.w[a.off_c2 + o * K2 + (ch + q) * 25 + tap] : 0.f;
   }
   sg_store8(a.W2p, C2_TILES, kb * SG_K + 8 * g, o, v);
+}
+
+// Pooling of one 16 x 16 tile of Z (positions 16 mt .. x filters) in registers:
+// z[r] = Z[y = 2 mt + g / 2][x = 4 (g % 2) + r]; lanes g and g ^ 2 hold the two rows of
+// the windows, the lower pair finishes the left window, the upper pair the
+// right one (window column px of c2_window).  w: the window's entries in
+// row-major order, code: its first largest one.
+struct C2Window {
+  float w[4], best;
+  int code;
+};
+__device__ __forceinline__ int c2_px(int g) { return 2 * (g & 1) + (g >> 1); }
+__device__ __forceinline__ C2Window c2_window(const sg_f32x4& acc, float bias, int g) {
+  C2Window p;
+  const int s = g >> 1;
+  float z[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) z[r] = acc[r] + bias;
+  const float r0 = __shfl_xor(s ? z[0] : z[2], 32), r1 = __shfl_xor(s ? z[1] : z[3], 32);
+  p.w[0] = s ? r0 : z[0];
+  p.w[1] = s ? r1 : z[1];
+  p.w[2] = s ? z[2] : r0;
+  p.w[3] = s ? z[3] : r1;
+  p.best = p.w[0];
+  p.code = 0;
+#pragma unroll
+  for (int q = 1; q < 4; ++q)
+    if (p.w[q] > p.best) {
+      p.best = p.w[q];
+      p.code = q;
+    }
+  return p;
+}
+__device__ __forceinline__ void c2_store(const CnnArgs& a, int b, int o, int mt, int px, const C2Window& p) {
+  const int64_t f = (int64_t)b * FEAT + o * NQ2 + mt * Q2 + px;
+  a.F[f] = p.best > 0.f ? p.best : 0.f;
+  a.code2[f] = static_cast<uint8_t>(p.best > 0.f ? p.code : 4);
+}
+
+// Pooling and ReLU decisions that rounding could take either way.  A decision
+// moves a whole window's gradient, so those that are closer than the
+// roundings of Z are taken on the sums of the fp32 matrix instruction (K in
+// steps of (tap, channel quad), tap by tap): the same decisions as if all of
+// Z were formed with it.  Closer than tau = 2^-21 |H1 of the image| |filter| +
+// 2^-18 |largest entry less its bias| + 2^-22 |bias|.  The two forms of a sum
+// differ by up to 1.2 2^-24 |H1| |filter| over uniform, normal, sparse and nearly
+// constant images with filters of either sign (two such differences make 0.3
+// of the first term), by 9 where all is positive (then the second term is
+// three times the first).  k_cnn_conv2_pool notes the windows (close2: bit 16 nt
+// + 4 mt + g of the image's word, g the lane group of the window in tile (mt,
+// nt)); k_cnn_conv2_close forms their tiles again: 16 - 18 us for 8000 images of
+// 28 x 28 with 80% zeros, 22 for blank ones, 520 for constant ones with 0.1%
+// noise, where every window is close.  (Done at once by the waves that find
+// them, the first took 53 us: the wave that found most ended last.)
+//
+// Windows whose four patches are the same (blank parts of an image) tie in
+// both forms and are left out; they are looked for in images where all column
+// tiles note the same window.  A block takes four images: wave w compares the
+// neighbours of image w, then forms row tile w of all four.
+__global__ __launch_bounds__(256) void k_cnn_conv2_close(CnnArgs a) {
+  __shared__ uint8_t same[4][NPOS1];   // H1 at a position equals its right (1), its lower neighbour (2), in all channels
+  __shared__ uint64_t words[4];
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int b0 = static_cast<int>(blockIdx.x) * 4;
+  {
+    uint64_t word = b0 + wv < a.n * a.B ? a.close2[b0 + wv] : 0;
+    uint64_t all = word & word >> 16 & word >> 32 & word >> 48 & 0xffffu;   // bit 4 mt + g
+    if (all != 0) {
+      const float* img = a.H1 + (int64_t)(b0 + wv) * H1LEN;
+      for (int p = lane; p < NPOS1; p += 64) {
+        const int right = p % Q1 + 1 < Q1 ? p + 1 : p, down = p + Q1 < NPOS1 ? p + Q1 : p;
+        bool er = true, ed = true;
+#pragma unroll
+        for (int ch = 0; ch < NC1; ++ch) {
+          const float v = img[ch * NPOS1 + p];
+          er &= v == img[ch * NPOS1 + right];
+          ed &= v == img[ch * NPOS1 + down];
+        }
+        same[wv][p] = static_cast<uint8_t>((er ? 1 : 0) | (ed ? 2 : 0));
+      }
+      asm volatile("" ::: "memory");   // the wave's LDS writes precede its reads
+      // lane (g, mt): the window's patches are the same if all of their
+      // neighbours in it are
+      const int mt = c & 3, x = 2 * c2_px(g), y = 2 * mt;
+      uint32_t r = 1, d = 2;
+#pragma unroll
+      for (int u = 0; u <= KS; ++u)
+#pragma unroll
+        for (int v = 0; v < KS; ++v) {
+          const uint32_t e = same[wv][(y + u) * Q1 + x + v];
+          r &= e;
+          if (u < KS) d &= e;
+        }
+      const uint64_t blank = __builtin_amdgcn_ballot_w64(r != 0 && d != 0);   // bit 16 g + mt
+      uint64_t drop = 0;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) drop |= (blank >> (16 * (q & 3) + (q >> 2)) & 1) << q;
+      drop &= all;
+      word &= ~(drop | drop << 16 | drop << 32 | drop << 48);
+    }
+    if (lane == 0) words[wv] = word;
+  }
+  __syncthreads();
+  const int mt = wv;
+#pragma unroll 1
+  for (int q = 0; q < 4; ++q) {
+    const uint64_t word = words[q] >> 4 * mt;
+    const float* img = a.H1 + (int64_t)(b0 + q) * H1LEN;
+#pragma unroll 1
+    for (int nt = 0; nt < 4; ++nt) {
+      if ((word >> 16 * nt & 15u) == 0) continue;
+      const int o = 16 * nt + c;
+      const float* h = img + g * NPOS1 + (2 * mt + (c >> 3)) * Q1 + (c & 7);
+      const float* w = a.w + a.off_c2 + (o < NC2 ? o : 0) * K2 + g * 25;
+      sg_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 25; ++t)
+#pragma unroll
+        for (int cq = 0; cq < NC1 / 4; ++cq)
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(h[4 * cq * NPOS1 + t / KS * Q1 + t % KS], w[4 * cq * 25 + t], acc, 0, 0, 0);
+      const C2Window p = c2_window(acc, a.w[a.off_c2 + NC2 * K2 + (o < NC2 ? o : 0)], g);
+      if (o < NC2) c2_store(a, b0 + q, o, mt, c2_px(g), p);
+    }
+  }
 }
 
 template <bool SHARED>
@@ -195,6 +339,9 @@ __global__ __launch_bounds__(256, 1) void k_cnn_conv2_pool(CnnArgs a) {
   float bias[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) bias[nt] = 16 * (nt0 + nt) + c < NC2 ? b2[16 * (nt0 + nt) + c] : 0.f;
+  float wnorm[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) wnorm[nt] = reinterpret_cast<const float*>(a.W2p + C2_FRAGS)[16 * (nt0 + nt) + c];
   for (int e = lane; e < 3 * C2_PART; e += 64) (&img[wv][0][0])[e] = 0;
   const int nB = a.n * a.B;
   float4 h[C2_TASKS];
@@ -207,7 +354,9 @@ __global__ __launch_bounds__(256, 1) void k_cnn_conv2_pool(CnnArgs a) {
       h[s] = make_float4(src[0], src[NPOS1], src[2 * NPOS1], src[3 * NPOS1]);
     }
   };
+  // into LDS as parts; returns the sum of the image's squares
   auto put = [&]() {
+    float sq = 0.f;
 #pragma unroll
     for (int s = 0; s < C2_TASKS; ++s) {
       const int e = lane + 64 * s, cq = e / NPOS1, pos = e - cq * NPOS1;
@@ -217,7 +366,11 @@ __global__ __launch_bounds__(256, 1) void k_cnn_conv2_pool(CnnArgs a) {
       *reinterpret_cast<sg_u32x2*>(p) = sg_u32x2{u.h, v.h};
       *reinterpret_cast<sg_u32x2*>(p + C2_PART) = sg_u32x2{u.m, v.m};
       *reinterpret_cast<sg_u32x2*>(p + 2 * C2_PART) = sg_u32x2{u.l, v.l};
+      sq = fmaf(h[s].x, h[s].x, fmaf(h[s].y, h[s].y, fmaf(h[s].z, h[s].z, fmaf(h[s].w, h[s].w, sq))));
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+    return sq;
   };
   sg_u32x4 rb[3];
   auto fetch_w = [&](int kb) {
@@ -242,7 +395,7 @@ __global__ __launch_bounds__(256, 1) void k_cnn_conv2_pool(CnnArgs a) {
   __syncthreads();
   int buf = 0;
   for (int b0 = static_cast<int>(blockIdx.x) * IMAGES; b0 < nB; b0 += stride, b += stride) {
-    put();
+    const float hnorm = sqrtf(put());
     asm volatile("" ::: "memory");   // the wave's LDS writes precede its reads
     fetch(b + stride);
     sg_f32x4 acc[NT][4];
@@ -310,31 +463,28 @@ __global__ __launch_bounds__(256, 1) void k_cnn_conv2_pool(CnnArgs a) {
         for (int t = 0; t < 25; ++t) s = fmaf(x[ch * NPOS1 + t / KS * Q1 + t % KS], w[ch * 25 + t], s);
       return s;
     });
-    // acc[nt][mt][r] = Z[y = 2 mt + g / 2][x = 4 (g % 2) + r]: lanes g and g ^ 2 hold
-    // the two rows of the windows; the lower pair finishes the left window, the
-    // upper pair the right one
-    const int s = g >> 1, px = 2 * (g & 1) + s;
+    uint64_t close = 0;   // windows decided within rounding (k_cnn_conv2_close)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int o = 16 * (nt0 + nt) + c;
+      const float tau0 = 0x1p-21f * hnorm * wnorm[nt] + 0x1p-22f * fabsf(bias[nt]);
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
-        float z[4];
+        const C2Window p = c2_window(acc[nt][mt], bias[nt], g);
+        if (have && o < NC2) c2_store(a, b, o, mt, c2_px(g), p);
+        const float tau = fmaf(0x1p-18f, fabsf(p.best - bias[nt]), tau0);
+        int within = fabsf(p.best) < tau ? 2 : 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) z[r] = acc[nt][mt][r] + bias[nt];
-        const float r0 = __shfl_xor(s ? z[0] : z[2], 32), r1 = __shfl_xor(s ? z[1] : z[3], 32);
-        const float w0 = s ? r0 : z[0], w1 = s ? r1 : z[1], w2 = s ? z[2] : r0, w3 = s ? z[3] : r1;
-        float best = w0;
-        int code = 0;
-        if (w1 > best) { best = w1; code = 1; }
-        if (w2 > best) { best = w2; code = 2; }
-        if (w3 > best) { best = w3; code = 3; }
-        if (have && o < NC2) {
-          const int64_t f = (int64_t)b * FEAT + o * NQ2 + mt * Q2 + px;
-          a.F[f] = best > 0.f ? best : 0.f;
-          a.code2[f] = static_cast<uint8_t>(best > 0.f ? code : 4);
-        }
+        for (int q = 0; q < 4; ++q) within += p.best - p.w[q] < tau;   // (the largest itself is one)
+        const uint64_t m = __builtin_amdgcn_ballot_w64(within >= 2 && o < NC2);
+        if (m != 0)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) close |= (m >> 16 * q & 0xffffu) != 0 ? uint64_t{1} << (16 * nt + 4 * mt + q) : 0u;
       }
+    }
+    if (have && lane == 0) {
+      if (SHARED) reinterpret_cast<uint16_t*>(a.close2 + b)[wv] = static_cast<uint16_t>(close);
+      else a.close2[b] = close;
     }
   }
 }
@@ -814,7 +964,7 @@ int cnn_chunks(int B) { return (B + kCnnChunk - 1) / kCnnChunk; }
 hipError_t launch_cnn_grads(const MlpPlan& mplan, const CnnArgs& a, hipStream_t s) {
   const int64_t nB = (int64_t)a.n * a.B;
   hipLaunchKernelGGL(k_cnn_conv1_pool, dim3(static_cast<unsigned>((nB * NPOS1 + 255) / 256)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_cnn_pack_w2, dim3((C2_SLICES * C2_TILES + 3) / 4), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_cnn_pack_w2, dim3((C2_SLICES + 16) * C2_TILES / 4), dim3(256), 0, s, a);
   // up to two images a CU the four waves of a block share one (a wave takes
   // about 20 us over an image of its own)
   if (nB <= 2 * kConvBlocks)
@@ -822,6 +972,7 @@ hipError_t launch_cnn_grads(const MlpPlan& mplan, const CnnArgs& a, hipStream_t 
   else
     hipLaunchKernelGGL(k_cnn_conv2_pool<false>, dim3(static_cast<unsigned>(std::min<int64_t>((nB + 3) / 4, kConvBlocks))),
                        dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_cnn_conv2_close, dim3(static_cast<unsigned>((nB + 3) / 4)), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the fully connected part: the MLP 800-H-C on the features, its G block

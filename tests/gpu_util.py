@@ -213,3 +213,34 @@ def cnn_best_flip(a, o, deltas, H, C, limit=12):
 def cnn_best_flip_err(a, o, deltas, H, C, limit=12) -> float:
     """The error of cnn_best_flip."""
     return cnn_best_flip(a, o, deltas, H, C, limit)[0]
+
+
+def fp32_chain(start, A, W, order):
+    """start + sum_k A[..., k] W[k, :] as a chain of fp32 fused multiply-adds in
+    the given order of k (products of two fp32 values are exact in fp64)."""
+    s = np.asarray(start, dtype=np.float32)
+    for k in order:
+        s = (A[..., k, None].astype(np.float64) * W[k].astype(np.float64) + s.astype(np.float64)).astype(np.float32)
+    return s
+
+
+def _patches(H, side):
+    """5 x 5 patches [B][side][side][channels * 25], (channel, tap) order."""
+    u = np.lib.stride_tricks.sliding_window_view(H, (5, 5), (2, 3))   # B, ch, side, side, 5, 5
+    return u.transpose(0, 2, 3, 1, 4, 5).reshape(H.shape[0], side, side, -1)
+
+
+# the fp32 matrix instruction's order of K in the second convolution: tap by tap,
+# channels in increasing order
+CONV2_FP32_ORDER = [25 * ch + t for t in range(25) for ch in range(20)]
+
+
+def cnn_conv_fp32(Wc1, bc1, X):
+    """The first convolution block of fp32 images X [B][784] in the kernel's
+    fp32 arithmetic: H1 [B][20][12][12], window codes, ReLU decisions."""
+    from oracle import model as omodel
+
+    A = _patches(np.asarray(X, np.float32).reshape(-1, 1, 28, 28), 24)
+    Z = fp32_chain(np.broadcast_to(bc1, A.shape[:3] + (20,)), A, Wc1.reshape(20, 25).T, range(25))
+    P, code = omodel.maxpool2(Z.transpose(0, 3, 1, 2))
+    return np.where(P > 0, P, np.float32(0)).astype(np.float32), code, P > 0
