@@ -162,6 +162,15 @@ typedef struct dbw_ctx dbw_ctx;
 /* P for a configuration; -1 if the configuration is invalid. */
 int64_t dbw_param_count(const dbw_config* cfg);
 
+/* The kernels that dbw_worker_grads and dbw_step run for the softmax gradients
+ * of cfg (diagnostics; HOST only, needs no device).  single_pass: 1 if one
+ * kernel reads X once (up to 16 classes), 0 if logits and gradient are two
+ * products; slabs: row slabs of a worker whose partial gradients are summed
+ * (single pass; else 1); per_row: 1 if minibatches given by `rows` share the
+ * logits of the dataset's rows.  (0, 1, 0) for the MLP and the CNN.
+ * DBW_EINVAL for an invalid cfg or a NULL pointer. */
+dbw_status dbw_grads_route(const dbw_config* cfg, int32_t* single_pass, int32_t* slabs, int32_t* per_row);
+
 /* Create a context bound to HIP stream `stream` (a hipStream_t, NULL for the
  * default stream) on the current device.  Validates cfg (n in [1, DBW_MAX_N],
  * B, d, C >= 1, C <= 4096, H >= 1 for the MLP and the CNN, d = 784 for the

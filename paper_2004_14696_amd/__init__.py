@@ -6,10 +6,10 @@ statistics, the DBW choice of k and the SGD update, all in hand-written HIP
 kernels for gfx950 behind the C ABI of ``include/dbw.h``.  This package is
 the Python binding of that library.
 """
-from .binding import (DBW_MLP, DBW_SOFTMAX, Config, Context, DBWError, load_library,  # noqa: F401
+from .binding import (DBW_MLP, DBW_SOFTMAX, Config, Context, DBWError, grads_route, load_library,  # noqa: F401
                       make_config, param_count, time_estimate)
 
-__all__ = ["Config", "Context", "DBWError", "load_library", "make_config", "param_count",
+__all__ = ["Config", "Context", "DBWError", "grads_route", "load_library", "make_config", "param_count",
            "time_estimate", "DBW_SOFTMAX", "DBW_MLP", "config_from"]
 
 

@@ -37,7 +37,7 @@ EXPORTED = (
     "dbw_samples_export", "dbw_samples_import", "dbw_profile_enable", "dbw_kernel_time",
     "dbw_profile_reset", "dbw_time_estimator_create", "dbw_time_estimator_destroy",
     "dbw_time_estimator_solve", "dbw_time_estimator_stats", "dbw_busy_export", "dbw_busy_import",
-    "dbw_grad_stats_static",
+    "dbw_grad_stats_static", "dbw_grads_route",
 )
 DBW_STATIC_SCRATCH_BYTES = 8 * 1024 * 1024
 
@@ -94,6 +94,8 @@ def load_library(path: str = LIB_PATH):
     P = c_void_p
     lib.dbw_param_count.argtypes = [POINTER(Config)]
     lib.dbw_param_count.restype = c_int64
+    lib.dbw_grads_route.argtypes = [POINTER(Config), POINTER(c_int32), POINTER(c_int32), POINTER(c_int32)]
+    lib.dbw_grads_route.restype = st
     lib.dbw_create.argtypes = [POINTER(Config), P, POINTER(P)]
     lib.dbw_create.restype = st
     lib.dbw_destroy.argtypes = [P]
@@ -174,6 +176,16 @@ def make_config(model: str | int, n: int, B: int, d: int, C: int, H: int = 0, et
 
 def param_count(cfg: Config) -> int:
     return int(load_library().dbw_param_count(ctypes.byref(cfg)))
+
+
+def grads_route(cfg: Config) -> tuple[bool, int, bool]:
+    """Kernels of the softmax gradients of a configuration (dbw_grads_route):
+    (single pass over X, row slabs per worker, logits per dataset row)."""
+    out = [c_int32() for _ in range(3)]
+    st = load_library().dbw_grads_route(ctypes.byref(cfg), *map(ctypes.byref, out))
+    if st != DBW_OK:
+        raise DBWError(st, "invalid configuration")
+    return bool(out[0].value), out[1].value, bool(out[2].value)
 
 
 def time_estimate(cnt, tsum) -> np.ndarray:

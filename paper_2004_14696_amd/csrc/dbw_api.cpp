@@ -512,6 +512,17 @@ DBW_API int64_t dbw_param_count(const dbw_config* cfg) {
   return param_count(*cfg);
 }
 
+DBW_API dbw_status dbw_grads_route(const dbw_config* cfg, int32_t* single_pass, int32_t* slabs, int32_t* per_row) {
+  std::string why;
+  if (!config_ok(cfg, &why) || !single_pass || !slabs || !per_row) return DBW_EINVAL;
+  dbw::SoftmaxPlan p;
+  if (cfg->model == DBW_SOFTMAX) p = dbw::softmax_plan(cfg->n, cfg->B, cfg->d, cfg->C, cfg->S);
+  *single_pass = p.fused;
+  *slabs = p.slabs;
+  *per_row = p.row_floats > 0 ? 1 : 0;
+  return DBW_OK;
+}
+
 namespace {
 thread_local std::string t_free_error = "no error";   // context-free calls of this thread
 }  // namespace

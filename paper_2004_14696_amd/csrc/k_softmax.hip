@@ -75,7 +75,7 @@ __device__ __forceinline__ int64_t xcd_logical(int64_t b, int64_t per_xcd) {
 constexpr int FUSED_MAX_ROWS = 1024;   // rows of one slab staged in LDS
 
 // ---------------------------------------------------------------------------
-// Matrix-core variant of the single pass (C <= 16, d % 4 == 0, d <= 3072).
+// The single pass over X (C <= 16, 4 <= d <= 3072).
 //
 // Eight waves split the feature dimension; wave w owns features
 // w*64U + 64u + 4m + j (u < U, m < 16, j < 4).  Rows stream through in
@@ -92,6 +92,11 @@ constexpr int FUSED_MAX_ROWS = 1024;   // rows of one slab staged in LDS
 // partials of the rows its lanes hold and runs their softmax (16-lane DPP
 // max and sum), so lane (m, g) forms r[row g + 4e][class m] itself -- the
 // B operand of the same MFMAs.  One block barrier per chunk.
+//
+// RAG (d % 4 != 0): rows start at any 4-byte boundary, which the loads allow; the
+// lane whose four features pass the row's end loads the row's last four and
+// shifts them down before they are used, zeros behind.  The last P % 4 values
+// of W and of G go one by one.
 constexpr int MF_WAVES = 8;
 constexpr int MF_T = MF_WAVES * WAVE;
 constexpr int MF_ROWS = 8;
@@ -125,7 +130,7 @@ __device__ __forceinline__ float f4_at(const float4& v, int j) {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <int U, int CW>
+template <int U, int CW, bool RAG>
 __global__ __launch_bounds__(MF_T) void k_softmax_mfma(SoftmaxArgs a, int slabs, int rps, int64_t per_xcd) {
   static_assert(CW % 2 == 0 && CW <= 16, "class padding");
   // W in lane order: lane (w, m) reads its 4U features x CW classes from one
@@ -154,9 +159,9 @@ __global__ __launch_bounds__(MF_T) void k_softmax_mfma(SoftmaxArgs a, int slabs,
   const int nrows = min(a.B, b0 + rps) - b0;
 
   // The chain to the first products is the row indices, then the rows: the
-  // indices are loaded first, then W (coalesced float4 pieces, P % 4 == 0
-  // since d % 4 == 0), then the labels, which are checked and staged only
-  // after the first rows are on their way (the wait for a load also waits
+  // indices are loaded first, then W (coalesced float4 pieces), then the
+  // labels, which are checked and staged only after the first rows are on
+  // their way (the wait for a load also waits
   // for every load issued before it, so the labels go out before the rows).
   constexpr int RPT = FUSED_MAX_ROWS / MF_T;   // slab rows per thread
   int64_t rowv[RPT];
@@ -176,6 +181,7 @@ __global__ __launch_bounds__(MF_T) void k_softmax_mfma(SoftmaxArgs a, int slabs,
       wl[k] = buf_f32x4(wrs, e4 < n4 ? static_cast<uint32_t>(e4 * 16) : kOutOfRange);
     }
   }
+  const float wrest = RAG && tid < static_cast<int>(P & 3) ? a.W[4 * (int64_t)n4 + tid] : 0.f;
   float4* w4 = reinterpret_cast<float4*>(Ws);
   if (d < MF_T * U) {
     // slots of features past d must read as 0 (their rows carry finite values
@@ -210,7 +216,23 @@ __global__ __launch_bounds__(MF_T) void k_softmax_mfma(SoftmaxArgs a, int slabs,
   // per load; kOutOfRange + 12 KiB stays out of range).
   auto load_u = [&](uint32_t roff, int u) -> float4 {
     const int f = fbase + 64 * u;
+    if (RAG) return buf_f32x4(xr, roff + (f + 4 <= d ? static_cast<uint32_t>(f * 4) : f < d ? static_cast<uint32_t>((d - 4) * 4) : 0u));
     return buf_f32x4(xr, roff + (f < d ? static_cast<uint32_t>(f * 4) : 0u));
+  };
+  // the row's end in its place (only the wave and group that hold it)
+  auto ragged = [&](float4 (&x)[2][U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int g0 = __builtin_amdgcn_readfirstlane(w) * 64 * U + 64 * u;
+      if (g0 >= d || g0 + 64 < d) continue;
+      const int f = fbase + 64 * u, sh = f < d ? max(0, f + 4 - d) : 0;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float4 v = x[e][u];
+        x[e][u] = make_float4(sh == 0 ? v.x : sh == 1 ? v.y : sh == 2 ? v.z : v.w, sh == 0 ? v.y : sh == 1 ? v.z : sh == 2 ? v.w : 0.f,
+                              sh == 0 ? v.z : sh == 1 ? v.w : 0.f, sh == 0 ? v.w : 0.f);
+      }
+    }
   };
   float4 xa[2][U], xb[2][U];   // two chunks in flight, roles alternate
   {
@@ -259,6 +281,10 @@ __global__ __launch_bounds__(MF_T) void k_softmax_mfma(SoftmaxArgs a, int slabs,
           }
         }
       }
+    }
+    if (RAG && tid < static_cast<int>(P & 3)) {
+      const int e = 4 * n4 + tid, f = e / C;
+      Ws[slot(f / 4, (f % 4) * CW + e - f * C)] = wrest;
     }
   }
   __syncthreads();
@@ -374,6 +400,7 @@ __global__ __launch_bounds__(MF_T) void k_softmax_mfma(SoftmaxArgs a, int slabs,
 #pragma unroll
       for (int u = 0; u < U; ++u) B[0][u] = load_u(rn, u);
     }
+    if (RAG) ragged(A);
     logits(A, z, &Ws[(w * 16 + m) * SL]);
     const int buf = (cb / MF_ROWS) & 1;
     reduce_logits(z, buf);
@@ -432,8 +459,12 @@ __global__ __launch_bounds__(MF_T) void k_softmax_mfma(SoftmaxArgs a, int slabs,
     __syncthreads();
     const float4* s4 = reinterpret_cast<const float4*>(Ws);
     float4* o4 = reinterpret_cast<float4*>(a.G + (int64_t)i * P);
-    if (!a.row_mask || a.row_mask[i])
+    if (a.row_mask && !a.row_mask[i]) {
+    } else if (RAG) {
+      for (int k = tid; k < static_cast<int>(P); k += MF_T) a.G[(int64_t)i * P + k] = Ws[k];
+    } else {
       for (int k = tid; k < static_cast<int>(P / 4); k += MF_T) o4[k] = s4[k];
+    }
   }
   if (w == 0) {
     // the loss of every row sits in its label's lane of wave 0
@@ -485,9 +516,13 @@ __global__ __launch_bounds__(256) void k_slab_reduce_tiles(SoftmaxArgs a, int sl
   const int f0 = x * 64;
   const int nf = min(64, d - f0);   // features past d are not stored
   float* dst = a.G + (int64_t)i * P + (int64_t)f0 * C;
-  if (!a.row_mask || a.row_mask[i])
+  if (a.row_mask && !a.row_mask[i]) {
+  } else if (P % 4 == 0) {
     for (int k = threadIdx.x; k < nf * C / 4; k += 256)
       reinterpret_cast<float4*>(dst)[k] = reinterpret_cast<const float4*>(tile)[k];
+  } else {
+    for (int k = threadIdx.x; k < nf * C; k += 256) dst[k] = tile[k];
+  }
   if (x == 0 && threadIdx.x == 0) {
     float l = 0.f;
     for (int q = 0; q < slabs; ++q) l += a.lossp[(int64_t)i * slabs + q];
@@ -921,8 +956,11 @@ template <int U, int CW>
 hipError_t launch_mfma_t(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream_t s) {
   const int64_t nb = (int64_t)a.n * p.slabs;
   const int64_t per_xcd = (nb + NXCD - 1) / NXCD;
-  hipLaunchKernelGGL((k_softmax_mfma<U, CW>), dim3(static_cast<unsigned>(per_xcd * NXCD)), dim3(MF_T), 0, s, a,
-                     p.slabs, p.rows_per_slab, per_xcd);
+  auto pass = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(per_xcd * NXCD)), dim3(MF_T), 0, s, a, p.slabs, p.rows_per_slab, per_xcd);
+  };
+  if (a.d % 4 == 0) pass(k_softmax_mfma<U, CW, false>);
+  else pass(k_softmax_mfma<U, CW, true>);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.slabs == 1 || a.keep_slabs) return e;
   const dim3 g2(static_cast<unsigned>((a.d + 63) / 64), static_cast<unsigned>(a.n));
@@ -963,29 +1001,39 @@ SoftmaxPlan split_plan(int n, int B, int d, int C, int64_t S) {
 
 }  // namespace
 
-// Single pass or GEMM path for up to 16 classes: the single pass reads X once
-// and runs near the memory rate once there is enough of it, but a block is a
-// chain of latencies (prologue, chunks of 8 rows, a barrier each) and pads the
-// features to 512 a wave row; the two products of the GEMM path spread a small
-// problem over the chip and X stays in the caches between them.  Measured
-// (us per step, single pass / GEMM path, rows = n x B): 4 x 32 x 784 23.5 /
-// 21.0; 16 x 128 x 784 26.6 / 23.1; 16 x 128 x 3072 38.9 / 32.9; 32 x 256 x
-// 784 30.0 / 28.4; 64 x 256 x 784 37.6 / 40.4; 64 x 256 x 3072 65 / 110; but
-// 128 x 200 x 200 42 / 33 and 256 x 512 x 200 123 / 66.
-constexpr int64_t kSinglePassMin = 6500000;   // elements of the minibatches
-constexpr int kSinglePassMinD = 256;
+// Single pass or GEMM path for up to 16 classes.  The single pass reads X once,
+// but a block is a chain: a prologue, then `chunks` chunks of 8 rows with a
+// barrier each; it pads the features to 512 U and the classes to 4, 10 or 16, and
+// several slabs a worker have to be summed (beyond 8 with a wait a slab in the
+// PS kernel).  The GEMM path spreads a small problem over the chip, pads rows to
+// 16 and 32, and reads X twice, from the caches while there is little of it.
+// The estimate is the single pass's time less the GEMM path's (us), fitted to
+// 2639 pairs of whole steps: n = 4 .. 256, B = 16 .. 512, d = 64 .. 3072, 2 .. 16 classes, all
+// or none of G written (the bits must not depend on that).  The path it takes
+// is 0.3% slower than the better one on average, more than 5% in 67 pairs, 12%
+// at most.  us, single pass / GEMM path, C = 4: 256 x 16 x 1500 27.9 / 35.9, 64 x 64 x
+// 1500 28.1 / 28.3, 16 x 64 x 3072 31.3 / 28.4; C = 10: 64 x 16 x 200 18.5 / 23.1, 16 x
+// 64 x 1500 29.7 / 26.0, 128 x 200 x 200 42 / 33; C = 16: 16 x 16 x 200 18.9 / 22.0, 4 x 64 x
+// 200 25.6 / 22.5, 16 x 256 x 1500 36.9 / 27.9.  From 8 million elements on (d >= 256)
+// the one reading of X decides: 64 x 256 x 3072 x 10 65 / 110, 256 x 48 x 744 x 16
+// 39.6 / 43.5.
+bool single_pass_pays(int64_t elements, int d, int width, int U, int chunks, int slabs) {
+  if (elements >= 8000000 && d >= 256) return true;
+  struct Fit {
+    double product, chunk, million, sum, many, gemm;
+  };
+  static constexpr Fit kFit[3] = {{0.40, 0.65, 1.20, 1.2, 1.6, 5.1}, {0.60, 0.60, 1.30, 4.8, 4.5, 4.3}, {0.90, 0.60, 0.75, 2.0, 5.0, 4.3}};
+  const Fit& f = kFit[width == 4 ? 0 : width == 10 ? 1 : 2];
+  return f.product * chunks * U + f.chunk * chunks - f.million * 1e-6 * elements + (slabs > 1 ? f.sum : 0.0) +
+             (slabs > 8 ? f.many : 0.0) < f.gemm;
+}
 
 SoftmaxPlan softmax_plan(int n, int B, int d, int C, int64_t S) {
   SoftmaxPlan p;
   const int cw = C <= 4 ? 4 : C <= 10 ? 10 : C <= 16 ? 16 : 0;
   const int U = (d + MF_T - 1) / MF_T;
   const bool fits = cw == 16 ? U <= 4 : U <= 6;
-  if (!cw || d % 4 != 0 || !fits || (int64_t)n * B * d < kSinglePassMin || d < kSinglePassMinD)
-    return split_plan(n, B, d, C, S);
-  // 8 waves x 64U features, W staged in LDS
-  p.fused = 1;
-  p.per_thread = U;
-  p.cpad = cw;
+  if (!cw || !fits || d < 4) return split_plan(n, B, d, C, S);
   // about 256 blocks, at least four 8-row chunks per slab
   int slabs = 256 / n, max_slabs = B / (4 * MF_ROWS);
   slabs = slabs < 1 ? 1 : slabs;
@@ -994,8 +1042,14 @@ SoftmaxPlan softmax_plan(int n, int B, int d, int C, int64_t S) {
   int rps = (B + slabs - 1) / slabs;
   rps = (rps + MF_ROWS - 1) / MF_ROWS * MF_ROWS;
   if (rps > FUSED_MAX_ROWS) rps = FUSED_MAX_ROWS;
+  slabs = (B + rps - 1) / rps;
+  if (!single_pass_pays((int64_t)n * B * d, d, cw, U, rps / MF_ROWS, slabs)) return split_plan(n, B, d, C, S);
+  // 8 waves x 64U features, W staged in LDS
+  p.fused = 1;
+  p.per_thread = U;
+  p.cpad = cw;
   p.rows_per_slab = rps;
-  p.slabs = (B + rps - 1) / rps;
+  p.slabs = slabs;
   p.part = (int64_t)MF_T * U * C;   // tile-order partial
   // one worker's partials are read through one buffer resource
   return (int64_t)p.slabs * p.part * 4 <= kMaxBufferBytes ? p : split_plan(n, B, d, C, S);

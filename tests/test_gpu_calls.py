@@ -43,8 +43,8 @@ SOFTMAX_SHAPES = [
     (2, 9, 3000, 16),
     (3, 21, 2048, 16),     # 16 classes, 2048 features
     (5, 37, 1536, 4),      # 4 classes, ragged 8-row chunks
-    (9, 300, 512, 7),      # several row slabs per worker, ragged last slab
-    (2, 10, 4500, 10),     # d beyond the fused kernel: GEMM path
+    (9, 300, 512, 7),
+    (2, 10, 4500, 10),     # d beyond the single pass
     (4, 24, 300, 100),     # 100 classes: GEMM path on the matrix cores
     (4, 70, 132, 20),      # one full class tile and one 4-wide stripe
     (3, 45, 516, 24),      # one full tile and two stripes
@@ -69,6 +69,78 @@ def test_worker_grads_softmax(n, B, d, C):
     for i in range(n):
         assert rel_err(host(G)[i], Go[i]) <= RTOL
     assert rel_err(host(loss), lo) <= RTOL
+
+
+# The single pass: every class width with classes below it, every count of
+# feature groups, feature counts off 4 (the row's end loaded from the row's last
+# four), rows off the chunks of 8, one slab a worker (G assembled in LDS) and
+# several, odd and even chunk counts, minibatches gathered and materialised.
+# (n, B, d, C, S, slabs)
+SINGLE_PASS_SHAPES = [
+    (200, 512, 260, 7, 0, 1), (200, 512, 261, 7, 3000, 1), (129, 101, 1000, 16, 0, 1), (129, 101, 1001, 15, 500, 1),
+    (40, 333, 1536, 4, 0, 6), (40, 333, 1537, 3, 900, 6), (9, 1000, 1020, 13, 4000, 25), (9, 1000, 1023, 13, 0, 25),
+    (20, 160, 3071, 10, 800, 5), (20, 160, 3072, 9, 0, 5), (30, 150, 2050, 3, 700, 4), (30, 150, 2048, 4, 0, 4),
+    (300, 16, 1999, 16, 0, 1), (300, 16, 2000, 11, 900, 1), (32, 400, 700, 9, 300, 8), (140, 72, 2561, 5, 600, 1),
+    (4, 16, 784, 4, 90, 1), (5, 13, 101, 3, 0, 1), (1, 7, 5, 2, 0, 1), (1, 1, 4, 2, 0, 1), (3, 16, 510, 10, 60, 1),
+    (2, 9, 1000, 10, 0, 1), (2, 16, 300, 16, 40, 1),
+]
+
+
+@pytest.mark.parametrize("n,B,d,C,S,slabs", SINGLE_PASS_SHAPES)
+def test_worker_grads_softmax_single_pass(n, B, d, C, S, slabs):
+    assert pb.grads_route(pb.make_config("softmax", n, B, d, C, S=S)) == (True, slabs, False)
+    g = torch.Generator(device="cuda").manual_seed(n * 13 + B * 5 + d * 3 + C)
+    X = torch.randn((S, d) if S else (n, B, d), generator=g, device="cuda")
+    y = torch.randint(0, C, X.shape[:-1], generator=g, device="cuda", dtype=torch.int32)
+    rows = torch.randint(0, S, (n, B), generator=g, device="cuda", dtype=torch.int32) if S else None
+    if S:
+        rows[0, 0], rows[-1, -1] = 0, S - 1
+    W = 0.3 / d ** 0.5 * torch.randn(d * C, generator=g, device="cuda")
+    ctx = _ctx(n, B, d, C, S=S)
+    # (behind G, to see that nothing is written past it)
+    buf = torch.full((n * d * C + 64,), 7.0, device="cuda")
+    G, loss = ctx.worker_grads(W, X, y, rows=rows, G=buf[:n * d * C].view(n, d * C))
+    ctx.sync()
+    assert bool((buf[n * d * C:] == 7.0).all())
+    # rounding of fp32 sums of d and B terms; exp and log to a few ulp
+    tol = 2.0 ** -23 * (16 + d ** 0.5 + B ** 0.5)
+    for i in sorted({0, n // 2, n - 1}):
+        Xi, yi = (X[rows[i].long()], y[rows[i].long()]) if S else (X[i], y[i])
+        Gi, li = omodel.softmax_worker_grads(host(W).astype(np.float64), host(Xi)[None].astype(np.float64),
+                                             host(yi)[None], C)
+        assert rel_err(host(G)[i], Gi[0]) <= tol
+        assert rel_err(host(loss)[i], li[0]) <= tol
+
+
+@pytest.mark.parametrize("d", [700, 701])
+def test_worker_grads_softmax_single_pass_rows_next_to_others(d):
+    # A row's neighbours in memory (NaN here) stay out of its results, and a bad
+    # row index or label is reported.
+    n, B, C, S = 32, 400, 9, 300
+    assert pb.grads_route(pb.make_config("softmax", n, B, d, C, S=S)) == (True, 8, False)
+    rng = np.random.default_rng(d)
+    X = rng.standard_normal((S, d)).astype(np.float32)
+    X[1::2] = np.nan
+    y = rng.integers(0, C, size=S, dtype=np.int32)
+    rows = (2 * rng.integers(0, S // 2, size=(n, B))).astype(np.int32)
+    W = (0.01 * rng.standard_normal((d, C))).astype(np.float32)
+    ctx = _ctx(n, B, d, C, S=S)
+    Wd, Xd, yd = to_dev(torch, W.ravel()), to_dev(torch, X), to_dev(torch, y)
+    G, loss = ctx.worker_grads(Wd, Xd, yd, rows=to_dev(torch, rows))
+    ctx.sync()
+    tol = 2.0 ** -23 * (16 + d ** 0.5 + B ** 0.5)
+    for i in (0, n - 1):
+        Gi, li = omodel.softmax_worker_grads(W.astype(np.float64).ravel(), X[rows[i]][None].astype(np.float64), y[rows[i]][None], C)
+        assert rel_err(host(G)[i], Gi[0]) <= tol and rel_err(host(loss)[i], li[0]) <= tol
+    bad = rows.copy()
+    bad[3, 399] = S
+    yb = y.copy()
+    yb[rows[5, 7]] = C
+    for r, lab, status in ((bad, y, pb.DBW_ERANGE), (rows, yb, pb.DBW_EINVAL)):
+        ctx.worker_grads(Wd, Xd, to_dev(torch, lab), rows=to_dev(torch, r))
+        with pytest.raises(pb.DBWError) as e:
+            ctx.sync()
+        assert e.value.status == status
 
 
 # Edges of the split products: K tails of 1 .. 31 after whole slices of 32 and
@@ -681,8 +753,11 @@ def test_choose_b_guard_and_negative_gains():
 # -- fixed-order reductions ----------------------------------------------------------------
 
 @pytest.mark.parametrize("model,n,B,d,H,C", [
-    ("softmax", 16, 128, 784, 0, 10),     # single pass, row slabs summed in slab order
-    ("softmax", 9, 300, 512, 0, 7),       # several slabs, ragged last slab
+    ("softmax", 16, 128, 784, 0, 10),     # products, K split over a block's waves
+    ("softmax", 9, 300, 512, 0, 7),
+    ("softmax", 32, 400, 700, 0, 9),      # single pass, row slabs summed in slab order
+    ("softmax", 9, 1000, 1021, 0, 13),    # 25 slabs, features off 4
+    ("softmax", 200, 512, 261, 0, 7),     # single pass, one slab
     ("softmax", 4, 24, 300, 0, 100),      # narrow-class matrix-core path
     ("softmax", 2, 130, 388, 0, 52),      # class tiles and a stripe
     ("mlp", 32, 64, 784, 512, 10),        # split K, head slabs, slab sums beside dW1

@@ -301,8 +301,9 @@ def test_lockstep_256_workers_100_classes_full_run_benchmarked_mode():
 @pytest.mark.parametrize("base", [C2, C3], ids=lambda c: c.name)
 @pytest.mark.parametrize("k", ["one", "all"])
 def test_lockstep_benchmarked_mode_static_k(base, k):
-    # the slab-source PS kernel at its extremes: a single selected worker (the
-    # variance then takes the window mean) and every worker
+    # the PS kernel (C2: from rows, C3: from slab partials) at its extremes: a
+    # single selected worker (the variance then takes the window mean) and
+    # every worker
     kk = 1 if k == "one" else base.n
     orc = _lockstep(base.replace(g_rows="none", policy="static", k_static=kk), 8)
     assert orc.ks == [kk] * 8
@@ -339,23 +340,35 @@ def test_free_running_trajectory(cfg):
 
 
 def test_lockstep_selected_rows_16_workers():
-    # the selected workers' slab partials are aggregated in one kernel; only
-    # their rows of G are written
+    # the two products write every row to a buffer of their own; the PS kernel
+    # copies the selected ones to G
     _lockstep(C2.replace(g_rows="selected"), 60)
 
 
 def test_lockstep_selected_rows_64_workers_first_iterations():
+    # the selected workers' slab partials are aggregated in one kernel; only
+    # their rows of G are written
     _lockstep(C3.replace(g_rows="selected"), 8)
 
 
-@pytest.mark.parametrize("base", [C2, C3], ids=lambda c: c.name)
-def test_slab_aggregation_matches_row_aggregation(base):
+# C2: from rows; the others from the single pass's slab partials, with every slab
+# count the PS kernel unrolls differently, and feature counts off 4
+def _slabs(n, B, d, C):
+    return C3.replace(name=f"n{n}_B{B}_d{d}_C{C}", n=n, B=B, d=d, C=C, S=2000)
+
+
+@pytest.mark.parametrize("base,slabs", [(C2, 1), (C3, 4), (_slabs(100, 100, 1000, 10), 2), (_slabs(80, 120, 1021, 7), 3),
+                                        (_slabs(50, 200, 900, 4), 5), (_slabs(42, 250, 1102, 10), 6),
+                                        (_slabs(36, 300, 802, 3), 7), (_slabs(32, 300, 1030, 13), 8),
+                                        (_slabs(18, 500, 1027, 10), 13)], ids=lambda c: getattr(c, "name", None))
+def test_slab_aggregation_matches_row_aggregation(base, slabs):
     # The same iterations with every row of G written and read back, with the
     # selected rows only, and with none: k, the mask, g, the update and the
     # losses are bitwise equal; the statistics differ only by the order of
     # their partial sums.  Rows of workers that were not selected keep stale
     # values in the fused modes.
     cfg = base.replace(policy="static", k_static=base.n // 2 + 1)
+    assert pb.grads_route(pb.config_from(cfg, S=cfg.S)) == (base is not C2, slabs, False)
     X, y = gen.dataset(cfg)
     Xd, yd = to_dev(torch, X), to_dev(torch, y)
     modes = ("all", "selected", "none")
@@ -485,8 +498,10 @@ def _exact_offset_batch(n, B, d, rng):
     (8, 16, 8, 8),
     (6, 16, 40000, 2),     # P = 160000: separate choice, then the aggregation kernel
     (6, 16, 40000, 6),
-    (4, 256, 64, 2),       # row slabs: the selected workers' slab partials summed in the PS kernel
+    (4, 256, 64, 2),
     (4, 256, 64, 4),
+    (32, 256, 1000, 2),    # row slabs: the selected workers' slab partials summed in the PS kernel
+    (32, 256, 1000, 32),
 ])
 def test_step_statistics_large_common_offset(n, B, d, k):
     # The PS kernels accumulate deviations from the fastest worker's row (a
@@ -495,6 +510,7 @@ def test_step_statistics_large_common_offset(n, B, d, k):
     # about 0.02: a sum of squares taken without the shift would lose every
     # digit of Eq. sumvariancekt in fp32.
     C = 4
+    assert pb.grads_route(pb.make_config("softmax", n, B, d, C)) == ((n, d) != (6, 40000) and B * d != 64 * 256, 8 if n == 32 else 1, False)
     rng = np.random.default_rng(7000 + n * d + k)
     X, y = _exact_offset_batch(n, B, d, rng)
     ticks = rng.permutation(np.arange(1, n + 1, dtype=np.int64) * 1000)

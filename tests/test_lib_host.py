@@ -54,6 +54,28 @@ def test_param_count_and_config_validation(lib):
     assert pb.param_count(pb.make_config("mlp", 4, 8, 5, 3, H=0)) == -1
 
 
+def test_grads_route(lib):
+    # the workloads; the two sides of the single pass's rule and its limits
+    # (C <= 16, d <= 3072, 16 classes only up to 2048 features); minibatches that
+    # repeat the dataset's rows
+    def route(n, B, d, C, S=0, model="softmax", H=0, **kw):
+        return pb.grads_route(pb.make_config(model, n, B, d, C, H, S=S, **kw))
+    assert route(4, 32, 784, 10, 60000) == route(16, 128, 784, 10, 60000) == (False, 1, False)
+    assert route(64, 256, 3072, 10, 50000) == (True, 4, False)
+    assert route(256, 512, 3072, 100, 50000) == (False, 1, True)
+    assert route(256, 512, 3072, 100) == route(64, 256, 3073, 10) == route(64, 256, 2052, 16) == (False, 1, False)
+    assert route(64, 256, 2048, 16) == route(64, 256, 1021, 16) == (True, 4, False)
+    assert route(64, 256, 1021, 17) == route(8, 40, 3, 2) == (False, 1, False)
+    assert route(16, 16, 200, 10) == (True, 1, False) and route(16, 64, 1500, 10) == (False, 1, False)
+    assert route(24, 512, 40, 20, 8192) == (False, 1, True) and route(23, 534, 40, 20, 8192) == (False, 1, False)
+    assert route(32, 64, 784, 10, model="mlp", H=512) == (False, 1, False)
+    # the rows of G a step writes do not change the path (its bits are those of "all")
+    for n, B, d, C in ((16, 128, 784, 10), (64, 64, 200, 4), (32, 300, 1030, 13)):
+        assert len({route(n, B, d, C, g_rows=g) for g in ("all", "selected", "none")}) == 1
+    with pytest.raises(pb.DBWError):
+        route(0, 1, 1, 2)
+
+
 def _grid(rng, n, rows, iters, full=True, law="exp"):
     cnt = np.zeros((n, n), np.int64)
     tsum = np.zeros((n, n), np.int64)
