@@ -197,7 +197,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_mlp_dw1(MlpArgs a, int slabs, 
     __syncthreads();
     sg_loop<MT == 1, MT, NT, NW, 1>(
         L, c0 / SG_K, c0 / SG_K + nb,
-        [&](int kb, float (&x)[MT][8]) { sg_load_cols<MT>(xs, srow + (kb * SG_K - c0) + 8 * g, foff, x); },
+        [&](int kb, float (&x)[MT][8], uint32_t dead = 0) { sg_load_cols<MT>(xs, srow + (kb * SG_K - c0) + 8 * g, foff, x, dead); },
         [&](int, float (&x)[MT][8]) { sg_shift<MT>(shift, edge, x); },
         [&](int kb) { return dp + sg_frag(kb, tiles, nt0, 0) * 64; }, acc);
   }

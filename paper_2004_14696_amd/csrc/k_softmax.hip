@@ -797,7 +797,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_grads(SoftmaxArgs a, int ti
     for (int b = tid; b < nb * SG_K; b += 64 * NW)
       srow[b] = b < nr ? static_cast<uint32_t>(sample_row(a, i, c0 + b, false) * d * 4) : kOutOfRange;
     __syncthreads();
-    auto load = [&](int kb, float (&x)[MT][8]) { sg_load_cols<MT>(xs, srow + (kb * SG_K - c0) + 8 * g, foff, x); };
+    auto load = [&](int kb, float (&x)[MT][8], uint32_t dead = 0) { sg_load_cols<MT>(xs, srow + (kb * SG_K - c0) + 8 * g, foff, x, dead); };
     auto prep = [&](int, float (&x)[MT][8]) { sg_shift<MT>(shift, edge, x); };
     auto frag = [&](int kb) { return rp + sg_frag(kb, tiles, nt0, 0) * 64; };
     if constexpr (KS)

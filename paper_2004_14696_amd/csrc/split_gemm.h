@@ -160,18 +160,20 @@ __device__ __forceinline__ void sg_barrier() {
   asm volatile("s_barrier" ::: "memory");
 }
 
-// The slice loop over K slices kb0 .. kb1 - 1.  load(kb, x) fetches this
+// The slice loop over K slices kb0 .. kb1 - 1.  load(kb, x, dead) fetches this
 // wave's A values of a slice (MT tiles x 8), frag(kb) is the address of the
 // slice's first B fragment (NT * 3 of them, consecutive), prep(kb, x) runs just
 // before a slice's values are split.  PD slices are on their way in registers
 // (PD = 2 where a block's matrix work per slice is shorter than a memory
 // latency; 4 gained nothing more, nor did two teams of waves that split K); a
 // slice's B fragments are loaded before its A values, so that storing them to
-// LDS does not wait for the A values.  With one row tile the last PD slices
-// have bodies of their own, without the loads and the barrier that nothing
-// follows (a block with one slice fetched three: MLP 18 x 34 x 508-868-5 47.9 -> 45.8
-// us, softmax 64 x 38 x 164 x 580 45.5 -> 41.9); with more, the
-// bodies cost registers that spill, and loads past the last slice repeat it.
+// LDS does not wait for the A values.  Loads past the last slice are out of
+// range (dead), so that the number in flight is the same at every step and they
+// cost no memory access, and the last slice neither stages nor waits (fetching
+// it again, as before: step of 4 x 32 x 784 x 10 23.7 -> 20.6 us, MLP 32 x 64 x 784-512-10
+// 53.4 -> 51.8, softmax 64 x 38 x 164 x 580 45.5 -> 42.7).  Bodies of their own for
+// the last slices take up to 60 registers more, for the accumulators' ways
+// through them: 71 x 155 x 760 x 380 109 -> 117 us.
 template <bool APART, int MT, int NT, int NW, int PD, class Load, class Prep, class Frag>
 __device__ __forceinline__ void sg_loop(SgLds<NT, NW>& L, int kb0, int kb1, Load&& load, Prep&& prep, Frag&& frag,
                                         sg_f32x4 (&acc)[NT][MT]) {
@@ -181,13 +183,13 @@ __device__ __forceinline__ void sg_loop(SgLds<NT, NW>& L, int kb0, int kb1, Load
   sg_u32x4 rb[PD][NB];
   float x[PD][MT][8];
   auto fetch = [&](int kb, sg_u32x4 (&r)[NB], float (&v)[MT][8]) {
-    const sg_u32x4* src = frag(kb);
+    const bool live = kb < kb1;
+    kb = min(kb, kb1 - 1);
+    const __amdgpu_buffer_rsrc_t src = make_rsrc(frag(kb), live ? NT * 3 * 1024u : 0u);
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      const int f = wv + NW * q;
-      r[q] = src[(NT * 3 % NW == 0 ? f : min(f, NT * 3 - 1)) * 64 + lane];
-    }
-    load(kb, v);
+    for (int q = 0; q < NB; ++q)   // (fragments past the slice's NT * 3 read as 0)
+      r[q] = __builtin_bit_cast(sg_u32x4, __builtin_amdgcn_raw_buffer_load_b128(src, (wv * 64 + lane) * 16, q * NW * 1024, 0));
+    load(kb, v, live ? 0u : kOutOfRange);
   };
   auto stage = [&](int buf, const sg_u32x4 (&r)[NB]) {
 #pragma unroll
@@ -195,20 +197,21 @@ __device__ __forceinline__ void sg_loop(SgLds<NT, NW>& L, int kb0, int kb1, Load
   };
   if (kb0 >= kb1) return;
 #pragma unroll
-  for (int p = 0; p < PD; ++p) fetch(min(kb0 + p, kb1 - 1), rb[p], x[p]);   // (no branch: the waits stay partial)
+  for (int p = 0; p < PD; ++p) fetch(kb0 + p, rb[p], x[p]);
   stage(0, rb[0]);
   sg_barrier();
-  // slice kb: LDS buffer u (its B), register slot u % PD (its A).  FETCH: the
-  // slot is refilled with slice kb + PD once its A values are split (its B
-  // fragments were staged a slice ago); NEXT: another slice follows.
-  auto slice = [&](int kb, auto uc, auto fetch_c, auto next_c) {
+  // slice kb: LDS buffer u (its B), register slot u % PD (its A); the slot is
+  // refilled with slice kb + PD once its A values are split (its B fragments
+  // were staged a slice ago).  more: another slice follows (at the end of an
+  // odd count known beforehand: LAST)
+  auto slice = [&](int kb, auto uc, auto last, bool more) {
     constexpr int u = decltype(uc)::value, slot = u % PD, next = (u + 1) % PD;
-    constexpr bool FETCH = decltype(fetch_c)::value, NEXT = decltype(next_c)::value;
+    constexpr bool LAST = decltype(last)::value;
     SgParts a[MT];
     prep(kb, x[slot]);
 #pragma unroll
     for (int t = 0; t < MT; ++t) a[t] = sg_split8(x[slot][t]);
-    if constexpr (FETCH) fetch(MT == 1 ? kb + PD : min(kb + PD, kb1 - 1), rb[slot], x[slot]);
+    if constexpr (!LAST) fetch(kb + PD, rb[slot], x[slot]);
     __builtin_amdgcn_sched_barrier(0);   // the loads go out before the products
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
@@ -221,48 +224,19 @@ __device__ __forceinline__ void sg_loop(SgLds<NT, NW>& L, int kb0, int kb1, Load
       __builtin_amdgcn_sched_group_barrier(0x008, 6 * MT, 0);
     }
     __builtin_amdgcn_sched_barrier(0);   // and are waited for after them
-    if constexpr (NEXT) {
+    if (!LAST && more) {
       stage(u ^ 1, rb[next]);
       sg_barrier();
     }
   };
-  constexpr std::integral_constant<int, 0> even{};
-  constexpr std::integral_constant<int, 1> odd{};
-  constexpr std::true_type yes{};
-  constexpr std::false_type no{};
   // (whole pairs in the loop: a way round the second slice would make the
   // compiler wait for every load at the loop's head)
   int kb = kb0;
-  if constexpr (MT > 1) {
-    for (; kb + 1 < kb1; kb += 2) {
-      slice(kb, even, yes, yes);
-      slice(kb + 1, odd, yes, yes);
-    }
-    if (kb < kb1) slice(kb, even, yes, yes);
-    return;
+  for (; kb + 1 < kb1; kb += 2) {
+    slice(kb, std::integral_constant<int, 0>{}, std::false_type{}, true);
+    slice(kb + 1, std::integral_constant<int, 1>{}, std::false_type{}, kb + 2 < kb1);
   }
-  const int full = kb1 - PD;   // the slices before this one fetch another
-  if (PD == 1 || full >= kb0) {
-    for (; kb + 1 < full; kb += 2) {
-      slice(kb, even, yes, yes);
-      slice(kb + 1, odd, yes, yes);
-    }
-    if (kb < full) {
-      slice(kb, even, yes, yes);
-      if constexpr (PD == 1) {
-        slice(kb + 1, odd, no, no);
-        return;
-      } else {
-        slice(kb + 1, odd, no, yes);
-        kb += 2;
-      }
-    } else if constexpr (PD == 2) {
-      slice(kb, even, no, yes);
-      slice(kb + 1, odd, no, no);
-      return;
-    }
-  }
-  slice(kb, even, no, no);
+  if (kb < kb1) slice(kb, std::integral_constant<int, 0>{}, std::true_type{}, false);
 }
 
 // The loop for products with few tiles: the block's NW waves work on the same
@@ -387,13 +361,13 @@ struct SgRows {
     shift = TINY ? 0 : max(0, k0 - (K - 8));
   }
   __device__ __forceinline__ int slices() const { return (K + SG_K - 1) / SG_K; }
-  __device__ __forceinline__ void operator()(int kb, float (&x)[MT][8]) const {
+  __device__ __forceinline__ void operator()(int kb, float (&x)[MT][8], uint32_t dead = 0) const {
     if constexpr (TINY) {
       const int kg = 8 * ((threadIdx.x & 63) >> 4);
 #pragma unroll
       for (int t = 0; t < MT; ++t)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[t][e] = buf_f32(xs, kg + e < K ? roff[t] + 4 * e : kOutOfRange);
+        for (int e = 0; e < 8; ++e) x[t][e] = buf_f32(xs, (kg + e < K ? roff[t] + 4 * e : kOutOfRange) | dead);
     } else {
       // (the tail's offset goes to the vector operand, which alone must not be
       // negative for the bounds check: the first row's would be)
@@ -401,8 +375,9 @@ struct SgRows {
       const uint32_t so = kb == tail ? 0u : static_cast<uint32_t>(kb * SG_K * 4);
 #pragma unroll
       for (int t = 0; t < MT; ++t) {
-        const float4 u = buf_f32x4_s(xs, roff[t] + at, so);
-        const float4 v = buf_f32x4_s(xs, roff[t] + at + 16, so);
+        const uint32_t off = (roff[t] + at) | dead;
+        const float4 u = buf_f32x4_s(xs, off, so);
+        const float4 v = buf_f32x4_s(xs, off + 16, so);
         x[t][0] = u.x; x[t][1] = u.y; x[t][2] = u.z; x[t][3] = u.w;
         x[t][4] = v.x; x[t][5] = v.y; x[t][6] = v.z; x[t][7] = v.w;
       }
@@ -434,12 +409,13 @@ __device__ __forceinline__ void sg_feature(int f, int d, uint32_t& foff, int& sh
   foff = static_cast<uint32_t>(at * 4);
 }
 template <int MT>
-__device__ __forceinline__ void sg_load_cols(__amdgpu_buffer_rsrc_t xs, const uint32_t* srow, uint32_t foff, float (&x)[MT][8]) {
+__device__ __forceinline__ void sg_load_cols(__amdgpu_buffer_rsrc_t xs, const uint32_t* srow, uint32_t foff, float (&x)[MT][8],
+                                             uint32_t dead = 0) {
   static_assert(MT == 1 || MT == 2 || MT == 4, "features per lane");
   const sg_u32x4 o[2] = {*reinterpret_cast<const sg_u32x4*>(srow), *reinterpret_cast<const sg_u32x4*>(srow + 4)};
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const uint32_t off = o[e >> 2][e & 3] + foff;
+    const uint32_t off = (o[e >> 2][e & 3] + foff) | dead;
     if constexpr (MT == 1) {
       x[0][e] = buf_f32(xs, off);
     } else if constexpr (MT == 2) {
