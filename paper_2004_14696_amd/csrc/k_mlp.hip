@@ -462,9 +462,11 @@ hipError_t launch_dw1(const MlpPlan& p, const MlpArgs& a, hipStream_t s) {
   };
   const int64_t w16 = (int64_t)a.n * chunks * ((a.d + 15) / 16);
   // one feature a lane, or two (half the reads of dA) from 16384 tiles of 16
-  // features on: 32 x 64 x 784 x 512 (6272 tiles) 19.5 / 21.9 us, 16 x 256 x 3072 x
-  // 1024 (24576) 135 / 119, 16 x 500 x 800 x 500 (3200) 44.7 / 42.3
-  if (a.d < 2 || (w16 < 16384 && kblocks < 8)) go(k_mlp_dw1<1, NT, 4, 2>, 64);
+  // features on, with more than 7 slices of rows from 2048 on: 32 x 64 x 784 x 512
+  // (6272 tiles) 19.5 / 21.9 us, 16 x 256 x 3072 x 1024 (24576) 135 / 119, 16 x 500 x 800 x
+  // 500 (3200, 16 slices) 44.7 / 42.3; the whole call 18 x 495 x 440-492-7 (2016, 16)
+  // 97 / 109
+  if (a.d < 2 || w16 < 2048 || (w16 < 16384 && kblocks < 8)) go(k_mlp_dw1<1, NT, 4, 2>, 64);
   else go(k_mlp_dw1<2, NT, 4, 3>, 128);
   return hipGetLastError();
 }
@@ -488,9 +490,15 @@ MlpPlan mlp_plan(int n, int B, int d, int H, int C) {
   if (p.rows_per_slab > 1024) p.rows_per_slab = 1024;
   p.slabs = (B + p.rows_per_slab - 1) / p.rows_per_slab;
   // column tiles: of the hidden layer's W1 fragments, and of dA's (chunks of
-  // equal width, up to 8 tiles)
-  const int need = (H + 15) / 16, chunks = (need + 7) / 8;
+  // equal width, up to 8 tiles; narrower ones where they would leave the chip
+  // idle: 7 x 406 x 172-108-9, 77 tiles of 7 columns or 308 of 2: 41.8 / 31.2 us)
+  const int need = (H + 15) / 16;
+  int chunks = (need + 7) / 8;
   p.nt = (need + chunks - 1) / chunks;
+  while (p.nt > 2 && (int64_t)n * chunks * ((d + 15) / 16) < 256) {
+    p.nt = (p.nt + 1) / 2;
+    chunks = (need + p.nt - 1) / p.nt;
+  }
   p.tiles = p.nt * chunks;
   p.wtiles = (need + 7) / 8 * 8;
   p.w_bytes = sg_frag_bytes((d + SG_K - 1) / SG_K, p.wtiles);

@@ -540,7 +540,7 @@ __global__ __launch_bounds__(256) void k_slab_reduce_tiles(SoftmaxArgs a, int sl
 // The rows of the logits product are padded per worker to whole tiles of 16
 // (tpw tiles), so that a tile's residuals belong to one worker's fragments.
 
-constexpr int SG_DIRECT = 4;   // up to so many column tiles a K-split wave reads W itself
+constexpr int SG_DIRECT = 4;   // up to so many column tiles a K-split wave always reads W itself
 
 // Z[m][c] = sum_j X[row(m)][j] W[j][c] on MT x NT tiles of 16 x 16 per wave;
 // blockIdx.x = NW MT row tiles, blockIdx.y = NT column tiles.  NARROW: all
@@ -552,8 +552,9 @@ constexpr int SG_DIRECT = 4;   // up to so many column tiles a K-split wave read
 // minibatch).  256 x 512 x 3072 x
 // 100: 430 - 475 us (fp32 matrix-core form 629), 1.6 GB of X at 3.4 - 3.7 TB/s
 // and 1.1 - 1.3 PFLOP/s of issued bf16 products, both near what the chip holds.
+// DIRECT (KS): W itself, not its fragments.
 template <int MT, int NT, int NW, int OCC, bool KS, bool NARROW, bool TINY = false,
-          bool PER_ROW = false>
+          bool PER_ROW = false, bool DIRECT = (NT <= SG_DIRECT)>
 __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int tiles, int tpw) {
   __shared__ std::conditional_t<KS, SgRed<MT, NT, NW>, SgLds<NT, NW>> L;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
   {
     auto prep = [&](int kb, float (&x)[MT][8]) { X.prep(kb, x); };
     auto frag = [&](int kb) { return a.Wp + sg_frag(kb, tiles, nt0, 0) * 64; };
-    if constexpr (KS && NT <= SG_DIRECT)
+    if constexpr (KS && DIRECT)
       sg_loop_k<true, MT, NT, NW>(L, 0, X.slices(), X, prep, SgMatrix<NT>(make_rsrc(a.W, static_cast<uint32_t>((int64_t)d * C * 4)), C, nt0 * 16), acc);
     else if constexpr (KS)
       sg_loop_k<true, MT, NT, NW>(L, 0, X.slices(), X, prep, SgFrags<NT>{frag(0), (int64_t)tiles * 192}, acc);
@@ -661,11 +662,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         const float v[4] = {acc[nt][t][0], acc[nt][t][1], acc[nt][t][2], acc[nt][t][3]};
-        sg_store4(rp, tiles, b0, nt * 16 + c, v);
-        if (bt + 1 == tpw && (bt & 1) == 0) {   // the slice's other 16 rows do not exist
-          const float z[4] = {0.f, 0.f, 0.f, 0.f};
-          sg_store4(rp, tiles, b0 + 16, nt * 16 + c, z);
-        }
+        sg_store4(rp, tiles, b0, nt * 16 + c, v);   // (rows past the last tile stay as they were created, zero)
       }
     }
   }
@@ -675,7 +672,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
 // minibatches' rows (ZROWS_BATCH) or of the dataset's rows (ZROWS_DATASET: the
 // row of sample m is its dataset row), of which the row softmax is taken here,
 // or the dataset rows' residuals (ZROWS_RESIDUAL, with ce_row).  Block (x, i):
-// rows 8 x .. 8 x + 7 of worker i (padded to whole slices of 32), held in LDS;
+// rows 8 x .. 8 x + 7 of worker i (fragments past the B rows, up to whole slices
+// of 32, stay as they were created, zero), held in LDS;
 // every wave runs two rows' statistics and leaves their exponentials, then
 // packs a quarter of the columns.
 enum ZRows { ZROWS_BATCH, ZROWS_DATASET, ZROWS_RESIDUAL };
@@ -687,7 +685,7 @@ __global__ __launch_bounds__(256) void k_rows_pack(SoftmaxArgs a, int tiles, int
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int i = blockIdx.y, b0 = static_cast<int>(blockIdx.x) * 8;
   const int C = a.C, B = a.B;
-  const int nr = max(0, min(8, B - b0)), nz = nr * C;
+  const int nr = min(8, B - b0), nz = nr * C;
   if (FROM != ZROWS_BATCH) {
     if (tid < nr) {
       const int64_t row = sample_row(a, i, b0 + tid, true);
@@ -874,7 +872,7 @@ hipError_t launch_split_nt(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rt + per - 1) / per), chunks), dim3(threads), 0, s, al, tiles, ltpw);
   };
   auto pack = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(4 * kblocks, a.n), dim3(256), 8 * sizeof(float) * a.C, s, a, tiles, kblocks);
+    hipLaunchKernelGGL(kernel, dim3((a.B + 7) / 8, a.n), dim3(256), 8 * sizeof(float) * a.C, s, a, tiles, kblocks);
   };
   // Waves per SIMD of the large logits blocks: as many as leave no spills.
   constexpr int OC8 = NT >= 4 ? 2 : 4;
@@ -891,7 +889,12 @@ hipError_t launch_split_nt(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream
   enum { kLarge, kMiddle, kSplitK, kTiny };
   const int lv = a.d < 8 ? kTiny : rt * chunks >= 8192 || rt * chunks * NT >= 20000 ? kLarge
                  : rt * chunks > 512 || per_row ? kMiddle : kSplitK;
-  if (lv != kSplitK || NT > SG_DIRECT) {
+  // Wide K-split waves read W itself while the rows are few (row tiles times
+  // slices): the packing launch is saved, the loads and splits of W are more.  us,
+  // fragments / W: 15 x 29 x 204 x 308 (210) 22.4 / 20.4, 8 x 17 x 752 x 309 (384) 28.3 / 26.9,
+  // 6 x 155 x 460 x 796 (900) 49.1 / 56.5, 10 x 91 x 2208 x 720 (4140) 95 / 124.
+  const bool direct = lv == kSplitK && (NT <= SG_DIRECT || rt * ((a.d + SG_K - 1) / SG_K) <= 400);
+  if (!direct) {
     const int64_t wtasks = (int64_t)((a.d + SG_K - 1) / SG_K) * tiles;
     hipLaunchKernelGGL(k_sg_pack, dim3(static_cast<unsigned>((wtasks + 3) / 4)), dim3(256), 0, s, a.W, (int64_t)a.C, int64_t{1}, a.d,
                        a.C, tiles, a.Wp);
@@ -904,11 +907,13 @@ hipError_t launch_split_nt(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream
     if (lv == kLarge) logits(k_sg_logits<2, NT, 8, OC8, false, true>, 16, 512);
     else if (lv == kMiddle) logits(k_sg_logits<1, NT, 4, 2, false, true>, 4, 256);
     else if (lv == kTiny) logits(k_sg_logits<1, NT, 4, 2, false, true, true>, 4, 256);
+    else if (direct) logits(k_sg_logits<1, NT, 8, 2, true, true, false, false, true>, 1, 512);
     else logits(k_sg_logits<1, NT, 8, 2, true, true>, 1, 512);
   } else {
     if (lv == kLarge) logits(k_sg_logits<2, NT, 8, OC8, false, false>, 16, 512);
     else if (lv == kMiddle) logits(k_sg_logits<1, NT, 4, 2, false, false>, 4, 256);
     else if (lv == kTiny) logits(k_sg_logits<1, NT, 4, 2, false, false, true>, 4, 256);
+    else if (direct) logits(k_sg_logits<1, NT, 8, 2, true, false, false, false, true>, 1, 512);
     else logits(k_sg_logits<1, NT, 8, 2, true, false>, 1, 512);
     if (per_row) pack(k_rows_pack<ZROWS_DATASET>);
     else pack(k_rows_pack<ZROWS_BATCH>);

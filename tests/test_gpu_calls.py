@@ -154,6 +154,7 @@ SPLIT_SHAPES = [
     (1, 1025, 37, 19, 600), (2, 1100, 785, 10, 900), (16, 100, 785, 10, 2000), (9, 200, 190, 37, 0),
     (40, 512, 97, 20, 0), (300, 16, 515, 100, 4000), (130, 1024, 10, 97, 5000), (64, 40, 1030, 130, 0),
     (3, 24, 130, 4096, 100), (256, 16, 1027, 7, 900), (200, 12, 3070, 11, 0), (600, 32, 2051, 20, 700),
+    (4, 19, 140, 211, 50), (8, 24, 196, 856, 90), (6, 155, 460, 796, 0), (4, 20, 65, 100, 60), (3, 33, 90, 128, 0), (13, 58, 176, 372, 80),
 ]
 
 
@@ -316,6 +317,7 @@ MLP_SPLIT_SHAPES = [
     (2, 5, 1, 17, 3, 9), (2, 30, 7, 33, 10, 40), (3, 33, 8, 16, 2, 7), (2, 17, 31, 130, 16, 0), (1, 1030, 65, 48, 4, 500),
     (6, 19, 836, 784, 8, 0), (10, 499, 381, 135, 10, 3000), (40, 100, 1023, 1001, 3, 900), (32, 64, 784, 512, 10, 2000),
     (16, 256, 515, 1024, 10, 0), (200, 12, 130, 100, 5, 300),
+    (7, 406, 172, 108, 9, 500), (18, 495, 440, 492, 7, 0), (2, 300, 33, 200, 4, 90),
 ]
 
 
