@@ -453,16 +453,18 @@ __global__ __launch_bounds__(256, 1) void k_cnn_conv2_pool(CnnArgs a) {
       buf ^= 1;
     }
     const bool have = b < nB;
-    sg_redo<4, NT>(acc, [&](int mt, int r, int nt) {
-      const int m = 16 * mt + 4 * g + r, o = 16 * (nt0 + nt) + c;
-      if (!have || o >= NC2) return 0.f;
-      const float* x = a.H1 + (int64_t)b * H1LEN + (m / O2) * Q1 + m % O2;
-      const float* w = a.w + a.off_c2 + o * K2;
-      float s = 0.f;
-      for (int ch = 0; ch < NC1; ++ch)
-        for (int t = 0; t < 25; ++t) s = fmaf(x[ch * NPOS1 + t / KS * Q1 + t % KS], w[ch * 25 + t], s);
-      return s;
-    });
+    // (K index 20 tap + channel, the order of k_cnn_conv2_close)
+    sg_redo<4, NT>(
+        acc, K2,
+        [&](int mt, int k) {
+          const int t = k / NC1, ch = k % NC1;
+          return a.H1[(int64_t)(have ? b : 0) * H1LEN + ch * NPOS1 + (2 * mt + (c >> 3) + t / KS) * Q1 + (c & 7) + t % KS];
+        },
+        [&](int nt, int k) {
+          const int o = 16 * (nt0 + nt) + c;
+          const float v = a.w[a.off_c2 + min(o, NC2 - 1) * K2 + k % NC1 * 25 + k / NC1];
+          return o < NC2 ? v : 0.f;
+        });
     uint64_t close = 0;   // windows decided within rounding (k_cnn_conv2_close)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -513,13 +515,14 @@ __global__ __launch_bounds__(256, 2) void k_cnn_dfeat(CnnArgs a) {
   sg_loop<true, MT, DF_NT, 4, 2>(
       L, 0, A.slices(), A, [&](int kb, float (&x)[MT][8]) { A.prep(kb, x); },
       [&](int kb) { return a.Wp + sg_frag(kb, DF_TILES, nt0, 0) * 64; }, acc);
-  sg_redo<MT, DF_NT>(acc, [&](int t, int r, int nt) {
-    const int m = m0 + 16 * t + 4 * g + r, f = (nt0 + nt) * 16 + c;
-    if (m >= nB) return 0.f;
-    float s = 0.f;
-    for (int h = 0; h < H; ++h) s = fmaf(a.dA[(int64_t)m * H + h], a.w[(int64_t)f * H + h], s);
-    return s;
-  });
+  sg_redo<MT, DF_NT>(
+      acc, H,
+      [&](int t, int k) {
+        const int m = m0 + 16 * t + c;
+        const float v = a.dA[(int64_t)min(m, nB - 1) * H + k];
+        return m < nB ? v : 0.f;
+      },
+      [&](int nt, int k) { return a.w[(int64_t)((nt0 + nt) * 16 + c) * H + k]; });
 #pragma unroll
   for (int t = 0; t < MT; ++t)
 #pragma unroll

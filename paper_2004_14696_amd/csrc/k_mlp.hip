@@ -104,14 +104,18 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_mlp_hidden(MlpArgs a, int tile
       sg_loop<true, MT, NT, NW, 2>(L, 0, X.slices(), X, prep, [&](int kb) { return a.Wp + sg_frag(kb, tiles, nt0, 0) * 64; }, acc);
   }
   if (KS && wv > 0) return;
-  sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
-    const int m = m0 + 16 * t + 4 * g + r, h = (nt0 + nt) * 16 + c;
-    if (m >= Mrows || h >= H) return 0.f;
-    const float* x = a.X + mlp_row(a, m, false) * d;
-    float s = 0.f;
-    for (int j = 0; j < d; ++j) s = fmaf(x[j], a.w[(int64_t)j * H + h], s);
-    return s;
-  });
+  sg_redo<MT, NT>(
+      acc, d,
+      [&](int t, int k) {
+        const int m = m0 + 16 * t + c;
+        const float v = a.X[mlp_row(a, min(m, Mrows - 1), false) * d + k];
+        return m < Mrows ? v : 0.f;
+      },
+      [&](int nt, int k) {
+        const int h = (nt0 + nt) * 16 + c;
+        const float v = a.w[(int64_t)k * H + min(h, H - 1)];
+        return h < H ? v : 0.f;
+      });
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     const int h = (nt0 + nt) * 16 + c;
@@ -201,13 +205,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_mlp_dw1(MlpArgs a, int slabs, 
         [&](int, float (&x)[MT][8]) { sg_shift<MT>(shift, edge, x); },
         [&](int kb) { return dp + sg_frag(kb, tiles, nt0, 0) * 64; }, acc);
   }
-  sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
-    const int j = f0 + MT * (4 * g + r) + t, h = (nt0 + nt) * 16 + c;
-    if (j >= d || h >= H) return 0.f;
-    float s = 0.f;
-    for (int b = 0; b < B; ++b) s = fmaf(a.X[mlp_row(a, i, b, false) * d + j], sg_unpack(dp, tiles, b, h), s);
-    return s;
-  });
+  sg_redo<MT, NT>(
+      acc, B,
+      [&](int t, int b) {
+        const int j = f0 + MT * c + t;
+        const float v = a.X[mlp_row(a, i, b, false) * d + min(j, d - 1)];
+        return j < d ? v : 0.f;
+      },
+      [&](int nt, int b) { return sg_unpack(dp, tiles, b, (nt0 + nt) * 16 + c); });
   // the G rows of workers outside the row mask are computed but not stored
   if (a.row_mask && !a.row_mask[i]) return;
   float* Gi = a.G + (int64_t)i * P;

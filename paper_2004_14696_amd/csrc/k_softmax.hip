@@ -540,6 +540,10 @@ __global__ __launch_bounds__(256) void k_slab_reduce_tiles(SoftmaxArgs a, int sl
 // The rows of the logits product are padded per worker to whole tiles of 16
 // (tpw tiles), so that a tile's residuals belong to one worker's fragments.
 
+// The residuals (at most 1) are packed 2^32 times as large: all their bits down
+// to the least float then fit the three parts; the gradient's sums are brought
+// back at the end, exactly.
+constexpr float kResidualScale = 0x1p32f;
 constexpr int SG_DIRECT = 4;   // up to so many column tiles a K-split wave always reads W itself
 
 // Z[m][c] = sum_j X[row(m)][j] W[j][c] on MT x NT tiles of 16 x 16 per wave;
@@ -591,14 +595,19 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
       sg_loop<(MT == 1 && NT <= 4), MT, NT, NW, MT == 1 ? 2 : 1>(L, 0, X.slices(), X, prep, frag, acc);
   }
   if (KS && wv > 0) return;
-  sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
-    const int i = (t0 + t) / tpw, b = (t0 + t) % tpw * 16 + 4 * g + r, cc = (nt0 + nt) * 16 + c;
-    if (i >= a.n || b >= B || cc >= C) return 0.f;
-    const float* x = a.X + sample_row(a, i, b, false) * d;
-    float s = 0.f;
-    for (int j = 0; j < d; ++j) s = fmaf(x[j], a.W[(int64_t)j * C + cc], s);
-    return s;
-  });
+  sg_redo<MT, NT>(
+      acc, d,
+      [&](int t, int k) {
+        const int i = (t0 + t) / tpw, b = (t0 + t) % tpw * 16 + c;
+        const bool ok = i < a.n && b < B;
+        const float v = a.X[sample_row(a, ok ? i : 0, ok ? b : 0, false) * d + k];
+        return ok ? v : 0.f;
+      },
+      [&](int nt, int k) {
+        const int cc = (nt0 + nt) * 16 + c;
+        const float v = a.W[(int64_t)k * C + min(cc, C - 1)];
+        return cc < C ? v : 0.f;
+      });
 
   if (NARROW) {
 #pragma unroll
@@ -661,7 +670,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_logits(SoftmaxArgs a, int t
       sg_u32x4* rp = a.Rp + (int64_t)i * ((tpw + 1) / 2) * tiles * 3 * 64;
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        const float v[4] = {acc[nt][t][0], acc[nt][t][1], acc[nt][t][2], acc[nt][t][3]};
+        const float v[4] = {acc[nt][t][0] * kResidualScale, acc[nt][t][1] * kResidualScale, acc[nt][t][2] * kResidualScale,
+                            acc[nt][t][3] * kResidualScale};
         sg_store4(rp, tiles, b0, nt * 16 + c, v);   // (rows past the last tile stay as they were created, zero)
       }
     }
@@ -752,6 +762,7 @@ __global__ __launch_bounds__(256) void k_rows_pack(SoftmaxArgs a, int tiles, int
       if (e < nr && c < C)
         v[e] = FROM == ZROWS_RESIDUAL ? zrow[e * C + c]
                                       : (zrow[e * C + c] * sh_inv[e] - (c == sh_lab[e] ? 1.f : 0.f)) * invB;
+      v[e] *= kResidualScale;
     }
     sg_store8(rp, tiles, b0, c, v);
   }
@@ -803,13 +814,18 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_grads(SoftmaxArgs a, int ti
     else
       sg_loop<MT == 1, MT, NT, NW, MT == 1 ? 2 : 1>(L, c0 / SG_K, c0 / SG_K + nb, load, prep, frag, acc);
   }
-  sg_redo<MT, NT>(acc, [&](int t, int r, int nt) {
-    const int j = f0 + MT * (4 * g + r) + t, cc = (nt0 + nt) * 16 + c;
-    if (j >= d || cc >= C) return 0.f;
-    float s = 0.f;
-    for (int b = 0; b < B; ++b) s = fmaf(a.X[sample_row(a, i, b, false) * d + j], sg_unpack(rp, tiles, b, cc), s);
-    return s;
-  });
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) acc[nt][t] *= 1.f / kResidualScale;
+  sg_redo<MT, NT>(
+      acc, B,
+      [&](int t, int b) {
+        const int j = f0 + MT * c + t;
+        const float v = a.X[sample_row(a, i, b, false) * d + min(j, d - 1)];
+        return j < d ? v : 0.f;
+      },
+      [&](int nt, int b) { return sg_unpack(rp, tiles, b, (nt0 + nt) * 16 + c) * (1.f / kResidualScale); });
   // the G rows of workers outside the row mask are computed but not stored
   if ((!KS || wv == 0) && (!a.row_mask || a.row_mask[i])) {
     float* Gi = a.G + (int64_t)i * d * C;

@@ -1,13 +1,14 @@
 // fp32 products on the bf16 matrix cores: the operands in three bf16 parts.
 //
-// An fp32 value is the exact sum of three bf16 values, x = h + m + l (h = x
-// rounded to bf16, m = x - h rounded, l the rest: 8 + 8 + 8 significant bits),
-// over the whole fp32 range, since bf16 has fp32's exponents.  A product is
-// formed from the six partial products h h', h m', m h', h l', m m', l h', each
+// An fp32 value is the sum of three bf16 values, x = h + m + l (h = x rounded to
+// bf16, m = x - h rounded, l the rest: 8 + 8 + 8 significant bits).  It is exact from
+// 2^-110 up; below, l runs out of bf16's subnormals (which the matrix cores
+// honour) and x is off by up to 2^-134: 2^-24 of it at 2^-110, 2^-14 at 2^-120.  A product
+// is formed from the six partial products h h', h m', m h', h l', m m', l h', each
 // exact in the fp32 accumulator's input; the dropped ones (m l', l m', l l')
 // are below 2^-26 of it, less than the rounding of one fp32 addition.  The
-// fp32 instruction v_mfma_f32_16x16x4 does 64 multiply-adds a cycle, the bf16
-// one (16x16x32) 512 by six products = 85, at a third fewer roundings of the
+// fp32 instruction v_mfma_f32_16x16x4 does 32 multiply-adds a cycle, the bf16
+// one (16x16x32) 512 by six products = 85, at a quarter fewer roundings of the
 // accumulator; on this part the fp32 instruction also excludes vector work,
 // the bf16 one does not.
 //
@@ -17,12 +18,17 @@
 // block copies to LDS a slice of 32 K at a time; its NW waves, stacked along
 // M, share them.  Lane l = 16 g + c of v_mfma_f32_16x16x32_bf16 holds A row
 // c, K 8 g .. 8 g + 7; B column c, the same K; accumulator element r is row
-// 4 g + r, column c.
+// 4 g + r, column c (the fp32 instruction's too).
 //
 // Infinities and values that round to infinity in bf16 have no such parts
-// (inf - inf): an accumulator that is not finite is computed again as a plain
-// fp32 dot product by its lane (sg_redo), so those inputs give what fp32
-// arithmetic gives.
+// (inf - inf), and sums of very small products may be made of operands below
+// 2^-110.  An accumulator that is not finite, or below 2^-90, is formed again with
+// the fp32 instruction (sg_redo), so those inputs give what fp32 arithmetic
+// gives.  A larger sum is off by at most K 2^-134 times the other operand's
+// largest value for such operands: less than fp32's own rounding while that
+// product is below 2^20.  (The packed operand of a sum formed again is its
+// parts': the softmax's residuals are scaled so that these are exact; dA of the
+// MLP is held to 2^-134.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -444,36 +450,61 @@ __device__ __forceinline__ void sg_shift(int shift, bool edge, float (&x)[MT][8]
   }
 }
 
-// Accumulators that are not finite: dot(mt, r, nt) gives the lane's element
-// again in fp32.  One addition per accumulator when all are finite.
-template <int MT, int NT, class Dot>
-__device__ __forceinline__ void sg_redo(sg_f32x4 (&acc)[NT][MT], Dot&& dot) {
-  float s = 0.f;
+// A sum that its parts may not hold: not finite, or not zero and below 2^-90.
+__device__ __forceinline__ bool sg_doubtful(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v) & 0x7fffffffu;   // [2^-90, infinity) is [0x12800000, 0x7f800000)
+  return u - 0x12800000u >= 0x7f800000u - 0x12800000u && u != 0;
+}
+
+// Doubtful accumulators are formed again with the fp32 matrix instruction, a
+// tile at a time: ea(mt, k) is A of the lane's row c of tile mt at K index k, eb(nt, k)
+// B of the lane's column c of column tile nt (k < K; 0 where there is no row or
+// column).  2.5 instructions per accumulator when none is doubtful.  (A
+// scalar dot product in each lane took 30 - 170 times the whole launch where a NaN
+// has reached the parameters: 32 x 128 x 2048 x 1000 41 ms, now 3.3 (0.39 on fp32
+// products throughout); 24 x 200 x 1000 x 37 1.9, now 0.16 (0.13).)
+template <int MT, int NT, class Ea, class Eb>
+__device__ __forceinline__ void sg_redo(sg_f32x4 (&acc)[NT][MT], int K, Ea&& ea, Eb&& eb) {
+  float s = 0.f;             // NaN if one is not finite
+  uint32_t least = ~0u;      // the least 2 |bits| - 1 (zeros: the largest value)
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) s = fmaf(acc[nt][mt][r], 0.f, s);
-  if (__builtin_amdgcn_ballot_w64(s != s) == 0) return;
+      for (int r = 0; r < 4; ++r) {
+        s = fmaf(acc[nt][mt][r], 0.f, s);
+        least = min(least, (__builtin_bit_cast(uint32_t, acc[nt][mt][r]) << 1) - 1u);
+      }
+  if (__builtin_amdgcn_ballot_w64(s != s || least < 2u * 0x12800000u - 1u) == 0) return;
+  const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      bool bad = false;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bad |= sg_doubtful(acc[nt][mt][r]);
+      if (__builtin_amdgcn_ballot_w64(bad) == 0) continue;
+      sg_f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-  for (int e = 0; e < NT * MT * 4; ++e) {
-    float v = 0.f;
+      for (int k0 = 0; k0 < K; k0 += 16) {
+        float x[4], y[4];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+        for (int q = 0; q < 4; ++q) {
+          // (loads of the last k past K, whose values are dropped: no branches)
+          const int k = k0 + 4 * q + g, kc = min(k, K - 1);
+          x[q] = ea(mt, kc);
+          y[q] = eb(nt, kc);
+          x[q] = k < K ? x[q] : 0.f;
+          y[q] = k < K ? y[q] : 0.f;
+        }
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+        for (int q = 0; q < 4; ++q) z = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], y[q], z, 0, 0, 0);
+      }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v = (nt * MT + mt) * 4 + r == e ? acc[nt][mt][r] : v;
-    const float z = v * 0.f;
-    if (z != z) v = dot((e >> 2) % MT, e & 3, (e >> 2) / MT);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[nt][mt][r] = (nt * MT + mt) * 4 + r == e ? v : acc[nt][mt][r];
-  }
+      for (int r = 0; r < 4; ++r) acc[nt][mt][r] = sg_doubtful(acc[nt][mt][r]) ? z[r] : acc[nt][mt][r];
+    }
 }
 
 // Element (k, n) of a packed operand, put together again.

@@ -247,10 +247,25 @@ def test_worker_loss_cnn_image_counts(n, B):
     # rounding through sums of 25, 500, 800 and 40 terms
     tol = 2.0 ** -23 * (8 + 25 ** 0.5 + 500 ** 0.5 + 800 ** 0.5 + 40 ** 0.5)
     assert rel_err(host(run(X)), want.numpy()) <= tol
-    # an infinite pixel stays in its own worker (whose loss may be anything: a
-    # pooled NaN passes the ReLU as 0)
+    # an infinite pixel stays in its own worker, whose loss is what fp32 arithmetic
+    # gives: a window passes its first entry unless a later one is larger, so a
+    # NaN passes where it is first; the ReLU of NaN is 0
     X[-1, B // 2, 300] = float("inf")
     loss = host(run(X))
+    def pool(Z):
+        best = Z[:, :, 0::2, 0::2]
+        for p, q in ((0, 1), (1, 0), (1, 1)):
+            e = Z[:, :, p::2, q::2]
+            best = torch.where(e > best, e, best)
+        return torch.where(best > 0, best, torch.zeros_like(best))
+    h = X[-1].double().cpu().reshape(-1, 1, 28, 28)
+    h = pool(F.conv2d(h, K1.reshape(20, 1, 5, 5), c1))
+    h = pool(F.conv2d(h, K2.reshape(50, 20, 5, 5), c2)).reshape(B, 800)
+    h = h @ W1.reshape(800, 40) + b1
+    h = torch.where(h > 0, h, torch.zeros_like(h))
+    z = h @ W2.reshape(40, 10) + b2
+    bad = float(F.cross_entropy(z, y[-1].long().cpu())) if bool(torch.isfinite(z).all()) else float("nan")
+    assert np.isnan(loss[-1]) if np.isnan(bad) else abs(loss[-1] - bad) <= tol * bad
     if n > 1:
         assert rel_err(loss[:-1], want.numpy()[:-1]) <= tol
 
@@ -387,6 +402,111 @@ def test_worker_grads_softmax_non_finite_inputs(n, B, d, C):
         assert abs(loss[i] - lo[0]) <= 1e-5 * abs(lo[0])
         err = np.abs(G[i][:, keep] - Go)
         assert np.all(err <= 1e-5 * np.max(np.abs(Go), axis=1, keepdims=True)), i
+
+
+# Operands and results near the least floats, where the low parts of the split
+# products run out: a class of probability e^-85 in every row (its residuals are
+# below 1e-38), and features of about 1e-36.  K split over waves, one and
+# two row tiles, several column chunks, one to four features a lane.
+@pytest.mark.parametrize("n,B,d,C", [(3, 20, 40, 20), (2, 33, 77, 130), (40, 300, 45, 12), (256, 16, 65, 50), (128, 64, 4100, 18)])
+def test_worker_grads_softmax_tiny_operands(n, B, d, C):
+    rng = np.random.default_rng(n + d)
+    X = (rng.random((n, B, d), dtype=np.float32) + np.float32(0.1))
+    X[:, :, 0] = 1
+    W = (0.1 / d ** 0.5 * rng.standard_normal((d, C))).astype(np.float32)
+    W[0, 3] = -85
+    y = rng.integers(4, C, size=(n, B), dtype=np.int32)
+    ctx = _ctx(n, B, d, C)
+    yd = to_dev(torch, y)
+    G, _ = ctx.worker_grads(to_dev(torch, W.ravel()), to_dev(torch, X), yd)
+    ctx.sync()
+    # the class's logits are rounded to 85 x 2^-24 a few times, which are relative
+    # errors of its probability; values below 2^-126 are multiples of 2^-149
+    tol = 85 * 2.0 ** -24 * (4 + d ** 0.5)
+    for i in sorted({0, n // 2, n - 1}):
+        Go, _ = omodel.softmax_worker_grads(W.astype(np.float64).ravel(), X[i:i + 1].astype(np.float64), y[i:i + 1], C)
+        a, o = host(G)[i].reshape(d, C)[:, 3].astype(np.float64), Go.reshape(d, C)[:, 3]
+        assert 0 < np.max(o) < 1e-36
+        assert np.all(np.abs(a - o) <= tol * o + 2.0 ** -149 * (B ** 0.5 + 4)), (i, np.max(np.abs(a - o) / o))
+    Xs = (X * np.float32(1e-36)).astype(np.float32)
+    G, _ = ctx.worker_grads(to_dev(torch, W.ravel()), to_dev(torch, Xs), yd)
+    ctx.sync()
+    tol = 2.0 ** -23 * (8 + d ** 0.5 + B ** 0.5)
+    for i in sorted({0, n // 2, n - 1}):
+        Go, _ = omodel.softmax_worker_grads(W.astype(np.float64).ravel(), Xs[i:i + 1].astype(np.float64), y[i:i + 1], C)
+        assert rel_err(host(G)[i].astype(np.float64) * 1e36, Go[0] * 1e36) <= tol, i
+
+
+# (n, B, d, H, C): the hidden layer with K split over waves, 32 and 128 columns a
+# wave; dW1 with one and two features a lane
+MLP_RANGE_SHAPES = [(4, 20, 40, 36, 7), (32, 64, 100, 512, 5), (40, 256, 33, 512, 3), (40, 256, 1030, 512, 4)]
+
+
+@pytest.mark.parametrize("n,B,d,H,C", MLP_RANGE_SHAPES)
+def test_worker_grads_mlp_tiny_features(n, B, d, H, C):
+    # features of about 1e-36, no hidden bias: hidden values, dW1 and dW2 are of
+    # that size, and the ReLUs do not depend on it
+    rng = np.random.default_rng(n + d + H)
+    X = rng.random((n, B, d), dtype=np.float32)
+    W1 = (rng.standard_normal((d, H)) * (2.0 / d) ** 0.5).astype(np.float32)
+    W1 = np.abs(W1) * np.where(np.arange(H) % 3 == 0, np.float32(-1), np.float32(1))   # units all on or all off
+    W2 = (rng.standard_normal((H, C)) * (2.0 / H) ** 0.5).astype(np.float32)
+    y = rng.integers(0, C, size=(n, B), dtype=np.int32)
+    Xs = (X * np.float32(1e-36)).astype(np.float32)
+    w = np.concatenate([W1.ravel(), np.zeros(H), W2.ravel(), np.zeros(C)]).astype(np.float32)
+    ctx = _ctx(n, B, d, C, model="mlp", H=H)
+    G, _ = ctx.worker_grads(to_dev(torch, w), to_dev(torch, Xs), to_dev(torch, y))
+    ctx.sync()
+    tol = 2.0 ** -23 * (16 + d ** 0.5 + H ** 0.5 + B ** 0.5)
+    for i in sorted({0, n // 2, n - 1}):
+        Go, _ = omodel.mlp_worker_grads(w.astype(np.float64), Xs[i:i + 1].astype(np.float64), y[i:i + 1], H, C)
+        for lo, hi in ((0, d * H), (d * H + H, d * H + H + H * C)):
+            assert rel_err(host(G)[i][lo:hi].astype(np.float64) * 1e36, Go[0][lo:hi] * 1e36) <= tol, (i, lo)
+
+
+@pytest.mark.parametrize("n,B,d,H,C", MLP_RANGE_SHAPES)
+def test_worker_grads_mlp_non_finite_inputs(n, B, d, H, C):
+    # A nearly overflowing feature and a unit whose weights are -inf leave finite
+    # results; a NaN feature switches its row's units off (the ReLU of NaN is 0)
+    # and makes its own row of dW1 NaN; an infinite feature makes its worker's loss
+    # NaN; the other workers see none of it.
+    rng = np.random.default_rng(n * B + d)
+    X = rng.random((n, B, d), dtype=np.float32) + np.float32(0.1)
+    W1 = (rng.standard_normal((d, H)) * (2.0 / d) ** 0.5).astype(np.float32)
+    W1 = np.abs(W1) * np.where(np.arange(H) % 3 == 0, np.float32(-1), np.float32(1))   # units all on or all off
+    W1[1] = 0
+    W1[:, 5] = -np.inf
+    W2 = (rng.standard_normal((H, C)) * (2.0 / H) ** 0.5).astype(np.float32)
+    y = rng.integers(0, C, size=(n, B), dtype=np.int32)
+    w = np.concatenate([W1.ravel(), np.zeros(H), W2.ravel(), 0.1 * np.ones(C)]).astype(np.float32)
+    X[0, 0, 1] = 3.4e38
+    X[1, 2, 0] = np.nan
+    X[2, B - 1, d - 1] = np.inf
+    ctx = _ctx(n, B, d, C, model="mlp", H=H)
+    G, loss = ctx.worker_grads(to_dev(torch, w), to_dev(torch, X), to_dev(torch, y))
+    ctx.sync()
+    G, loss = host(G), host(loss)
+    assert np.isnan(loss[2])
+    tol = 2.0 ** -23 * (16 + d ** 0.5 + H ** 0.5 + B ** 0.5)
+    for i in sorted({0, 1, n // 2 + 1, n - 1}):
+        Xi = X[i].astype(np.float64)
+        on = np.tile((np.arange(H) % 3 != 0) & (np.arange(H) != 5), (B, 1))
+        if i == 1:
+            Xi[2, 0], on[2] = 0, False
+        # (a unit that is off enters nothing: any finite weights in its place)
+        Wf = W1.astype(np.float64)
+        Wf[:, 5] = 0
+        wf = np.concatenate([Wf.ravel(), w[d * H:].astype(np.float64)])
+        Go, lo = omodel.mlp_worker_grads(wf, Xi[None], y[i:i + 1], H, C, decisions={"on": on})
+        g1, o1 = G[i][:d * H].reshape(d, H), Go[0][:d * H].reshape(d, H)
+        if i == 1:
+            assert np.all(np.isnan(g1[0])) and not np.isnan(g1[1:]).any()
+            g1, o1 = g1[1:], o1[1:]
+        for a, o in zip(g1, o1):
+            assert np.max(np.abs(a - o)) <= tol * max(np.max(np.abs(o)), 1e-30), i
+        assert rel_err(G[i][d * H:-C], Go[0][d * H:-C]) <= tol, i
+        assert np.max(np.abs(G[i][-C:] - Go[0][-C:])) <= tol, i
+        assert abs(loss[i] - lo[0]) <= tol * abs(lo[0])
 
 
 @pytest.mark.parametrize("n,B,d,C,S", [(4, 32, 784, 10, 500), (6, 40, 3072, 10, 300), (3, 20, 200, 100, 90)])
