@@ -41,7 +41,6 @@ HBM_PEAK_GBS = 8000.0
 # fp32 products on the bf16 matrix cores (dense 2.5 PFLOP/s), six products of
 # bf16 parts each; the fp32 matrix instruction's own peak is 157.3
 MFMA_F32_PEAK_TFLOPS = 2500.0 / 6
-FUSED_MAX_CLASSES = 16         # the single-pass softmax kernel covers C <= 16
 FLUSH_BYTES = 1 << 30          # touched between launches for the cold figures (MALL is 256 MB)
 SETTLE_S = 0.1                 # untimed gradient launches before the timed ones (clock settling)
 
@@ -83,9 +82,27 @@ def grads_bytes(cfg, P: int, gathered: bool) -> int:
     return 4 * (rows * cfg.d + rows + (rows if gathered else 0) + P + cfg.n * P + cfg.n)
 
 
+def grads_route(cfg):
+    """(single pass, slabs, logits per dataset row) of the softmax gradients,
+    as the library says."""
+    from paper_2004_14696_amd import config_from
+    from paper_2004_14696_amd import grads_route as route
+    return route(config_from(cfg, S=cfg.S))
+
+
 def grads_flops(cfg) -> float:
-    """Useful fp32 flops of one worker-gradient launch (no padding): softmax
-    logits X W and gradient X^T R; MLP hidden layer, head forward, head
+    """Useful fp32 flops that one worker-gradient launch executes: those by
+    samples, less the logits of samples that repeat a dataset row where the
+    launch forms every row's logits once."""
+    f = grads_flops_by_samples(cfg)
+    if cfg.model == "softmax" and grads_route(cfg)[2]:
+        f -= 2.0 * (cfg.n * cfg.B - cfg.S) * cfg.d * cfg.C
+    return f
+
+
+def grads_flops_by_samples(cfg) -> float:
+    """Fp32 flops of one worker-gradient launch sample by sample (no padding):
+    softmax logits X W and gradient X^T R; MLP hidden layer, head forward, head
     backward (dW2 and the hidden-unit residuals) and X^T dA.  CNN per image:
     both convolutions forward (24x24x20x25 and 8x8x50x500 products), the
     gradients of the conv2 filters and of its input and of the conv1 filters
@@ -106,7 +123,7 @@ def grads_flops(cfg) -> float:
 def roofline_bound(cfg) -> str:
     """The single-pass softmax kernel streams each row once and is bounded by
     HBM; the two-product GEMM path and the MLP are matrix-core work."""
-    if cfg.model == "softmax" and cfg.C <= FUSED_MAX_CLASSES:
+    if cfg.model == "softmax" and grads_route(cfg)[0]:
         return "hbm"
     return "mfma"
 
@@ -114,9 +131,11 @@ def roofline_bound(cfg) -> str:
 def grads_kernels(cfg) -> str:
     """The kernels one worker-gradient launch runs (names as in the traces)."""
     if cfg.model == "softmax":
-        if cfg.C <= FUSED_MAX_CLASSES:
-            return "k_softmax_mfma + k_slab_reduce_tiles"
-        return "k_sg_pack + k_sg_logits + k_rows_pack + k_sg_grads"
+        single_pass, slabs, per_row = grads_route(cfg)
+        if single_pass:
+            return "k_softmax_mfma" + (" + k_slab_reduce_tiles" if slabs > 1 else "")
+        rows_pack = " + k_rows_pack" if per_row or cfg.C > 128 else ""
+        return f"k_sg_pack (where the logits do not read W itself) + k_sg_logits{rows_pack} + k_sg_grads"
     if cfg.model == "mlp":
         return "k_sg_pack + k_mlp_hidden + k_mlp_head + k_mlp_dw1 (with the head's slab sums)"
     return "k_cnn_* + MLP kernels on the 800 features"
@@ -320,16 +339,6 @@ def time_grads_cold(wl, first: int, steps: int, G, Lb):
     return cold
 
 
-def grads_flops_executed(cfg) -> float:
-    """grads_flops less the logits of samples that repeat a dataset row: with
-    1.5 samples a row or more the softmax GEMM path forms every row's logits
-    once."""
-    f = grads_flops(cfg)
-    if cfg.model == "softmax" and cfg.C > FUSED_MAX_CLASSES and cfg.S >= 8192 and 2 * cfg.n * cfg.B >= 3 * cfg.S:
-        f -= 2.0 * (cfg.n * cfg.B - cfg.S) * cfg.d * cfg.C
-    return f
-
-
 def roofline_block(cfg, P: int, warm_ms: float, cold_ms: float, launches: int) -> dict:
     gb = grads_bytes(cfg, P, True)
     bound = roofline_bound(cfg)
@@ -343,7 +352,8 @@ def roofline_block(cfg, P: int, warm_ms: float, cold_ms: float, launches: int) -
         "kernel": f"worker-gradient launch dbw_worker_grads ({grads_kernels(cfg)}); every G row written",
         "bound": bound, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
         "traffic": measured_traffic(cfg), "bytes_per_launch": gb, "flops_per_launch": grads_flops(cfg),
-        "flops_executed": grads_flops_executed(cfg),
+        "flops_by_samples": grads_flops_by_samples(cfg),
+        "tflops_by_samples": grads_flops_by_samples(cfg) / 1e12 / (warm_ms / 1e3),
         "avg_launch_ms": warm_ms, "launches": launches,
         "cold": {"avg_launch_ms": cold_ms, "achieved": achieved_cold, "frac": achieved_cold / peak,
                  "flush": "1 GiB device buffer read before each launch (untimed)"},

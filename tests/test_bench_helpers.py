@@ -29,6 +29,19 @@ def test_grads_flops_and_bound():
     assert bench.roofline_bound(c5) == "mfma"
 
 
+def test_kernels_and_executed_flops_follow_the_library():
+    # C1, C2: the two products, logits from W itself and all classes in a wave;
+    # C3: the single pass with four slabs; C5: logits once per dataset row
+    c1, c2, c3, c5 = get("C1"), get("C2"), get("C3"), get("C5")
+    for c in (c1, c2):
+        assert "k_sg_logits + k_sg_grads" in bench.grads_kernels(c) and bench.roofline_bound(c) == "mfma"
+        assert bench.grads_flops(c) == bench.grads_flops_by_samples(c)
+    assert bench.grads_kernels(c3) == "k_softmax_mfma + k_slab_reduce_tiles"
+    assert "k_rows_pack" in bench.grads_kernels(c5)
+    assert bench.grads_flops_by_samples(c5) == 4.0 * 256 * 512 * 3072 * 100
+    assert bench.grads_flops(c5) == 2.0 * (256 * 512 + c5.S) * 3072 * 100
+
+
 def _summary(tmp_path, src_rel, digest, value):
     rec = {"kernel_sources_sha256": {src_rel: digest}, "traffic_bytes_per_launch": value}
     p = tmp_path / "traffic.md"
@@ -53,7 +66,7 @@ def test_more_than_one_gpu_is_refused(capsys):
 
 
 def test_roofline_block_warm_and_cold():
-    # C5: 1.61e11 useful flops per launch; 2 ms warm and 2.5 ms cold
+    # C5: 1.11e11 flops executed a launch (1.61e11 by samples); 2 ms warm and 2.5 ms cold
     cfg = get("C5")
     r = bench.roofline_block(cfg, cfg.d * cfg.C, 2.0, 2.5, 20)
     assert r["bound"] == "mfma" and r["unit"] == "TFLOP/s"
