@@ -94,18 +94,21 @@ typedef enum { DBW_ESTIMATOR_ISOTONIC = 0, DBW_ESTIMATOR_NAIVE = 1 } dbw_estimat
 /* Rows of the worker-gradient buffer that dbw_step writes (the PS only uses
  * the k_t fastest gradients, Eq. grad_bw).  ALL: every worker's row (the
  * aggregation then reads the selected ones back).  SELECTED: only the
- * selected workers' rows; NONE: no row.  With SELECTED or NONE, wherever the
- * softmax gradient kernel splits a worker's minibatch into several row slabs,
- * one kernel sums the selected workers' slab partials and aggregates them
- * directly, so the unselected rows are never formed and no row is read back;
- * g_t, the updated w, the losses, k and the mask are bitwise those of ALL,
- * the statistics equal up to the order of their fp64 and fp32 partial sums.
- * Where the gradients come from per-worker GEMM tiles (softmax with more
- * than 16 classes under SELECTED or NONE, the MLP and the CNN under
- * SELECTED), the choice and the selection run before the gradient kernels,
- * which compute every worker's gradient but store only the selected rows;
- * k, the mask, g_t, w, the losses and the statistics are bitwise those of
- * ALL.  Rows not written hold unspecified values after dbw_step.
+ * selected workers' rows; NONE: no row is asked for.  With SELECTED or NONE,
+ * wherever the softmax gradients take the single pass (see dbw_grads_route)
+ * with several row slabs a worker, one kernel sums the selected workers' slab
+ * partials and aggregates them directly, so the unselected rows are never
+ * formed and no row is read back; g_t, the updated w, the losses, k and the
+ * mask are bitwise those of ALL, the statistics equal up to the order of their
+ * fp64 and fp32 partial sums.  Where the gradients come from per-worker GEMM
+ * tiles and P > 131072 (softmax under SELECTED or NONE, the MLP and the CNN
+ * under SELECTED), the choice and the selection run before the gradient
+ * kernels, which compute every worker's gradient but store only the selected
+ * rows; k, the mask, g_t, w, the losses and the statistics are bitwise those
+ * of ALL.  With smaller P every row is formed before the choice: softmax of up
+ * to 16 classes under SELECTED keeps them in a second buffer of n*P floats,
+ * from which the selected rows are copied; elsewhere G itself holds them, also
+ * under NONE.  Rows not written hold unspecified values after dbw_step.
  * dbw_worker_grads always writes every row. */
 typedef enum { DBW_G_ROWS_ALL = 0, DBW_G_ROWS_SELECTED = 1, DBW_G_ROWS_NONE = 2 } dbw_g_rows;
 
@@ -179,7 +182,11 @@ dbw_status dbw_grads_route(const dbw_config* cfg, int32_t* single_pass, int32_t*
  * later calls) and sets the estimator state to its initial value.  Returns
  * DBW_EUNSUPPORTED when one array the kernels address (P floats, the n*B*d
  * minibatch floats, the S*d dataset floats, n*B*C or n*B*H activations)
- * would reach 2 GiB. */
+ * would reach 2 GiB.  Beside G, the workspace of the softmax's two products
+ * holds the residuals as matrix-core fragments, 6 bytes a value with every
+ * worker's rows padded to 32 and the classes to 16 (n = 1024, B = 1, C = 4096:
+ * 805 MB), W likewise, and S*C floats where the dataset's rows share their
+ * logits; the MLP's and the CNN's hidden gradients are held the same way. */
 dbw_status dbw_create(const dbw_config* cfg, void* stream, dbw_ctx** out);
 void dbw_destroy(dbw_ctx* ctx);
 /* Text of the last failure on ctx; with ctx NULL, of the last failed
@@ -200,7 +207,12 @@ dbw_status dbw_sync(dbw_ctx* ctx);
  * [n][B]; else X is the resident dataset DEVICE float [S][d], y its labels
  * DEVICE int32 [S], and rows DEVICE int32 [n][B] lists each worker's row
  * indices into it.  Labels must lie in [0, C).  w, X and G must be 16-byte
- * aligned (DBW_EINVAL otherwise). */
+ * aligned (DBW_EINVAL otherwise).  With rows, all S rows of X and y may be
+ * read, also those in no minibatch (their values do not matter and their
+ * labels are not checked): none may be written meanwhile.  Where the
+ * dataset's rows share their logits (dbw_grads_route), the same minibatches
+ * passed materialised give results that agree to fp32 rounding; elsewhere they
+ * give the same bits. */
 dbw_status dbw_worker_grads(dbw_ctx* ctx, const float* w, const float* X, const int32_t* y,
                             const int32_t* rows, float* G, float* loss);
 
