@@ -859,8 +859,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_sg_grads(SoftmaxArgs a, int ti
 }
 
 // Whether the logits run over the dataset's rows (see launch_split_nt).  Below
-// 1.5 samples a row the gather costs what the shared rows save; below 8192
-// rows (two row tiles a CU) there is nothing to save.
+// 1.5 samples a row the gather costs what the shared rows save.  Below 8192
+// rows (two row tiles a CU) it depends on the work: us of the launch, per
+// sample / per row, 256 x 512 x 3072 x 100 of 4096 rows 897 / 563, 128 x 300 x 256 x 300 of
+// 4000 123 / 90, but 64 x 256 x 784 x 40 of 4000 36.9 / 40.3, 32 x 128 x 500 x 60 of 1500
+// 16.2 / 27.3; those stay with the samples.
 bool split_per_row(int n, int B, int d, int64_t S) {
   return S >= 8192 && d >= 8 && 2 * (int64_t)n * B >= 3 * S;
 }
@@ -898,7 +901,9 @@ hipError_t launch_split_nt(const SoftmaxPlan& p, const SoftmaxArgs& a, hipStream
   // tiles), 16 row tiles a block, which reads its fragments half as often.  us
   // of the launch, the large / middle / K-split form: 256 x 512 x 3072 x 100
   // (8192 tiles) 934 / 1028 / 1641; its logits over 50000 dataset rows (3125
-  // tiles of 7 columns) 216 / 289 / -; 20000 x 500 x 60 (1250) 28 / 17 / -; 128 x
+  // tiles of 7 columns) 216 / 289 / -; 20000 x 500 x 60 (1250) 28 / 17 / -; of the whole
+  // launch, 160 x 256 x 3072 x 100 (2560 of 7) 389 / 395, 170 x 256 x 500 x 112 (2720 of
+  // 7) 84 / 76, 128 x 256 x 1000 x 100 (2048 of 7) 121 / 95; 128 x
   // 512 x 256 x 50 (4096) 51 / 49 / 81; 64 x 256 x 3072 x 100 (1024) 250 / 163 /
   // 209; 32 x 200 x 1024 x 64 (416) 73 / 40 / 36; 16 x 100 x 785 x 20 (112)
   // 40 / 25 / 17.
