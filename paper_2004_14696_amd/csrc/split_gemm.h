@@ -205,11 +205,15 @@ __device__ __forceinline__ void sg_loop(SgLds<NT, NW>& L, int kb0, int kb1, Load
       load(kb, v, 0u);
       return;
     }
-    const __amdgpu_buffer_rsrc_t src = make_rsrc(frag(kb), live ? NT * 3 * 1024u : 0u);
+    // (dead slices by the vector offset: the resource's size, from which the
+    // bounds check takes the scalar offset, stays larger than that)
+    const uint32_t dead = live ? 0u : kOutOfRange;
+    const __amdgpu_buffer_rsrc_t src = make_rsrc(frag(kb), NT * 3 * 1024u);
+    const uint32_t off = static_cast<uint32_t>((wv * 64 + lane) * 16) | dead;
 #pragma unroll
     for (int q = 0; q < NB; ++q)   // (fragments past the slice's NT * 3 read as 0)
-      r[q] = __builtin_bit_cast(sg_u32x4, __builtin_amdgcn_raw_buffer_load_b128(src, (wv * 64 + lane) * 16, q * NW * 1024, 0));
-    load(kb, v, live ? 0u : kOutOfRange);
+      r[q] = __builtin_bit_cast(sg_u32x4, __builtin_amdgcn_raw_buffer_load_b128(src, off, q * NW * 1024, 0));
+    load(kb, v, dead);
   };
   auto stage = [&](int buf, const sg_u32x4 (&r)[NB]) {
 #pragma unroll
