@@ -292,7 +292,7 @@ def test_lockstep_256_workers_100_classes_first_iterations():
 @pytest.mark.timeout(1500)
 def test_lockstep_256_workers_100_classes_full_run_benchmarked_mode():
     # all 50 iterations of the largest workload in the benchmarked mode (the
-    # matrix-core GEMM path writes every row; the PS reads the selected ones);
+    # choice runs first, the gradient kernels store only the selected rows);
     # the oracle takes several seconds per iteration
     orc = _lockstep(C5.replace(g_rows="none"), C5.iters)
     assert len(set(orc.ks)) > 1
